@@ -188,8 +188,7 @@ struct ApplyResult {
 // then the dot and update passes of the argument block.
 static void arnoldi_step(sgn_ctx* c, const KrylovArgs& ka, bool mixed, hipStream_t s, Profiler* prof) {
   if (mixed) {
-    wilson_apply_multi32(c->lat, c->links32, static_cast<const float2*>(ka.ulonext), 0, c->z32, 0, 1, true, s,
-                         prof);
+    wilson_apply32(c->lat, c->links32, static_cast<const float2*>(ka.ulonext), c->z32, s, prof);
     krylov_dot<float2>(c->kw, ka, true, s, prof);
     krylov_update<float2>(c->kw, ka, s, prof);
   } else {
@@ -1227,15 +1226,24 @@ size_t sgn_footprint_bytes(const sgn_ctx* c, int kmax, int nrhs) {
 int sgn_matvec(sgn_ctx* c, const double* x, double* y) {
   return guarded(c, [&] {
     SGN_REQUIRE(x && y && x != y, SGN_EINVAL, "x and y must be distinct non-NULL buffers");
+    Profiler* prof = c->prof.on ? &c->prof : nullptr;
+    if (!overlapping(x, y, (size_t)c->N)) {
+      wilson_apply_abi(c->lat, c->links, reinterpret_cast<const double2*>(x), reinterpret_cast<double2*>(y),
+                       c->stream, prof);
+      SGN_HIP(hipStreamSynchronize(c->stream));
+      if (prof) prof->flush();
+      return SGN_OK;
+    }
+    // buffers that share memory: through packed copies
     double2 *a = nullptr, *b = nullptr;
     SGN_HIP(hipMalloc(&a, sizeof(double2) * c->ldq));
     SGN_HIP(hipMalloc(&b, sizeof(double2) * c->ldq));
     try {
       wilson_pack(c->lat, reinterpret_cast<const double2*>(x), a, c->stream);
-      wilson_apply(c->lat, c->links, a, b, nullptr, nullptr, c->stream, c->prof.on ? &c->prof : nullptr);
+      wilson_apply(c->lat, c->links, a, b, nullptr, nullptr, c->stream, prof);
       wilson_unpack(c->lat, b, reinterpret_cast<double2*>(y), c->stream);
       SGN_HIP(hipStreamSynchronize(c->stream));
-      if (c->prof.on) c->prof.flush();
+      if (prof) prof->flush();
     } catch (...) {
       (void)hipFree(a);
       (void)hipFree(b);
@@ -1258,6 +1266,12 @@ int sgn_matvec_noalloc(sgn_ctx* c, const double* x, double* y) {
     SGN_HIP(hipGetDevice(&dev));
     SGN_REQUIRE(dev == c->device, SGN_ESTATE, "the context's device must be current");
     auto* base = static_cast<double2*>(scratch_device_ptr(dev));
+    if (!overlapping(x, y, (size_t)c->N)) {
+      wilson_apply_abi(c->lat, c->links, reinterpret_cast<const double2*>(x), reinterpret_cast<double2*>(y),
+                       c->stream, nullptr);
+      SGN_HIP(hipStreamSynchronize(c->stream));
+      return SGN_OK;
+    }
     double2* a = base;
     double2* b = base + c->ldq;
     wilson_pack(c->lat, reinterpret_cast<const double2*>(x), a, c->stream);

@@ -195,14 +195,13 @@ template <typename C>
 void wilson_apply_slots(const Lattice& lat, const C* links, const C* in, size_t istride, C* out, size_t ostride,
                         const SlotMap& map, hipStream_t s, Profiler* prof);
 
-// Out_r = H_w(mu) In_r for nrhs vectors at fixed strides, one launch.  split: one
-// hop per thread for every right-hand side (each result bitwise independent of
-// nrhs); otherwise, for nrhs >= 2, one site per thread with the link shared.
-void wilson_apply_multi(const Lattice& lat, const double2* links, const double2* in, size_t istride, double2* out,
-                        size_t ostride, int nrhs, bool split, hipStream_t s, Profiler* prof);
-// FP32 links and spinors (mixed precision)
-void wilson_apply_multi32(const Lattice& lat, const float2* links, const float2* in, size_t istride, float2* out,
-                          size_t ostride, int nrhs, bool split, hipStream_t s, Profiler* prof);
+// Out = H_w(mu) In with FP32 links and spinors (mixed precision)
+void wilson_apply32(const Lattice& lat, const float2* links, const float2* in, float2* out, hipStream_t s,
+                    Profiler* prof);
+// y = H_w(mu) x in the interface layout (component 12 n + c), bitwise the
+// packed form's result; x and y must not overlap
+void wilson_apply_abi(const Lattice& lat, const double2* links, const double2* x, double2* y, hipStream_t s,
+                      Profiler* prof);
 void wilson_links_f32(const double2* links, float2* links32, int V, hipStream_t s);
 
 // workspace of the block (s-step) Arnoldi process (block.hip), per slot at

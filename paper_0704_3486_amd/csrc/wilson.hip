@@ -29,8 +29,6 @@
 
 namespace {
 
-constexpr int kWilsonBlock = 128;
-
 // complex helpers generic over double2 / float2
 template <typename C> struct Real;
 template <> struct Real<double2> { using type = double; };
@@ -49,83 +47,28 @@ template <typename C> __device__ inline C tmul(C a, C b) { return mk<C>(a.x * b.
 template <typename C> __device__ inline C tfma(C a, C b, C acc) {
   return mk<C>(acc.x + a.x * b.x - a.y * b.y, acc.y + a.x * b.y + a.y * b.x);
 }
-// acc + conj(a) b
-template <typename C> __device__ inline C tfmac(C a, C b, C acc) {
-  return mk<C>(acc.x + a.x * b.x + a.y * b.y, acc.y + a.x * b.y - a.y * b.x);
-}
-
-// Spin-projection table of (1 + gamma_nu) in the chiral basis:
-//   h0 = p0 + a0 p[i0],  h1 = p1 + a1 p[i1]      (upper two spin components)
-//   lower0 = b0 chi[j0],  lower1 = b1 chi[j1]     (chi = U h, the colour-rotated half spinor)
-// with a, b in {+-1, +-i} stored as (re, im) sign pairs; (1 - gamma_nu) negates a0, a1, b0, b1.
+// Spin projection of (1 + gamma_nu) in the chiral basis, one colour vector
+// su = 0, 1 of the half spinor at a time:
+//   h_su = p_su + a p[partner],  lower component 2 + li = b chi_su  (chi = U h),
+// with a, b in {+-1, +-i} as (re, im) pairs; (1 - gamma_nu) negates a and b.
+// Computed rather than looked up: a switch over nu or a table in memory would
+// put branches or another wait before the first loads.
 struct SpinProj {
-  int i0, i1, j0, j1;
-  int a0r, a0i, a1r, a1i, b0r, b0i, b1r, b1i;
+  int partner, li, ar, ai, br, bi;
 };
 
-__device__ inline SpinProj spin_proj(int nu) {
-  switch (nu) {
-    case 0: return SpinProj{3, 2, 1, 0, 0, -1, 0, -1, 0, 1, 0, 1};
-    case 1: return SpinProj{3, 2, 1, 0, -1, 0, 1, 0, 1, 0, -1, 0};
-    case 2: return SpinProj{2, 3, 0, 1, 0, -1, 0, 1, 0, 1, 0, -1};
-    default: return SpinProj{2, 3, 0, 1, 1, 0, 1, 0, 1, 0, 1, 0};
-  }
-}
-
-// (re, im) * sign pair (exact: entries are 0 or +-1)
-template <typename C>
-__device__ inline C unit_mul(int sr, int si, C v, typename Real<C>::type sg) {
-  using R = typename Real<C>::type;
-  return mk<C>(sg * ((R)sr * v.x - (R)si * v.y), sg * ((R)sr * v.y + (R)si * v.x));
-}
-
-// contribution of hop d (nu = d/2, forward if d even) to the 12 components of
-// sum_hops at one site: the half-spinor of the neighbour m times the link
-// (U_{n,nu} forward, U_{m,nu}^dag backward), times e^{+-mu} on time hops,
-// expanded back to four spins
-template <typename C>
-__device__ inline void hop_term(const C u[9], const C* __restrict__ v, int V, int m, int d,
-                                typename Real<C>::type emu, typename Real<C>::type emmu, typename Real<C>::type bc,
-                                C o[4][3]) {
-  using R = typename Real<C>::type;
-  const int nu = d >> 1;
-  const bool fwd = (d & 1) == 0;
-  const R sg = fwd ? (R)1 : (R)-1;
-  const R phase = (nu == 3) ? (fwd ? emu : emmu) * bc : (R)1;
-  const SpinProj P = spin_proj(nu);
-  C h0[3], h1[3];
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    const C p0 = v[c * V + m];
-    const C p1 = v[(3 + c) * V + m];
-    const C pa = v[(3 * P.i0 + c) * V + m];
-    const C pb = v[(3 * P.i1 + c) * V + m];
-    h0[c] = tadd(p0, unit_mul(P.a0r, P.a0i, pa, sg));
-    h1[c] = tadd(p1, unit_mul(P.a1r, P.a1i, pb, sg));
-  }
-#pragma unroll
-  for (int r = 0; r < 3; ++r) {
-    C s0 = mk<C>(0, 0), s1 = mk<C>(0, 0);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      if (fwd) {
-        s0 = tfma(u[3 * r + c], h0[c], s0);
-        s1 = tfma(u[3 * r + c], h1[c], s1);
-      } else {
-        s0 = tfmac(u[3 * c + r], h0[c], s0);
-        s1 = tfmac(u[3 * c + r], h1[c], s1);
-      }
-    }
-    o[0][r] = tscale(s0, phase);
-    o[1][r] = tscale(s1, phase);
-  }
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    const C x0 = (P.j0 == 0) ? o[0][c] : o[1][c];
-    const C x1 = (P.j1 == 0) ? o[0][c] : o[1][c];
-    o[2][c] = unit_mul(P.b0r, P.b0i, x0, sg);
-    o[3][c] = unit_mul(P.b1r, P.b1i, x1, sg);
-  }
+__device__ inline SpinProj spin_proj(int nu, int su) {
+  const bool odd = nu & 1;
+  SpinProj P;
+  P.partner = nu < 2 ? 3 - su : 2 + su;
+  P.li = nu < 2 ? 1 - su : su;
+  const int re_a = su == 0 && nu == 1 ? -1 : 1, im_a = su == 1 && nu == 2 ? 1 : -1;
+  const int re_b = P.li == 1 && nu == 1 ? -1 : 1, im_b = P.li == 1 && nu == 2 ? -1 : 1;
+  P.ar = odd ? re_a : 0;
+  P.ai = odd ? 0 : im_a;
+  P.br = odd ? re_b : 0;
+  P.bi = odd ? 0 : im_b;
+  return P;
 }
 
 constexpr int kLinkRows = 2;               // rows of an SU(3) link held in memory
@@ -147,82 +90,24 @@ __device__ inline void load_link(const C* __restrict__ links, int V, int nu, int
   u[8] = mk<C>(c2.x, -c2.y);
 }
 
-// neighbour of site n (coordinates x, y, z, t) along hop d, periodic wrap
-__device__ inline int hop_neighbour(int n, int d, int x, int y, int z, int t, int Lx, int Ly, int Lz, int Lt) {
-  const int nu = d >> 1;
-  const int L = nu == 0 ? Lx : nu == 1 ? Ly : nu == 2 ? Lz : Lt;
-  const int coord = nu == 0 ? x : nu == 1 ? y : nu == 2 ? z : t;
-  const int stride = nu == 0 ? 1 : nu == 1 ? Lx : nu == 2 ? Lx * Ly : Lx * Ly * Lz;
-  if ((d & 1) == 0) return (coord == L - 1) ? n - (L - 1) * stride : n + stride;
-  return (coord == 0) ? n + (L - 1) * stride : n - stride;
-}
-
-// Out_r = H_w(mu) In_r for RB right-hand sides per thread, one site per thread
-// (blockIdx.y picks the group of RB); the link of each hop is loaded once and
-// applied to all RB.  Used for several right-hand sides on large lattices.
-template <typename C, int RB>
-__global__ void __launch_bounds__(kWilsonBlock)
-wilson_hw_kernel(const C* __restrict__ links, const C* __restrict__ in, size_t istride, C* __restrict__ out,
-                 size_t ostride, int nrhs, int Lx, int Ly, int Lz, int Lt, double kappa_d, double emu_d,
-                 double emmu_d) {
-  using R = typename Real<C>::type;
-  const int V = Lx * Ly * Lz * Lt;
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
-  const int rb0 = blockIdx.y * RB;
-  if (n >= V) return;
-  const int x = n % Lx;
-  const int y = (n / Lx) % Ly;
-  const int z = (n / (Lx * Ly)) % Lz;
-  const int t = n / (Lx * Ly * Lz);
-  const R kappa = (R)kappa_d, emu = (R)emu_d, emmu = (R)emmu_d;
-
-  C acc[RB][4][3];
-#pragma unroll
-  for (int b = 0; b < RB; ++b)
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) acc[b][s][c] = mk<C>(0, 0);
-
-  // The eight hops run as a rolled loop so that only one hop's neighbour
-  // spinors and link are live at a time (an unrolled body spills on gfx950).
-#pragma unroll 1
-  for (int d = 0; d < 8; ++d) {
-    const int m = hop_neighbour(n, d, x, y, z, t, Lx, Ly, Lz, Lt);
-    const int ls = (d & 1) == 0 ? n : m;  // site that owns the link
-    C u[9];
-    load_link<C>(links, V, d >> 1, ls, u);
-    // antiperiodic in time: the hops across the time boundary
-    const R bc = ((d == 6 && t == Lt - 1) || (d == 7 && t == 0)) ? (R)-1 : (R)1;
-#pragma unroll
-    for (int b = 0; b < RB; ++b) {
-      if (rb0 + b >= nrhs) break;
-      C o[4][3];
-      hop_term<C>(u, in + (size_t)(rb0 + b) * istride, V, m, d, emu, emmu, bc, o);
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) acc[b][s][c] = tadd(acc[b][s][c], o[s][c]);
-    }
+// Quotient by a divisor fixed per launch: q = n / d for 0 <= n < 2^31 as one
+// high multiplication, M = ceil(2^(31 + s) / d) with 2^(s-1) < d <= 2^s (the
+// error n (M d - 2^(31+s)) / (d 2^(31+s)) stays below 1 / d).  The compiler's
+// division by a runtime value is a chain of about 25 instructions, and the
+// site's coordinates take three of them before the first load can issue.
+struct FastDiv {
+  unsigned m = 0, s = 0;  // s = 0: d = 1
+  __host__ static FastDiv make(int d) {
+    FastDiv f;
+    while ((1ll << f.s) < d) ++f.s;
+    f.m = (unsigned)(((1ull << (31 + f.s)) + (unsigned long long)d - 1) / (unsigned long long)d);
+    return f;
   }
-
-#pragma unroll
-  for (int b = 0; b < RB; ++b) {
-    if (rb0 + b >= nrhs) break;
-    const C* __restrict__ v = in + (size_t)(rb0 + b) * istride;
-    C* __restrict__ o = out + (size_t)(rb0 + b) * ostride;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const R g5 = (s < 2) ? (R)1 : (R)-1;
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        const int idx = (3 * s + c) * V + n;
-        // gamma5 (psi - kappa * hops)
-        o[idx] = tscale(tsub(v[idx], tscale(acc[b][s][c], kappa)), g5);
-      }
-    }
+  __device__ inline int div(int n) const {
+    const unsigned h = __umulhi((unsigned)n, m);
+    return s ? (int)(h >> (s - 1)) : n;
   }
-}
+};
 
 // Workgroup b runs on XCD b mod 8, each XCD with its own L2.  Renumber the
 // blocks so that XCD x works through one contiguous range of sites (about
@@ -230,95 +115,187 @@ wilson_hw_kernel(const C* __restrict__ links, const C* __restrict__ in, size_t i
 // reads were then mostly fetched into the same L2 by the blocks just before
 // it.  A bijection on [0, nblk).
 constexpr int kXcds = 8;
-constexpr int kSiteGroup = 32;  // sites per workgroup of the stencil
-__device__ inline int xcd_block(int b, int nblk) {
+constexpr int kSiteGroup = 32;  // the walk blocks are segments of this many sites
+__device__ inline int xcd_block(unsigned b, unsigned nblk) {
   const int x = b % kXcds, i = b / kXcds, q = nblk / kXcds, r = nblk % kXcds;
   return x * q + min(x, r) + i;
 }
 
-// Order in which the workgroups (16 lexicographically consecutive sites
-// each) visit the lattice.  Lexicographic order puts the t-neighbours of a
-// site a whole time slice of work away, beyond L2 on large lattices.  The
-// blocked order walks 4D blocks of Lx x By x Bz x Bt sites (inside a block:
-// 16-site segments of By rows, then z, then t; the blocks with t fastest), so
-// every neighbour of a site is touched within about Lx By Bz sites of work.
+// Order in which the workgroups (lexicographically consecutive sites each)
+// visit the lattice.  Lexicographic order puts the t-neighbours of a site a
+// whole time slice of work away, beyond L2 on large lattices.  The blocked
+// order walks 4D blocks of Lx x By x Bz x Bt sites (inside a block: segments
+// of By rows, then z, then t; the blocks with t fastest), so every neighbour
+// of a site is touched within about Lx By Bz sites of work.
 // on = 0: lexicographic (lattices the blocks do not tile, or too small to care).
 struct SiteOrder {
   int on = 0;
   int By = 1, Bz = 1, Bt = 1;
-  int segw = 1;  // workgroups per segment: Lx By / kSiteGroup
+  int wpb = 1;  // workgroups per block
+  FastDiv dwpb, dseg, dsegz, dntb, dnyz;  // by wpb, segw, segw Bz, Lt / Bt, (Lt / Bt)(Lz / Bz)
+  int segw = 1, ntb = 1, nzb = 1;         // workgroups per segment, blocks in t and z
 };
 
 // first site of logical workgroup w
-__device__ inline int order_site(int w, const SiteOrder& o, int Lx, int Ly, int Lz, int Lt, int sites_per_wg) {
+__device__ inline int order_site(int w, const SiteOrder& o, int Lx, int Ly, int Lz, int sites_per_wg) {
   if (!o.on) return w * sites_per_wg;
-  const int wpb = o.segw * o.Bz * o.Bt;
-  const int blk = w / wpb, in = w - blk * wpb;
-  const int seg = in % o.segw, zi = (in / o.segw) % o.Bz, ti = in / (o.segw * o.Bz);
-  const int ntb = Lt / o.Bt, nzb = Lz / o.Bz;
-  const int tb = blk % ntb, zb = (blk / ntb) % nzb, yb = blk / (ntb * nzb);
+  const int blk = o.dwpb.div(w), in = w - blk * o.wpb;
+  const int i1 = o.dseg.div(in), ti = o.dsegz.div(in);
+  const int seg = in - i1 * o.segw, zi = i1 - ti * o.Bz;
+  const int b1 = o.dntb.div(blk), yb = o.dnyz.div(blk);
+  const int tb = blk - b1 * o.ntb, zb = b1 - yb * o.nzb;
   const int t = tb * o.Bt + ti, z = zb * o.Bz + zi, y0 = yb * o.By;
   return ((t * Lz + z) * Ly + y0) * Lx + seg * sites_per_wg;
 }
 
-template <typename C>
-__device__ inline C shfl_xor_c(C v, int mask) {
-  return mk<C>(__shfl_xor(v.x, mask, 64), __shfl_xor(v.y, mask, 64));
+// lattice extents and strides with the quotients the site coordinates need
+// (indexed by the direction; nblk: workgroups per right-hand side)
+struct Geom {
+  int L[4], stride[4];
+  FastDiv div[4];  // by stride[nu]
+  int V, nblk;
+  double kappa, emu, emmu;
+};
+
+// value of lane l % 32 (lo: the forward hop) and of lane 32 + l % 32 (hi: the
+// backward hop) in every lane l
+template <typename R>
+struct Halves {
+  R lo, hi;
+};
+__device__ inline Halves<float> halves(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return {__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+__device__ inline Halves<double> halves(double v) {
+  const unsigned l = (unsigned)__double2loint(v), h = (unsigned)__double2hiint(v);
+  const auto rl = __builtin_amdgcn_permlane32_swap(l, l, false, false);
+  const auto rh = __builtin_amdgcn_permlane32_swap(h, h, false, false);
+  return {__hiloint2double((int)rh[0], (int)rl[0]), __hiloint2double((int)rh[1], (int)rl[1])};
 }
 
-// Out_r = H_w(mu) In_r.  A workgroup holds kSiteGroup = 32 sites and four
-// wavefronts, wavefront nu taking direction nu for all 32 sites: lanes 0..31
-// the forward hop, lanes 32..63 the backward hop of the same sites.  The
-// direction, its link array, spin projector and phase are then uniform over
-// the wavefront; the backward lanes turn U_{m,nu} into U_{m,nu}^dag with
-// selects, so both halves run one instruction stream.  One butterfly shuffle
-// (xor 32) adds the two hops, p_nu = fwd_nu + bwd_nu (the same bits in both
-// halves: addition is commutative); the four p_nu meet in LDS and are summed
-// in direction order.  The site's own spinor entries for the second phase
-// are loaded with the hop operands, so a workgroup waits on memory once.
+// Out_r = H_w(mu) In_r.  A workgroup holds S sites and four wavefronts,
+// wavefront nu taking direction nu for all S sites: lanes 0..31 the forward
+// hop, lanes 32..63 the backward hop.  With S = 32 a lane forms both colour
+// vectors of its hop's half spinor; with S = 16 lanes l and l + 16 of a half
+// form one each (12 instead of 18 operand loads per lane and twice the
+// workgroups).  The direction, its link array, spin projector and phase are
+// uniform over the wavefront; the backward lanes turn U_{m,nu} into
+// U_{m,nu}^dag with selects, so both halves run one instruction stream.  A
+// lane-half swap gives every lane both hops: the first half writes the upper
+// spin components fwd + bwd, the second the lower ones, b_nu (fwd - bwd); the
+// four directions meet in LDS and are summed in direction order.  Every
+// component's arithmetic is the same for either S.  The site's own spinor
+// entries for the second phase are loaded with the hop operands, so a
+// workgroup waits on memory once.
 // blockIdx.y = right-hand side (slot map).  Optional: scale = *inv_beta on
 // input and output, copy_out = In * scale; with CHEB, Out_r = ca H_w In_r +
 // cb Prev_r (Prev_r = prev + slot pstride; prev null: cb ignored), a step of
 // a three-term polynomial recurrence.
-template <typename C, bool CHEB>
+// ABI: in and out are in the interface layout (component 12 n + c).  A
+// site's 12 entries are then contiguous, so the wavefront reads its neighbour
+// sites' entries in that order and turns them through LDS.
+//
+// Small lattices are bound by the chain of dependent steps (an empty kernel
+// takes 2.45 us back to back): 6^4 takes 3.4 us with S = 16, 3.9 with S = 32
+// (5.1 with divisions, a switch over nu and both hops' twelve components
+// through the shuffles).  Large ones are bound by memory: 32^4, 0.81 GB of
+// operands, 227 us = 3.5 TB/s with S = 32, 268 us with S = 16 (263 us before),
+// and 242 us in the interface layout with S = 16 (272 us with S = 32, whose
+// 53 KB of LDS leave two wavefronts per SIMD less); packing, applying and
+// unpacking took 415 us.
+template <typename C, int S, bool CHEB, bool ABI>
 __global__ void __launch_bounds__(256)
 wilson_hw_dir_kernel(const C* __restrict__ links, const C* __restrict__ in, size_t istride, C* __restrict__ out,
-                     size_t ostride, const double* __restrict__ inv_beta, C* __restrict__ copy_out, int Lx, int Ly,
-                     int Lz, int Lt, double kappa_d, double emu_d, double emmu_d, SlotMap map, SiteOrder order,
-                     const C* __restrict__ prev, size_t pstride, double ca, double cb) {
+                     size_t ostride, const double* __restrict__ inv_beta, C* __restrict__ copy_out, Geom g,
+                     SlotMap map, SiteOrder order, const C* __restrict__ prev, size_t pstride, double ca, double cb) {
   using R = typename Real<C>::type;
-  constexpr int kThreads = 256, kOut = 12 * kSiteGroup;
-  const int V = Lx * Ly * Lz * Lt;
+  static_assert(S == 32 || S == 16, "sites per workgroup");
+  constexpr int kThreads = 256, kOut = 12 * S;
+  constexpr int kRounds = (kOut + kThreads - 1) / kThreads;
+  constexpr int NH = S / 16;  // colour vectors per lane
+  constexpr int kPad = ABI ? 13 : S;  // LDS row: one site's components (ABI), else one component's sites
+  const int V = g.V;
   const int lane = threadIdx.x & 63;
   const int nu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int sl = lane & (kSiteGroup - 1);
-  const bool fwd = lane < kSiteGroup;
-  const int n0 = order_site(xcd_block(blockIdx.x, gridDim.x), order, Lx, Ly, Lz, Lt, kSiteGroup);
+  const int sl = lane & (S - 1);
+  const int hs = (lane >> 4) & 1;  // S = 16: this lane's colour vector
+  const bool fwd = lane < 32;
+  const int slot = map.slot[blockIdx.y];
+  const int n0 = order_site(xcd_block(blockIdx.x, g.nblk), order, g.L[0], g.L[1], g.L[2], S);
   const int n = n0 + sl;
   const int nc = n < V ? n : V - 1;  // lanes past the lattice work on a valid site, never written out
-  const int slot = map.n > 0 ? map.slot[blockIdx.y] : (int)blockIdx.y;
   const C* __restrict__ v = in + (size_t)slot * istride;
-  // second-phase outputs of this thread: p = tid + q kThreads < kOut, i.e.
-  // component p / kSiteGroup of site n0 + p % kSiteGroup
-  C self[2], pv[2];
-  const C* __restrict__ pr = (CHEB && prev) ? prev + (size_t)slot * pstride : nullptr;
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int p = threadIdx.x + q * kThreads, nn = n0 + p % kSiteGroup;
-    const bool ok = p < kOut && nn < V;
-    self[q] = ok ? v[(size_t)(p / kSiteGroup) * V + nn] : mk<C>(0, 0);
-    // the recurrence's previous term, loaded with the operands (one wait)
-    if constexpr (CHEB) pv[q] = (ok && pr) ? pr[(size_t)(p / kSiteGroup) * V + nn] : mk<C>(0, 0);
-  }
-  const int x = nc % Lx;
-  const int y = (nc / Lx) % Ly;
-  const int z = (nc / (Lx * Ly)) % Lz;
-  const int t = nc / (Lx * Ly * Lz);
-  const int m = hop_neighbour(nc, 2 * nu + (fwd ? 0 : 1), x, y, z, t, Lx, Ly, Lz, Lt);
+  // the coordinate along nu: n / stride_nu mod L_nu, from the next direction's quotient
+  const int Lnu = g.L[nu], stride = g.stride[nu];
+  const int q0 = g.div[nu].div(nc), q1 = nu == 3 ? 0 : g.div[(nu + 1) & 3].div(nc);
+  const int coord = q0 - q1 * Lnu;
+  // neighbour along the hop, periodic wrap
+  const bool wrap = coord == (fwd ? Lnu - 1 : 0);
+  const int m = nc + (fwd ? stride : -stride) * (wrap ? 1 - Lnu : 1);
   const int ls = fwd ? nc : m;  // site that owns the link
+  // spinor entries of the hop: colour vector su needs spins su and its partner
+  C pu[NH][3], pl[NH][3];
+  // the partial sums of direction k at smem[k kSlab]; before them (ABI) that
+  // wavefront's neighbour entries in the same place
+  constexpr int kSlab = ABI ? 2 * S * kPad : 12 * S;
+  __shared__ C smem[4 * kSlab];
+  if constexpr (ABI) {
+    // entry e of the wavefront's 2 S neighbour sites: site e / 12, component e % 12
+    C* const nbr = smem + nu * kSlab;
+    constexpr int kEnt = 2 * S * 12 / 64;
+    C ent[kEnt];
+#pragma unroll
+    for (int i = 0; i < kEnt; ++i) {
+      const int e = i * 64 + lane, q = e / 12, comp = e - 12 * q;
+      // sites 0..S-1: forward (lanes 0..S-1), S..2S-1: backward (lanes 32..)
+      const int mq = __shfl(m, q < S ? q : 32 + q - S, 64);
+      ent[i] = v[(size_t)mq * 12 + comp];
+    }
+#pragma unroll
+    for (int i = 0; i < kEnt; ++i) {
+      const int e = i * 64 + lane, q = e / 12, comp = e - 12 * q;
+      nbr[q * kPad + comp] = ent[i];
+    }
+    __syncthreads();
+    const C* row = nbr + ((fwd ? 0 : S) + sl) * kPad;
+#pragma unroll
+    for (int h = 0; h < NH; ++h) {
+      const int su = NH == 2 ? h : hs, lo = spin_proj(nu, su).partner;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        pu[h][c] = row[3 * su + c];
+        pl[h][c] = row[3 * lo + c];
+      }
+    }
+  } else {
+#pragma unroll
+    for (int h = 0; h < NH; ++h) {
+      const int su = NH == 2 ? h : hs, lo = spin_proj(nu, su).partner;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        pu[h][c] = v[(size_t)((3 * su + c) * V + m)];
+        pl[h][c] = v[(size_t)((3 * lo + c) * V + m)];
+      }
+    }
+  }
   C u[9];
   load_link<C>(links, V, nu, ls, u);
+  // second-phase outputs of this thread: p = tid + q kThreads < kOut, i.e.
+  // component p / S of site n0 + p % S (ABI: component p % 12 of site n0 + p / 12)
+  C self[kRounds], pv[kRounds];
+  const C* __restrict__ pr = (CHEB && prev) ? prev + (size_t)slot * pstride : nullptr;
+#pragma unroll
+  for (int q = 0; q < kRounds; ++q) {
+    const int p = threadIdx.x + q * kThreads, s2 = ABI ? p / 12 : p % S, nn = n0 + s2;
+    const bool ok = p < kOut && nn < V;
+    const size_t idx = ABI ? (size_t)n0 * 12 + p : (size_t)(p / S) * V + nn;
+    self[q] = ok ? v[idx] : mk<C>(0, 0);
+    // the recurrence's previous term, loaded with the operands (one wait)
+    if constexpr (CHEB) pv[q] = (ok && pr) ? pr[idx] : mk<C>(0, 0);
+  }
   // the matrix applied to the half spinor: U (forward) or U^dag (backward)
+  const R sg = fwd ? (R)1 : (R)-1;
   C w9[9];
 #pragma unroll
   for (int r = 0; r < 3; ++r)
@@ -327,62 +304,62 @@ wilson_hw_dir_kernel(const C* __restrict__ links, const C* __restrict__ in, size
       const C a = u[3 * r + c], b = u[3 * c + r];
       w9[3 * r + c] = fwd ? a : mk<C>(b.x, -b.y);
     }
-  const SpinProj P = spin_proj(nu);
-  const R sg = fwd ? (R)1 : (R)-1;
   // e^{+-mu} on time hops, and the antiperiodic sign on the two hops across
   // the time boundary (forward from the last slice, backward from the first)
-  const bool across = nu == 3 && (fwd ? t == Lt - 1 : t == 0);
-  const R phase = (nu == 3) ? (fwd ? (R)emu_d : (R)emmu_d) * (across ? (R)-1 : (R)1) : (R)1;
-  C h0[3], h1[3];
+  const R phase = (nu == 3) ? (fwd ? (R)g.emu : (R)g.emmu) * (wrap ? (R)-1 : (R)1) : (R)1;
+  C chi[NH][3];
 #pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    const C p0 = v[(size_t)c * V + m];
-    const C p1 = v[(size_t)(3 + c) * V + m];
-    const C pa = v[(size_t)(3 * P.i0 + c) * V + m];
-    const C pb = v[(size_t)(3 * P.i1 + c) * V + m];
-    h0[c] = tadd(p0, unit_mul(P.a0r, P.a0i, pa, sg));
-    h1[c] = tadd(p1, unit_mul(P.a1r, P.a1i, pb, sg));
+  for (int h = 0; h < NH; ++h) {
+    // h = p_u + sg a p_l with a in {+-1, +-i}: the products are exact
+    const SpinProj P = spin_proj(nu, NH == 2 ? h : hs);
+    const R ar = sg * (R)P.ar, ai = sg * (R)P.ai;
+    C hv[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      hv[c] = mk<C>(fma(ar, pl[h][c].x, fma(-ai, pl[h][c].y, pu[h][c].x)),
+                    fma(ar, pl[h][c].y, fma(ai, pl[h][c].x, pu[h][c].y)));
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      C s0 = mk<C>(0, 0);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) s0 = tfma(w9[3 * r + c], hv[c], s0);
+      chi[h][r] = tscale(s0, phase);
+    }
   }
-  C o[4][3];
+  // both hops in every lane: the first half of the lanes sums the upper
+  // components, the second forms the lower ones: spin 2 + i is b_i chi[j_i]
+  auto at = [&](int k, int comp, int site) -> C& {
+    return smem[k * kSlab + (ABI ? site * kPad + comp : comp * S + site)];
+  };
 #pragma unroll
-  for (int r = 0; r < 3; ++r) {
-    C s0 = mk<C>(0, 0), s1 = mk<C>(0, 0);
+  for (int h = 0; h < NH; ++h) {
+    const int su = NH == 2 ? h : hs;
+    const SpinProj P = spin_proj(nu, su);
+    const R br = (R)P.br, bi = (R)P.bi;
+    const int comp0 = 3 * (fwd ? su : 2 + P.li);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      s0 = tfma(w9[3 * r + c], h0[c], s0);
-      s1 = tfma(w9[3 * r + c], h1[c], s1);
+      const auto hx = halves(chi[h][c].x), hy = halves(chi[h][c].y);
+      const C f = mk<C>(hx.lo, hy.lo), b = mk<C>(hx.hi, hy.hi);
+      const C d = tsub(f, b);
+      const C up = tadd(f, b), low = mk<C>(br * d.x - bi * d.y, br * d.y + bi * d.x);
+      // (a select of the parts: one of the structs would go through scratch)
+      at(nu, comp0 + c, sl) = mk<C>(fwd ? up.x : low.x, fwd ? up.y : low.y);
     }
-    o[0][r] = tscale(s0, phase);
-    o[1][r] = tscale(s1, phase);
   }
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    const C x0 = (P.j0 == 0) ? o[0][c] : o[1][c];
-    const C x1 = (P.j1 == 0) ? o[0][c] : o[1][c];
-    o[2][c] = unit_mul(P.b0r, P.b0i, x0, sg);
-    o[3][c] = unit_mul(P.b1r, P.b1i, x1, sg);
-  }
-  __shared__ C part[12][4][kSiteGroup];
-#pragma unroll
-  for (int s = 0; s < 4; ++s)
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      const C pnu = tadd(o[s][c], shfl_xor_c(o[s][c], 32));
-      if (fwd) part[3 * s + c][nu][sl] = pnu;
-    }
   __syncthreads();
-  const R kappa = (R)kappa_d;
+  const R kappa = (R)g.kappa;
   const R scale = inv_beta ? (R)(*inv_beta) : (R)1;
   C* __restrict__ w = out + (size_t)slot * ostride;
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
+  for (int q = 0; q < kRounds; ++q) {
     const int p = threadIdx.x + q * kThreads;
-    const int comp = p / kSiteGroup, s2 = p % kSiteGroup, nn = n0 + s2;
+    const int comp = ABI ? p % 12 : p / S, s2 = ABI ? p / 12 : p % S, nn = n0 + s2;
     if (p >= kOut || nn >= V) continue;
     C acc = mk<C>(0, 0);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) acc = tadd(acc, part[comp][k][s2]);
-    const size_t idx = (size_t)comp * V + nn;
+    for (int k = 0; k < 4; ++k) acc = tadd(acc, at(k, comp, s2));
+    const size_t idx = ABI ? (size_t)n0 * 12 + p : (size_t)comp * V + nn;
     // gamma5 (psi - kappa * hops), all times 1/beta
     const R g5 = comp < 6 ? (R)1 : (R)-1;
     C val = tscale(tsub(self[q], tscale(acc, kappa)), g5 * scale);
@@ -527,8 +504,9 @@ void overlap_adjoint_finish(const double2* x, double2* y, size_t n, hipStream_t 
 }
 
 // the blocked order when the lattice is large enough to leave L2 and its
-// extents admit the blocks (Lx By a multiple of the workgroup's 16 sites)
-static SiteOrder site_order(const Lattice& lat) {
+// extents admit the blocks (Lx By a multiple of kSiteGroup); spw: sites per
+// workgroup, a divisor of kSiteGroup
+static SiteOrder site_order(const Lattice& lat, int spw) {
   SiteOrder o;
   const int Lx = lat.L[0], Ly = lat.L[1], Lz = lat.L[2], Lt = lat.L[3];
   if (lat.blk[0] < 0) return o;
@@ -536,25 +514,48 @@ static SiteOrder site_order(const Lattice& lat) {
     o.By = lat.blk[0];
     o.Bz = lat.blk[1];
     o.Bt = lat.blk[2];
-    o.segw = Lx * o.By / kSiteGroup;
-    o.on = 1;
-    return o;
+  } else {
+    if (lat.V < 65536) return o;
+    // preferred extents first (at 32^4, Lx x 4 x 16 x 4 walked 6 % faster than
+    // Lx x 8 x 8 x 4 and 14 % faster than the natural order)
+    auto pick = [](int L, std::initializer_list<int> pref, auto ok) {
+      for (int b : pref)
+        if (L % b == 0 && ok(b)) return b;
+      return 0;
+    };
+    o.By = pick(Ly, {4, 8, 2, 16, 1}, [&](int b) { return (Lx * b) % kSiteGroup == 0; });
+    o.Bz = pick(Lz, {16, 8, 4, 2, 1}, [](int) { return true; });
+    o.Bt = pick(Lt, {4, 8, 2, 1}, [](int) { return true; });
+    if (o.By == 0 || o.Bz == 0 || o.Bt == 0) return SiteOrder{};
   }
-  if (lat.V < 65536) return o;
-  // preferred extents first (at 32^4, Lx x 4 x 16 x 4 walked 6 % faster than
-  // Lx x 8 x 8 x 4 and 14 % faster than the natural order)
-  auto pick = [](int L, std::initializer_list<int> pref, auto ok) {
-    for (int b : pref)
-      if (L % b == 0 && ok(b)) return b;
-    return 0;
-  };
-  o.By = pick(Ly, {4, 8, 2, 16, 1}, [&](int b) { return (Lx * b) % kSiteGroup == 0; });
-  o.Bz = pick(Lz, {16, 8, 4, 2, 1}, [](int) { return true; });
-  o.Bt = pick(Lt, {4, 8, 2, 1}, [](int) { return true; });
-  if (o.By == 0 || o.Bz == 0 || o.Bt == 0) return SiteOrder{};
-  o.segw = Lx * o.By / kSiteGroup;
+  o.segw = Lx * o.By / spw;
+  o.wpb = o.segw * o.Bz * o.Bt;
+  o.ntb = Lt / o.Bt;
+  o.nzb = Lz / o.Bz;
+  o.dwpb = FastDiv::make(o.wpb);
+  o.dseg = FastDiv::make(o.segw);
+  o.dsegz = FastDiv::make(o.segw * o.Bz);
+  o.dntb = FastDiv::make(o.ntb);
+  o.dnyz = FastDiv::make(o.ntb * o.nzb);
   o.on = 1;
   return o;
+}
+
+static Geom geom(const Lattice& lat, int nblk) {
+  Geom g{};
+  int st = 1;
+  for (int nu = 0; nu < 4; ++nu) {
+    g.L[nu] = lat.L[nu];
+    g.stride[nu] = st;
+    g.div[nu] = FastDiv::make(st);
+    st *= lat.L[nu];
+  }
+  g.V = lat.V;
+  g.nblk = nblk;
+  g.kappa = lat.kappa;
+  g.emu = lat.emu;
+  g.emmu = lat.emmu;
+  return g;
 }
 
 bool wilson_blocks_valid(const Lattice& lat, int By, int Bz, int Bt) {
@@ -564,90 +565,84 @@ bool wilson_blocks_valid(const Lattice& lat, int By, int Bz, int Bt) {
          (lat.L[0] * By) % kSiteGroup == 0;
 }
 
+// One launch of the stencil for the slots of map.  The site split S by the
+// number of 32-site workgroups: below two per CU the chip is short of
+// workgroups and 16 sites are faster (6^4 x 8 slots, 328 of them: 5.7 against
+// 6.1 us; 8^4 x 3, 384: 5.6 against 6.0), above it the link loads that the two
+// lanes of a site repeat cost more (12^4, 648: 7.4 against 7.2 us; 8^4 x 8,
+// 1024: 9.3 against 8.9).
+constexpr long long kSplitBelow = 512;
+
+template <typename C, int S, bool CHEB, bool ABI>
+static void hw_launch_as(const Lattice& lat, const C* links, const C* in, size_t istride, C* out, size_t ostride,
+                         const double* inv_beta, C* copy_out, const SlotMap& map, const C* prev, size_t pstride,
+                         double ca, double cb, double bytes, hipStream_t s, Profiler* prof) {
+  const int nblk = (lat.V + S - 1) / S;
+  prof_launch(prof, K_WILSON, bytes, 1392.0 * lat.V * map.n, wilson_hw_dir_kernel<C, S, CHEB, ABI>,
+              dim3(nblk, map.n), dim3(256), 0, s, links, in, istride, out, ostride, inv_beta, copy_out,
+              geom(lat, nblk), map, site_order(lat, S), prev, pstride, ca, cb);
+}
+
+template <typename C, bool CHEB>
+static void hw_launch(const Lattice& lat, const C* links, const C* in, size_t istride, C* out, size_t ostride,
+                      const double* inv_beta, C* copy_out, const SlotMap& map, const C* prev, size_t pstride,
+                      double ca, double cb, double bytes, hipStream_t s, Profiler* prof) {
+  const bool fine = (long long)((lat.V + 31) / 32) * map.n < kSplitBelow;
+  (fine ? hw_launch_as<C, 16, CHEB, false> : hw_launch_as<C, 32, CHEB, false>)(
+      lat, links, in, istride, out, ostride, inv_beta, copy_out, map, prev, pstride, ca, cb, bytes, s, prof);
+}
+
+static SlotMap one_slot() {
+  SlotMap m;
+  m.n = 1;
+  return m;
+}
+
 void wilson_apply(const Lattice& lat, const double2* links, const double2* in, double2* out,
                   const double* inv_beta, double2* copy_out, hipStream_t s, Profiler* prof) {
-  const int V = lat.V;
   // algorithmic bytes: read v (12), write w (12), 4 links of 6 stored entries
   // (24) per site; + copy (12)
   const double per_site = (48.0 + (copy_out ? 12.0 : 0.0)) * 16.0;
-  prof_launch(prof, K_WILSON, per_site * V, 1392.0 * V, wilson_hw_dir_kernel<double2, false>,
-              dim3((V + kSiteGroup - 1) / kSiteGroup, 1), dim3(256), 0, s, links, in, (size_t)0, out, (size_t)0,
-              inv_beta, copy_out, lat.L[0], lat.L[1], lat.L[2], lat.L[3], lat.kappa, lat.emu, lat.emmu, SlotMap{},
-              site_order(lat), (const double2*)nullptr, (size_t)0, 1.0, 0.0);
+  hw_launch<double2, false>(lat, links, in, 0, out, 0, inv_beta, copy_out, one_slot(), nullptr, 0, 1.0, 0.0,
+                            per_site * lat.V, s, prof);
+}
+
+void wilson_apply32(const Lattice& lat, const float2* links, const float2* in, float2* out, hipStream_t s,
+                    Profiler* prof) {
+  hw_launch<float2, false>(lat, links, in, 0, out, 0, nullptr, nullptr, one_slot(), nullptr, 0, 1.0, 0.0,
+                           48.0 * 8.0 * lat.V, s, prof);
+}
+
+void wilson_apply_abi(const Lattice& lat, const double2* links, const double2* x, double2* y, hipStream_t s,
+                      Profiler* prof) {
+  hw_launch_as<double2, 16, false, true>(lat, links, x, 0, y, 0, nullptr, nullptr, one_slot(), nullptr, 0, 1.0, 0.0,
+                                         48.0 * 16.0 * lat.V, s, prof);
 }
 
 void wilson_apply_cheb_slots(const Lattice& lat, const double2* links, const double2* in, size_t istride,
                              double2* out, size_t ostride, const double2* prev, size_t pstride, double ca, double cb,
                              const SlotMap& map, hipStream_t s, Profiler* prof) {
   SGN_REQUIRE(map.n >= 1 && map.n <= kMaxBatch, SGN_EINVAL, "wilson: slot map must hold 1..64 slots");
-  const int V = lat.V;
   // per site: the links (24 stored entries) once, per slot read v and
   // prev, write w (12 each)
-  const double bytes = (24.0 + (24.0 + (prev ? 12.0 : 0.0)) * map.n) * 16.0 * V;
-  prof_launch(prof, K_WILSON, bytes, 1392.0 * V * map.n, wilson_hw_dir_kernel<double2, true>,
-              dim3((V + kSiteGroup - 1) / kSiteGroup, map.n), dim3(256), 0, s, links, in, istride, out, ostride,
-              (const double*)nullptr, (double2*)nullptr, lat.L[0], lat.L[1], lat.L[2], lat.L[3], lat.kappa, lat.emu,
-              lat.emmu, map, site_order(lat), prev, pstride, ca, cb);
-}
-
-// several right-hand sides: one hop per thread (bitwise the single-RHS
-// result) unless the lattice is large enough that one site per thread fills
-// the chip, where the link is shared by up to four right-hand sides
-template <typename C>
-static void wilson_multi(const Lattice& lat, const C* links, const C* in, size_t istride, C* out, size_t ostride,
-                         int nrhs, bool split, hipStream_t s, Profiler* prof) {
-  const int V = lat.V;
-  SGN_REQUIRE(nrhs >= 1, SGN_EINVAL, "wilson: nrhs must be positive");
-  const int idx = prof ? prof->begin(K_WILSON) : -1;
-  const dim3 blk(kWilsonBlock);
-  const unsigned gx = (V + kWilsonBlock - 1) / kWilsonBlock;
-  const int L0 = lat.L[0], L1 = lat.L[1], L2 = lat.L[2], L3 = lat.L[3];
-  if (split || nrhs == 1) {
-    hipLaunchKernelGGL((wilson_hw_dir_kernel<C, false>), dim3((V + kSiteGroup - 1) / kSiteGroup, nrhs),
-                       dim3(256), 0, s, links, in, istride, out, ostride, nullptr, nullptr, L0, L1, L2,
-                       L3, lat.kappa, lat.emu, lat.emmu, SlotMap{}, site_order(lat), (const C*)nullptr, (size_t)0,
-                       1.0, 0.0);
-  } else if (nrhs >= 4 && sizeof(C) == 8) {
-    hipLaunchKernelGGL((wilson_hw_kernel<C, 4>), dim3(gx, (nrhs + 3) / 4), blk, 0, s, links, in, istride, out,
-                       ostride, nrhs, L0, L1, L2, L3, lat.kappa, lat.emu, lat.emmu);
-  } else {
-    hipLaunchKernelGGL((wilson_hw_kernel<C, 2>), dim3(gx, (nrhs + 1) / 2), blk, 0, s, links, in, istride, out,
-                       ostride, nrhs, L0, L1, L2, L3, lat.kappa, lat.emu, lat.emmu);
-  }
-  SGN_HIP(hipGetLastError());
-  if (prof) {
-    const double b = (double)sizeof(C);
-    // per site: 24 spinor entries per RHS (read + write) and 36 link entries once per launch
-    prof->end(idx, (24.0 * nrhs + 24.0) * b * V, 1392.0 * V * nrhs);
-  }
+  const double bytes = (24.0 + (24.0 + (prev ? 12.0 : 0.0)) * map.n) * 16.0 * lat.V;
+  hw_launch<double2, true>(lat, links, in, istride, out, ostride, nullptr, nullptr, map, prev, pstride, ca, cb, bytes,
+                           s, prof);
 }
 
 template <typename C>
 void wilson_apply_slots(const Lattice& lat, const C* links, const C* in, size_t istride, C* out, size_t ostride,
                         const SlotMap& map, hipStream_t s, Profiler* prof) {
   SGN_REQUIRE(map.n >= 1 && map.n <= kMaxBatch, SGN_EINVAL, "wilson: slot map must hold 1..64 slots");
-  const int V = lat.V;
   // per site: the links (24 stored entries) once, per slot read v (12) and write w (12)
   const double b = (double)sizeof(C);
-  prof_launch(prof, K_WILSON, (24.0 + 24.0 * map.n) * b * V, 1392.0 * V * map.n, wilson_hw_dir_kernel<C, false>,
-              dim3((V + kSiteGroup - 1) / kSiteGroup, map.n), dim3(256), 0, s, links, in, istride, out, ostride,
-              (const double*)nullptr, (C*)nullptr, lat.L[0], lat.L[1], lat.L[2], lat.L[3], lat.kappa, lat.emu,
-              lat.emmu, map, site_order(lat), (const C*)nullptr, (size_t)0, 1.0, 0.0);
+  hw_launch<C, false>(lat, links, in, istride, out, ostride, nullptr, nullptr, map, nullptr, 0, 1.0, 0.0,
+                      (24.0 + 24.0 * map.n) * b * lat.V, s, prof);
 }
 template void wilson_apply_slots<double2>(const Lattice&, const double2*, const double2*, size_t, double2*, size_t,
                                           const SlotMap&, hipStream_t, Profiler*);
 template void wilson_apply_slots<float2>(const Lattice&, const float2*, const float2*, size_t, float2*, size_t,
                                          const SlotMap&, hipStream_t, Profiler*);
-
-void wilson_apply_multi(const Lattice& lat, const double2* links, const double2* in, size_t istride, double2* out,
-                        size_t ostride, int nrhs, bool split, hipStream_t s, Profiler* prof) {
-  wilson_multi<double2>(lat, links, in, istride, out, ostride, nrhs, split, s, prof);
-}
-
-void wilson_apply_multi32(const Lattice& lat, const float2* links, const float2* in, size_t istride, float2* out,
-                          size_t ostride, int nrhs, bool split, hipStream_t s, Profiler* prof) {
-  wilson_multi<float2>(lat, links, in, istride, out, ostride, nrhs, split, s, prof);
-}
 
 void wilson_links_f32(const double2* links, float2* links32, int V, hipStream_t s) {
   const size_t n = wilson_link_entries(V);
