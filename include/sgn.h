@@ -382,7 +382,8 @@ int sgn_get_block_steps(const sgn_ctx* ctx, int* s, double* e_out);
  * eq:modArnoldi; the Gram-Schmidt dot and update passes of step (iv)):
  * update_batch (4, 8 or 16) basis columns whose loads each lane of the
  * update pass issues before their arithmetic, dot_cols (1, 2 or 4) basis
- * columns per wavefront of the dot pass, and update_waves (8 or 16)
+ * columns whose loads a wavefront of the dot pass issues together (4 acts
+ * as 2), and update_waves (8 or 16)
  * wavefronts per 64-row workgroup of the update pass.  update_batch and
  * dot_cols form every sum in the same order, so results are bitwise the
  * same for all their values; update_waves changes which columns each

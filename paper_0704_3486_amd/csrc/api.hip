@@ -189,11 +189,11 @@ struct ApplyResult {
 static void arnoldi_step(sgn_ctx* c, const KrylovArgs& ka, bool mixed, hipStream_t s, Profiler* prof) {
   if (mixed) {
     wilson_apply32(c->lat, c->links32, static_cast<const float2*>(ka.ulonext), c->z32, s, prof);
-    krylov_dot<float2>(c->kw, ka, true, s, prof);
+    krylov_dot<float2>(c->kw, ka, true, false, s, prof);
     krylov_update<float2>(c->kw, ka, s, prof);
   } else {
     wilson_apply(c->lat, c->links, ka.u, c->wB, nullptr, nullptr, s, prof);
-    krylov_dot<double2>(c->kw, ka, true, s, prof);
+    krylov_dot<double2>(c->kw, ka, true, false, s, prof);
     krylov_update<double2>(c->kw, ka, s, prof);
   }
 }
@@ -366,9 +366,9 @@ static int run_apply_impl(sgn_ctx* c, const double2* x_abi, double2* y_abi, doub
         ka.single(kk);
         ka.u = ucur;
         if (mixed)
-          krylov_dot<float2>(c->kw, ka, false, s, prof);
+          krylov_dot<float2>(c->kw, ka, false, true, s, prof);
         else
-          krylov_dot<double2>(c->kw, ka, false, s, prof);
+          krylov_dot<double2>(c->kw, ka, false, true, s, prof);
         krylov_patch(c->kw, ka, n, c->F, 0, true, s);
         it = dense_sign(c->dense, n, c->F, n, c->F, n, s, prof, c->cheb_e);
       } else {

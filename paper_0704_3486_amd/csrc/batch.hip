@@ -224,9 +224,9 @@ int run_batch(sgn_ctx* c, int nr, const double2* X_abi, double2* Y_abi, double t
         if (kk > 0) {
           // finish the re-orthogonalisation of the last column, on a copy
           if (mixed)
-            krylov_dot<float2>(b.kw, kc, false, s, prof);
+            krylov_dot<float2>(b.kw, kc, false, true, s, prof);
           else
-            krylov_dot<double2>(b.kw, kc, false, s, prof);
+            krylov_dot<double2>(b.kw, kc, false, true, s, prof);
         }
         krylov_patch(b.kw, kc, n, Apat, nn, kk > 0, s);
         const int it = dense_sign_batched(b.dense, n, nb, Apat, n, nn, Fout, n, nn, s, prof);
@@ -307,12 +307,12 @@ int run_batch(sgn_ctx* c, int nr, const double2* X_abi, double2* Y_abi, double t
     if (mixed) {
       wilson_apply_slots<float2>(c->lat, c->links32, half_lo(j), ldq, static_cast<float2*>(b.z), ldq, map, st, pf);
       ka.ulonext = half_lo(j + 1);
-      krylov_dot<float2>(b.kw, ka, true, st, pf);
+      krylov_dot<float2>(b.kw, ka, true, false, st, pf);
       krylov_update<float2>(b.kw, ka, st, pf);
     } else {
       wilson_apply_slots<double2>(c->lat, c->links, half_u(j), ldq, static_cast<double2*>(b.z), ldq, map, st, pf);
       ka.ulonext = nullptr;
-      krylov_dot<double2>(b.kw, ka, true, st, pf);
+      krylov_dot<double2>(b.kw, ka, true, false, st, pf);
       krylov_update<double2>(b.kw, ka, st, pf);
     }
   };

@@ -25,9 +25,9 @@ enum {
 // forms every sum in the same order, so results do not depend on them; only
 // the time does.
 //   ub:  update pass, column loads per lane issued before their arithmetic (4, 8, 16)
-//   cpw: dot pass, columns per wavefront (1, 2, 4): fewer columns per
-//        wavefront means more workgroups, shorter chains of dependent loads,
-//        and more re-reads of u and z from cache
+//   cpw: dot pass, columns whose loads a wavefront issues together (1, 2;
+//        4 is taken as 2: four columns' operands take more registers than
+//        they save trips)
 //   uw:  update pass, wavefronts per 64-row workgroup (8, 16).  Unlike ub and
 //        cpw this changes which columns each wavefront sums, so results
 //        differ at the rounding level between its values (every path of a
@@ -117,9 +117,11 @@ void krylov_alloc(KrylovWork& w, int N, size_t ldq, int ncol_cap, int nslots);
 void krylov_free(KrylovWork& w);
 void krylov_bind(const KrylovWork& w, KrylovArgs& A);
 
-// a = Q_J^dag u, b = Q_J^dag z (if with_z), raw scalars; per launch slot
+// a = Q_J^dag u, b = Q_J^dag z (if with_z), raw scalars; per launch slot.
+// Left as partial sums for krylov_update where it adds them itself, unless
+// `reduce` (then a is complete in memory, for krylov_patch)
 template <typename VT>
-void krylov_dot(const KrylovWork& w, const KrylovArgs& A, bool with_z, hipStream_t s, Profiler* prof);
+void krylov_dot(const KrylovWork& w, const KrylovArgs& A, bool with_z, bool reduce, hipStream_t s, Profiler* prof);
 // v_J, next candidate, Hessenberg column J and re-orthogonalisation of column J-1
 template <typename VT>
 void krylov_update(const KrylovWork& w, const KrylovArgs& A, hipStream_t s, Profiler* prof);

@@ -65,41 +65,104 @@ __device__ inline void ld_pair(const float2* __restrict__ p, int il, double2& q0
 template <typename VT>
 constexpr int rows_per_lane() { return sizeof(VT) == 8 ? 2 : 1; }
 
-__device__ inline double2 wsum2(double2 v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    v.x += __shfl_xor(v.x, off, 64);
-    v.y += __shfl_xor(v.y, off, 64);
+// v of lane l ^ 8, 4, 2 or 1, by data-parallel moves within 16 lanes
+template <int CTRL>
+__device__ inline double dpp_move(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+__device__ inline double lane_xor8(double v) { return dpp_move<0x128>(v); }                   // row_ror:8
+__device__ inline double lane_xor4(double v) { return dpp_move<0x1B>(dpp_move<0x141>(v)); }  // half mirror, quad reversal
+__device__ inline double lane_xor2(double v) { return dpp_move<0x4E>(v); }                    // quad_perm 2 3 0 1
+__device__ inline double lane_xor1(double v) { return dpp_move<0xB1>(v); }                    // quad_perm 1 0 3 2
+
+// a of lanes with the bit clear beside b of its partners, and the other way
+// round: after the swap x + y is, in a lane with the bit clear, a + (a of
+// lane ^ bit), and with the bit set the same of b
+template <int BIT>
+__device__ inline double swap_add(double a, double b) {
+  static_assert(BIT == 32 || BIT == 16, "half-wavefront or row swaps");
+  const unsigned al = (unsigned)__double2loint(a), ah = (unsigned)__double2hiint(a);
+  const unsigned bl = (unsigned)__double2loint(b), bh = (unsigned)__double2hiint(b);
+  if constexpr (BIT == 32) {
+    const auto l = __builtin_amdgcn_permlane32_swap(al, bl, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
+    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+  } else {
+    const auto l = __builtin_amdgcn_permlane16_swap(al, bl, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
+    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
   }
+}
+__device__ inline double pick_add8(double a, double b, bool set) {
+  const double keep = set ? b : a, send = set ? a : b;
+  return keep + lane_xor8(send);
+}
+
+// the sum over the 64 lanes, in every lane: an xor butterfly with offsets 32,
+// 16, 8, 4, 2, 1 without LDS
+__device__ inline double wsum1(double v) {
+  v = swap_add<32>(v, v);
+  v = swap_add<16>(v, v);
+  v += lane_xor8(v);
+  v += lane_xor4(v);
+  v += lane_xor2(v);
+  v += lane_xor1(v);
   return v;
 }
-__device__ inline double wsum1(double v) {
+__device__ inline double2 wsum2(double2 v) { return make_double2(wsum1(v.x), wsum1(v.y)); }
+
+// Sums of NV values over the 64 lanes, each in the order of an xor butterfly
+// with offsets 32, 16, 8, 4, 2, 1.  The first log2(NV) steps also halve the
+// number of values a lane holds (a lane keeps the half its bit names), so the
+// 8 values of two columns take 10 exchanges instead of 48.  On return a lane
+// holds the sum of value (its top log2(NV) bits).
+template <int NV>
+__device__ inline double wave_sums(double (&v)[NV], int lane) {
+  static_assert(NV == 4 || NV == 8, "one or two columns");
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
+  for (int i = 0; i < NV / 2; ++i) v[i] = swap_add<32>(v[i], v[i + NV / 2]);
+#pragma unroll
+  for (int i = 0; i < NV / 4; ++i) v[i] = swap_add<16>(v[i], v[i + NV / 4]);
+  if constexpr (NV >= 8) {
+    v[0] = pick_add8(v[0], v[1], lane & 8);
+  } else {
+    v[0] += lane_xor8(v[0]);
+  }
+  v[0] += lane_xor4(v[0]);
+  v[0] += lane_xor2(v[0]);
+  v[0] += lane_xor1(v[0]);
+  return v[0];
 }
 
 // wavefront index as a scalar (uniform) value
 __device__ inline int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 
-// column c of Q for right-hand side slot r
-template <typename VT>
-__device__ inline double2 qload(const KrylovArgs& A, int r, int c, int i) {
-  if (c < A.m) return A.S[(size_t)c * A.ldq + i];
-  const VT* V = static_cast<const VT*>(A.V) + (size_t)r * A.vstride + (size_t)(c - A.m) * A.ldq;
-  return ld2(V, i);
-}
-
 // launch position z (an index into the batch) -> buffer slot and step
 __device__ inline int slot_of(const KrylovArgs& A, int z) { return A.act[z]; }
 __device__ inline int step_of(const KrylovArgs& A, int z) { return A.jdev ? *A.jdev + A.joff : A.jv[z]; }
 
+// Workgroup i runs on XCD i mod 8.  The dot and update passes give the rows of
+// tile t (512 rows) to XCD t mod 8, so the columns that the dot pass reads
+// into an XCD's 4 MB of L2 are still there for the update pass, and the other
+// way round, as far as they fit (the L2 keeps its contents from one kernel to
+// the next: 32 MB read twice by the same XCDs take no longer than an empty
+// kernel, read by other XCDs 5.8 us).  i -> (tile t, index in [0, per)):
+// false for the padding.
+constexpr int kXcds = 8;
+__device__ inline bool tile_of(unsigned i, unsigned per, int ntiles, int& t, unsigned& in) {
+  const unsigned l = i / kXcds, q = l / per;
+  in = l - q * per;
+  t = (int)(q * kXcds + i % kXcds);
+  return t < ntiles;
+}
+inline size_t tile_grid(size_t per, int ntiles) { return (size_t)kXcds * per * ((ntiles + kXcds - 1) / kXcds); }
+
 // ---------------------------------------------------------------------------
-// dot pass: per (row tile, column group) partial sums of Q^dag u and Q^dag z,
-// plus |u|^2, u^dag z, |z|^2 per row tile.  No cross-workgroup communication:
-// the partials are reduced by kred_kernel in a fixed order.
-// the rows past N carry zero weights (uv = zv = 0 there) and load a valid
-// row instead: unconditional loads, all in flight together
+// dot pass: sums of Q^dag u and Q^dag z over row tiles, plus |u|^2, u^dag z,
+// |z|^2 per tile.  Rows past N carry zero weights (uv = zv = 0 there) and load
+// a valid row instead: unconditional loads, all in flight together.
 // Row of a lane's slot t in a tile: R = 1, row0 + 64 t + lane; R = 2 (FP32
 // columns), the pair row0 + 128 (t / 2) + 2 lane + {0, 1}
 template <int R>
@@ -107,98 +170,308 @@ __device__ inline int dot_row(int row0, int t, int lane) {
   return R == 1 ? row0 + t * 64 + lane : row0 + (t >> 1) * 128 + 2 * lane + (t & 1);
 }
 
-template <typename QT, int R>
-__device__ inline void dot_cols(const QT* __restrict__ q, const double2 uv[kRpl], const double2 zv[kRpl], int row0,
-                                int lane, int N, double2& aa, double2& bb) {
-  double2 qv[kRpl];
-  if constexpr (R == 1) {
+// a lane's kRpl rows of one column, as loaded: FP64 entries, or FP32 pairs
+template <typename QT>
+struct ColBuf {
+  double2 q[kRpl];
+  template <int R>
+  __device__ inline void load(const double2* __restrict__ p, int row0, int lane, int N) {
 #pragma unroll
-    for (int t = 0; t < kRpl; ++t) qv[t] = ld2(q, min(dot_row<1>(row0, t, lane), N - 1));
-  } else {
-    // N is even, so a pair lies wholly below N or wholly at or above it
+    for (int t = 0; t < kRpl; t += R) {
+      const int i = min(dot_row<R>(row0, t, lane), N - R);
 #pragma unroll
-    for (int t = 0; t < kRpl; t += 2) ld_pair(q, min(dot_row<2>(row0, t, lane), N - 2), qv[t], qv[t + 1]);
-  }
-#pragma unroll
-  for (int t = 0; t < kRpl; ++t) {
-    aa = cfmac(qv[t], uv[t], aa);
-    bb = cfmac(qv[t], zv[t], bb);
-  }
-}
-
-// workgroup id = z + nb (rt + nrt cg): batch position fastest, then row
-// tile; column group cg holds columns [4 CPW cg, 4 CPW (cg + 1)), CPW per wavefront
-template <typename VT, int CPW>
-__global__ void __launch_bounds__(256) kdot_kernel(KrylovArgs A, int with_z) {
-  constexpr int R = rows_per_lane<VT>();
-  const int zb = blockIdx.x % A.nb, rest = blockIdx.x / A.nb;
-  const int rt = rest % A.nrt_dot, cg = rest / A.nrt_dot;
-  const int r = slot_of(A, zb);
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int N = A.N, J = A.m + step_of(A, zb);
-  const int row0 = rt * kDRows;
-  const double2* __restrict__ u = A.u + (size_t)r * A.ustride;
-  const VT* __restrict__ z = static_cast<const VT*>(A.z) + (size_t)r * A.zstride;
-  double2* Pa = A.Pa + (size_t)r * A.pstride;
-  double2* Pb = A.Pb + (size_t)r * A.pstride;
-  double* Pcd = A.Pcd + (size_t)r * A.cdstride;
-
-  double2 uv[kRpl], zv[kRpl];
-#pragma unroll
-  for (int t = 0; t < kRpl; ++t) {
-    const int i = dot_row<R>(row0, t, lane);
-    uv[t] = (i < N) ? u[i] : make_double2(0.0, 0.0);
-    zv[t] = (with_z && i < N) ? ld2(z, i) : make_double2(0.0, 0.0);
-  }
-  const int cw = (cg * 4 + wave) * CPW;  // first column of this wavefront
-#pragma unroll
-  for (int cc = 0; cc < CPW; ++cc) {
-    const int c = cw + cc;
-    if (c < J) {
-      double2 aa = make_double2(0.0, 0.0), bb = make_double2(0.0, 0.0);
-      if (c < A.m) {
-        dot_cols<double2, R>(A.S + (size_t)c * A.ldq, uv, zv, row0, lane, N, aa, bb);
-      } else {
-        const VT* q = static_cast<const VT*>(A.V) + (size_t)r * A.vstride + (size_t)(c - A.m) * A.ldq;
-        dot_cols<VT, R>(q, uv, zv, row0, lane, N, aa, bb);
-      }
-      aa = wsum2(aa);
-      bb = wsum2(bb);
-      if (lane == 0) {
-        Pa[(size_t)rt * A.ldp + c] = aa;
-        Pb[(size_t)rt * A.ldp + c] = bb;
-      }
+      for (int k = 0; k < R; ++k) q[t + k] = p[i + k];
     }
   }
-  if (cg == 0 && wave == 0) {
-    // |u|^2, u^dag z, |z|^2 of this row tile (the four wavefronts hold the
-    // same rows, so one of them accounts for the tile)
+  __device__ inline double2 at(int t) const { return q[t]; }
+};
+template <>
+struct ColBuf<float2> {
+  float4 q[kRpl / 2];
+  template <int R>
+  __device__ inline void load(const float2* __restrict__ p, int row0, int lane, int N) {
+    static_assert(R == 2, "FP32 columns come in row pairs");
+    // N is even, so a pair lies wholly below N or wholly at or above it
+#pragma unroll
+    for (int t = 0; t < kRpl; t += 2)
+      q[t / 2] = *reinterpret_cast<const float4*>(p + min(dot_row<2>(row0, t, lane), N - 2));
+  }
+  __device__ inline double2 at(int t) const {
+    const float4 v = q[t / 2];
+    return t & 1 ? make_double2((double)v.z, (double)v.w) : make_double2((double)v.x, (double)v.y);
+  }
+};
+
+// the tile's weights u and z in a lane, and its raw sums |u|^2, u^dag z, |z|^2
+template <typename VT, int R>
+struct Weights {
+  double2 u[kRpl], z[kRpl];
+  __device__ inline void load(const KrylovArgs& A, int r, int row0, int lane, bool with_z) {
+    const double2* __restrict__ up = A.u + (size_t)r * A.ustride;
+    const VT* __restrict__ zp = static_cast<const VT*>(A.z) + (size_t)r * A.zstride;
+    const bool whole = row0 + kDRows <= A.N;  // uniform; else rows past N carry zeros
+#pragma unroll
+    for (int t = 0; t < kRpl; ++t) {
+      const int i = dot_row<R>(row0, t, lane);
+      u[t] = up[min(i, A.N - 1)];
+      z[t] = with_z ? ld2(zp, min(i, A.N - 1)) : make_double2(0.0, 0.0);
+    }
+    if (whole) return;
+#pragma unroll
+    for (int t = 0; t < kRpl; ++t)
+      if (dot_row<R>(row0, t, lane) >= A.N) u[t] = z[t] = make_double2(0.0, 0.0);
+  }
+  __device__ inline void raw_sums(double* __restrict__ out, int lane) const {
     double cs = 0.0, zs = 0.0;
     double2 ds = make_double2(0.0, 0.0);
 #pragma unroll
     for (int t = 0; t < kRpl; ++t) {
-      cs += cabs2(uv[t]);
-      zs += cabs2(zv[t]);
-      ds = cfmac(uv[t], zv[t], ds);
+      cs += cabs2(u[t]);
+      zs += cabs2(z[t]);
+      ds = cfmac(u[t], z[t], ds);
     }
-    cs = wsum1(cs);
-    zs = wsum1(zs);
-    ds = wsum2(ds);
-    if (lane == 0) {
-      Pcd[4 * rt + 0] = cs;
-      Pcd[4 * rt + 1] = ds.x;
-      Pcd[4 * rt + 2] = ds.y;
-      Pcd[4 * rt + 3] = zs;
-    }
+    double v[4] = {cs, ds.x, ds.y, zs};
+    const double sum = wave_sums<4>(v, lane);
+    if ((lane & 15) == 0) out[lane >> 4] = sum;
   }
+  // the sums of C columns: value 4 cc + {0, 1, 2, 3} is Re a, Im a, Re b, Im b
+  // of column cc; on return lane l holds value l / (16 / C)
+  template <typename QT, int C>
+  __device__ inline double dot(const ColBuf<QT> (&q)[C], int lane) const {
+    double v[4 * C];
+#pragma unroll
+    for (int cc = 0; cc < C; ++cc) {
+      double2 aa = make_double2(0.0, 0.0), bb = make_double2(0.0, 0.0);
+#pragma unroll
+      for (int t = 0; t < kRpl; ++t) {
+        const double2 qv = q[cc].at(t);
+        aa = cfmac(qv, u[t], aa);
+        bb = cfmac(qv, z[t], bb);
+      }
+      v[4 * cc] = aa.x;
+      v[4 * cc + 1] = aa.y;
+      v[4 * cc + 2] = bb.x;
+      v[4 * cc + 3] = bb.y;
+    }
+    return wave_sums<4 * C>(v, lane);
+  }
+};
+
+// C columns from c0 on of the Schur (S) or Krylov part; columns past cend
+// reload the last one (their sums are not used)
+template <typename QT, int C, int R>
+__device__ inline void load_cols(ColBuf<QT> (&q)[C], const QT* __restrict__ base, size_t ldq, int c0, int cend,
+                                 int row0, int lane, int N) {
+#pragma unroll
+  for (int cc = 0; cc < C; ++cc) q[cc].template load<R>(base + (size_t)min(c0 + cc, cend - 1) * ldq, row0, lane, N);
+}
+
+// Columns [c0, c0 + C ng) of one base against the tile's weights, C at a time,
+// the next C loaded before the sums of the current ones; put(c, k, sum) takes
+// value k of column c (counted from the base)
+template <typename QT, int C, int R, typename W, typename Put>
+__device__ inline void dot_walk(const W& w, const QT* __restrict__ base, size_t ldq, int c0, int ng, int cend,
+                                int row0, int lane, int N, Put put) {
+  auto out = [&](int cb, double sum) {
+    constexpr int kLanes = 16 / C;  // lanes that hold the same value
+    const int k = lane / kLanes;
+    if (lane % kLanes == 0 && cb + k / 4 < cend) put(cb + k / 4, k % 4, sum);
+  };
+  ColBuf<QT> qa[C], qb[C];
+  load_cols<QT, C, R>(qa, base, ldq, c0, cend, row0, lane, N);
+  for (int g = 0; g < ng; g += 2) {
+    const int cb = c0 + g * C;
+    if (cb >= cend) return;
+    const bool second = g + 1 < ng && cb + C < cend;
+    if (second) load_cols<QT, C, R>(qb, base, ldq, cb + C, cend, row0, lane, N);
+    out(cb, w.template dot<QT, C>(qa, lane));
+    if (!second) return;
+    if (g + 2 < ng && cb + 2 * C < cend) load_cols<QT, C, R>(qa, base, ldq, cb + 2 * C, cend, row0, lane, N);
+    out(cb + C, w.template dot<QT, C>(qb, lane));
+  }
+}
+
+// Column groups of a launch: gs groups of `width` Schur columns, then the
+// Krylov columns' groups (a group never mixes the two)
+struct ColGroups {
+  int gs, width;
+};
+
+// Many row tiles: a workgroup's four wavefronts take ng batches of C columns
+// each of one tile; the partial sums of every tile go to memory and
+// kred_kernel adds them in a fixed order.  Bound by memory: 12^4 x 32 slots,
+// 40 Schur and 130 FP32 columns, 8.4 GB: 1.88 ms with the reduction, 4.5 TB/s
+// (2.45 ms with one column's loads in flight and six shuffles for each of its
+// four sums); without Schur columns 4.9 TB/s, of the 6.1 that a plain read of
+// this size reaches.
+template <typename VT, int C>
+__global__ void __launch_bounds__(256) kdot_kernel(KrylovArgs A, int with_z, ColGroups G, int ng, int ngroups) {
+  constexpr int R = rows_per_lane<VT>();
+  int rt;
+  unsigned in;
+  if (!tile_of(blockIdx.x, A.nb * ngroups, A.nrt_dot, rt, in)) return;
+  const int cg = (int)(in / A.nb), zb = (int)(in - (unsigned)cg * A.nb);
+  const int r = slot_of(A, zb);
+  const int lane = threadIdx.x & 63, wave = wave_id();
+  const int N = A.N, kcols = step_of(A, zb), J = A.m + kcols;
+  const int row0 = rt * kDRows;
+  const bool schur = cg < G.gs;
+  const int c0 = (schur ? cg : cg - G.gs) * G.width + wave * ng * C, cend = schur ? A.m : kcols;
+  const bool raw = cg == 0 && wave == 0;
+  if (c0 >= cend && !raw) return;
+  Weights<VT, R> w;
+  w.load(A, r, row0, lane, with_z);
+  if (raw) w.raw_sums(A.Pcd + (size_t)r * A.cdstride + 4 * rt, lane);
+  if (c0 >= cend) return;
+  double* pa = reinterpret_cast<double*>(A.Pa + (size_t)r * A.pstride + (size_t)rt * A.ldp);
+  double* pb = reinterpret_cast<double*>(A.Pb + (size_t)r * A.pstride + (size_t)rt * A.ldp);
+  const int off = schur ? 0 : A.m;
+  auto put = [&](int c, int k, double sum) { (k < 2 ? pa : pb)[2 * (off + c) + (k & 1)] = sum; };
+  // FP64 Schur columns beside FP32 Krylov columns: half the batch for the same bytes
+  constexpr int CS = R == 2 && C > 1 ? C / 2 : C;
+  if (schur)
+    dot_walk<double2, CS, R>(w, A.S, A.ldq, c0, ng * (C / CS), cend, row0, lane, N, put);
+  else
+    dot_walk<VT, C, R>(w, static_cast<const VT*>(A.V) + (size_t)r * A.vstride, A.ldq, c0, ng, cend, row0, lane, N,
+                       put);
+}
+
+// lane's part of raw scalar q (0..3) over the row tiles: tiles lane, lane + 64, ...
+__device__ inline double raw_part(const double* __restrict__ Pcd, int q, int nrt, int lane) {
+  double acc = 0.0;
+  for (int t0 = lane; t0 < nrt; t0 += 64 * 8) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = (t0 + 64 * u < nrt) ? Pcd[4 * (t0 + 64 * u) + q] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) acc += v[u];
+  }
+  return acc;
+}
+
+// Few row tiles (kPartTiles or fewer): a workgroup takes C columns and the
+// tiles p, p + 8, ... of part p = 0..7, a wavefront per tile, and adds their
+// sums in order; the update pass adds the eight parts in order itself.  The
+// sums are those of kdot_kernel and kred_kernel, without the reduction's
+// launch (3.6 us of a step).
+constexpr int kParts = 8;
+constexpr int kPartTiles = 64;
+template <typename VT, int C>
+__global__ void __launch_bounds__(64 * kPartTiles / kParts) kdot_parts_kernel(KrylovArgs A, int with_z, ColGroups G,
+                                                                      int ngroups) {
+  constexpr int R = rows_per_lane<VT>();
+  const int part = blockIdx.x % kParts;  // tiles of one part: one XCD
+  const unsigned l = blockIdx.x / kParts;
+  const int cg = (int)(l / A.nb), zb = (int)(l - (unsigned)cg * A.nb);
+  const int r = slot_of(A, zb);
+  const int lane = threadIdx.x & 63, wave = wave_id();
+  const int kcols = step_of(A, zb);
+  const bool schur = cg < G.gs;
+  const int c0 = (schur ? cg : cg - G.gs) * C, cend = schur ? A.m : kcols;
+  const bool raw = cg == 0;
+  const int ntiles = part < A.nrt_dot ? (A.nrt_dot - part + kParts - 1) / kParts : 0;
+  __shared__ double sums[kPartTiles / kParts][4 * C];
+  const int nw = blockDim.x >> 6;
+  auto walk = [&](const auto* base, auto tag) {
+    using QT = decltype(tag);
+    for (int tl = wave; tl < ntiles; tl += nw) {
+      const int rt = part + kParts * tl, row0 = rt * kDRows;
+      ColBuf<QT> q[C];
+      if (c0 < cend) load_cols<QT, C, R>(q, base, A.ldq, c0, cend, row0, lane, A.N);
+      Weights<VT, R> w;
+      w.load(A, r, row0, lane, with_z);
+      if (c0 < cend) {
+        const double sum = w.template dot<QT, C>(q, lane);
+        if (lane % (16 / C) == 0) sums[tl][lane / (16 / C)] = sum;
+      }
+      if (raw) w.raw_sums(A.Pcd + (size_t)r * A.cdstride + 4 * rt, lane);
+    }
+  };
+  if (c0 < cend || raw) {
+    if (schur)
+      walk(A.S, double2{});
+    else
+      walk(static_cast<const VT*>(A.V) + (size_t)r * A.vstride, VT{});
+  }
+  __syncthreads();
+  const int k = threadIdx.x;
+  if (k < 4 * C && c0 + k / 4 < cend) {
+    double acc = 0.0;
+    for (int tl = 0; tl < ntiles; ++tl) acc += sums[tl][k];
+    double2* P = (k & 2 ? A.Pb : A.Pa) + (size_t)r * A.pstride + (size_t)part * A.ldp;
+    reinterpret_cast<double*>(P + (schur ? 0 : A.m) + c0 + k / 4)[k & 1] = acc;
+  }
+}
+
+// The fewest row tiles (kParts or fewer: one per part): a workgroup takes C
+// columns over all rows, a wavefront per tile, and adds the tiles' sums from
+// LDS in order, so that a, b and the raw scalars are complete.
+template <typename VT, int C>
+__global__ void __launch_bounds__(64 * kParts) kdot_whole_kernel(KrylovArgs A, int with_z, ColGroups G) {
+  constexpr int R = rows_per_lane<VT>();
+  const int cg = blockIdx.x / A.nb, zb = blockIdx.x - cg * A.nb;
+  const int r = slot_of(A, zb);
+  const int lane = threadIdx.x & 63, wave = wave_id();
+  const int kcols = step_of(A, zb);
+  const bool schur = cg < G.gs;
+  const int c0 = (schur ? cg : cg - G.gs) * C, cend = schur ? A.m : kcols;
+  const bool raw = cg == 0;
+  if (c0 >= cend && !raw) return;
+  const int nrt = A.nrt_dot, nw = blockDim.x >> 6;
+  __shared__ double sums[kParts][4 * C];
+  __shared__ double rsum[4 * kParts];
+  auto walk = [&](const auto* base, auto tag) {
+    using QT = decltype(tag);
+    for (int rt = wave; rt < nrt; rt += nw) {
+      const int row0 = rt * kDRows;
+      ColBuf<QT> q[C];
+      if (c0 < cend) load_cols<QT, C, R>(q, base, A.ldq, c0, cend, row0, lane, A.N);
+      Weights<VT, R> w;
+      w.load(A, r, row0, lane, with_z);
+      if (c0 < cend) {
+        const double sum = w.template dot<QT, C>(q, lane);
+        if (lane % (16 / C) == 0) sums[rt][lane / (16 / C)] = sum;
+      }
+      if (raw) w.raw_sums(rsum + 4 * rt, lane);
+    }
+  };
+  if (schur)
+    walk(A.S, double2{});
+  else
+    walk(static_cast<const VT*>(A.V) + (size_t)r * A.vstride, VT{});
+  __syncthreads();
+  const int k = threadIdx.x;
+  if (k < 4 * C && c0 + k / 4 < cend) {
+    double acc = 0.0;
+    for (int rt = 0; rt < nrt; ++rt) acc += sums[rt][k];
+    double2* out = (k & 2 ? A.b : A.a) + (size_t)r * A.abstride;
+    reinterpret_cast<double*>(out + (schur ? 0 : A.m) + c0 + k / 4)[k & 1] = acc;
+  }
+  if (raw)  // scalar q of wavefronts q, q + nw, ...
+    for (int q = wave; q < 4; q += nw) {
+      const double acc = wsum1(raw_part(rsum, q, nrt, lane));
+      if (lane == 0) A.sc[(size_t)r * kScStride + kScRawC + q] = acc;
+    }
+}
+
+// Column c of a (or b) from the eight parts P, in order
+__device__ inline double2 sum_parts(const double2* __restrict__ P, int ldp, int c) {
+  double2 v[kParts];
+#pragma unroll
+  for (int p = 0; p < kParts; ++p) v[p] = P[(size_t)p * ldp + c];
+  double2 sum = v[0];
+#pragma unroll
+  for (int p = 1; p < kParts; ++p) sum = cadd(sum, v[p]);
+  return sum;
 }
 
 // reduce the dot partials over row tiles in a fixed order: 32 columns per
 // workgroup, 8 threads per column (each sums every 8th row tile), then a
-// fixed-order combine; workgroup 0 also sums the scalars c, d, |z|^2
-__global__ void __launch_bounds__(256) kred_kernel(KrylovArgs A) {
+// fixed-order combine; workgroup 0 also sums the scalars c, d, |z|^2.
+// parts: the partials are those of kdot_parts_kernel (eight per column)
+__global__ void __launch_bounds__(256) kred_kernel(KrylovArgs A, int parts) {
   const int r = slot_of(A, blockIdx.z);
-  const int J = A.m + step_of(A, blockIdx.z), nrt = A.nrt_dot;
+  const int J = A.m + step_of(A, blockIdx.z), nrt = parts ? kParts : A.nrt_dot;
   const double2* Pa = A.Pa + (size_t)r * A.pstride;
   const double2* Pb = A.Pb + (size_t)r * A.pstride;
   const double* Pcd = A.Pcd + (size_t)r * A.cdstride;
@@ -236,18 +509,10 @@ __global__ void __launch_bounds__(256) kred_kernel(KrylovArgs A) {
     A.b[(size_t)r * A.abstride + c] = tb;
   }
   if (blockIdx.x == 0) {
-    // wavefront q sums scalar q over the row tiles: lane partials (tiles
-    // lane, lane + 64, ...) then a fixed butterfly
+    // wavefront q sums scalar q over the row tiles: lane partials, then a
+    // fixed butterfly
     const int q = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    double acc = 0.0;
-    for (int t0 = lane; t0 < nrt; t0 += 64 * 8) {
-      double v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = (t0 + 64 * u < nrt) ? Pcd[4 * (t0 + 64 * u) + q] : 0.0;
-#pragma unroll
-      for (int u = 0; u < 8; ++u) acc += v[u];
-    }
-    acc = wsum1(acc);
+    const double acc = wsum1(raw_part(Pcd, q, A.nrt_dot, lane));
     if (lane == 0) A.sc[(size_t)r * kScStride + kScRawC + q] = acc;
   }
 }
@@ -263,24 +528,9 @@ struct StepScalars {
   double scale;
 };
 
-// this thread's columns of a and b: the first two are loaded by the caller
-// (early, so their latency overlaps other work), the rest here
-template <int NT>
-__device__ inline void scalar_partials(const double2* av, const double2* bv, int J, double2 a0, double2 b0,
-                                       double2 a1, double2 b1, double& s0, double2& s12) {
-  const int tid = threadIdx.x;
-  s0 = cabs2(a0) + cabs2(a1);
-  s12 = cadd(cmulc(a0, b0), cmulc(a1, b1));
-  for (int c = tid + 2 * NT; c < J; c += NT) {
-    const double2 x1 = av[c], x2 = bv[c];
-    s0 += cabs2(x1);
-    s12 = cadd(s12, cmulc(x1, x2));
-  }
-}
-
 template <int NW>
-__device__ StepScalars step_scalars(const KrylovArgs& A, int r, int j, double s0, double2 s12,
-                                    double* red /* LDS [3][NW] */) {
+__device__ StepScalars step_scalars(const KrylovArgs& A, int r, double ref, double s0, double2 s12,
+                                    double* red /* LDS [3][NW] */, const double* raw /* the raw sums */) {
   const int lane = threadIdx.x & 63, wave = wave_id();
   s0 = wsum1(s0);
   s12 = wsum2(s12);
@@ -297,21 +547,63 @@ __device__ StepScalars step_scalars(const KrylovArgs& A, int r, int j, double s0
     ab.x += red[NW + w];
     ab.y += red[2 * NW + w];
   }
-  const double* sc = A.sc + (size_t)r * kScStride;
   StepScalars st;
-  const double c = sc[kScRawC];
-  const double2 d = make_double2(sc[kScRawC + 1], sc[kScRawC + 2]);
-  const double zz = sc[kScRawC + 3];
+  const double c = raw[0];
+  const double2 d = make_double2(raw[1], raw[2]);
+  const double zz = raw[3];
   const double rho2 = c - aa;
   const double rho = rho2 > 0.0 ? sqrt(rho2) : 0.0;
   st.finite = isfinite(c) && isfinite(d.x) && isfinite(d.y) && isfinite(zz);
-  st.brk = !(rho > A.brk_tol * sc[kScRef + (j & 1)]) || !st.finite;
+  st.brk = !(rho > A.brk_tol * ref) || !st.finite;
   st.inv = st.brk ? 0.0 : 1.0 / rho;
   st.rho = st.brk ? 0.0 : rho;
   st.gam = cscale(csub(d, ab), st.inv);
   st.gr = cscale(st.gam, st.inv);
   st.scale = sqrt(zz) * st.inv;
   return st;
+}
+
+// Coefficients a, b of up to kCoefCap columns of a step in LDS, as every
+// wavefront of the update pass reads them; longer steps take them in spans.
+// kCoefPad zeros follow, the coefficients of a last batch's missing columns.
+constexpr int kCoefCap = 1024;
+constexpr int kCoefPad = 64;
+struct Coefs {
+  const double2 *a, *b;  // LDS, column c at c - c0
+  int c0;
+};
+
+// a, b of columns [c0, c0 + n) into LDS from the eight parts of the dot pass
+__device__ inline void fetch_coefs(const KrylovArgs& A, int r, int c0, int n, double2* la, double2* lb) {
+  const int tid = threadIdx.x, nt = blockDim.x;
+  const double2* Pa = A.Pa + (size_t)r * A.pstride;
+  const double2* Pb = A.Pb + (size_t)r * A.pstride;
+  for (int i = tid; i < 2 * n; i += nt) {
+    const bool second = i >= n;
+    const int c = second ? i - n : i;
+    (second ? lb : la)[c] = sum_parts(second ? Pb : Pa, A.ldp, c0 + c);
+  }
+  for (int i = tid; i < kCoefPad; i += nt) la[n + i] = lb[n + i] = make_double2(0.0, 0.0);
+}
+
+// the raw sums u^dag u, u^dag z (re, im), |z|^2 into LDS: wavefront q < 4 sums
+// scalar q over the row tiles
+__device__ inline void fetch_raw(const KrylovArgs& A, int r, double* raw) {
+  const int lane = threadIdx.x & 63, wave = wave_id();
+  if (wave >= 4) return;
+  const double acc = wsum1(raw_part(A.Pcd + (size_t)r * A.cdstride, wave, A.nrt_dot, lane));
+  if (lane == 0) raw[wave] = acc;
+}
+
+// this thread's partial sums over the columns c = tid, tid + NT, ... of a span
+// (spans are multiples of NT): |a_c|^2 and conj(a_c) b_c
+template <int NT>
+__device__ inline void scalar_partials(const double2* la, const double2* lb, int n, double& s0, double2& s12) {
+  for (int i = threadIdx.x; i < n; i += NT) {
+    const double2 x1 = la[i], x2 = lb[i];
+    s0 += cabs2(x1);
+    s12 = cadd(s12, cmulc(x1, x2));
+  }
 }
 
 // Hessenberg column J and the re-orthogonalisation of column J-1, one row per
@@ -358,70 +650,193 @@ __device__ void hcol_row_wave(const KrylovArgs& A, int r, int j, int row, int la
   H[(size_t)J * ldh + row] = cscale(csub(g, ha), inv);
 }
 
-// sa += sum_c q_c[i] a_c, sb += sum_c q_c[i] b_c over the columns c = c0,
-// c0 + NW, ... < cend, in that order; column c sits at base + (c - cofs)
-// ldq.  Each batch of KB column loads (and their coefficients) is issued
-// before its arithmetic, the last, partial batch too, so a sweep costs
-// ceil(ncols / KB) memory round trips: a slot past cend reloads column
-// cend - 1 (a cache hit) and adds it with coefficient zero, which leaves the
-// sums unchanged since basis vectors are finite.
+// The same row with the coefficients in LDS; the gather of its first 4 x 64
+// entries and its entry of column J-1 are under way before they are (start).
+struct HRow {
+  double2 hv[4], hl, ha, c0;
+  __device__ inline void load(const double2* H, int ldh, int row, int lane, int l0, int end) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int l = l0 + t * 64 + lane;
+      if (l < end) hv[t] = H[(size_t)l * ldh + row];
+    }
+  }
+  __device__ inline void start(const KrylovArgs& A, int r, int j, int row, int lane, int lim) {
+    const int J = A.m + j;
+    ha = make_double2(0.0, 0.0);
+    if (row >= J) return;
+    const double2* H = A.H + (size_t)r * A.hstride;
+    load(H, A.ldh, row, lane, 0, lim);
+    if (j > 0)
+      hl = H[(size_t)(J - 1) * A.ldh + row];
+    else if (row < A.m)
+      c0 = A.c0[(size_t)r * A.c0stride + row];
+  }
+  // columns l = lane, lane + 64, ... of [c0, c0 + n) below lim, in order, 4
+  // loads in flight per lane
+  __device__ inline void sum(const KrylovArgs& A, int r, int row, int lane, int c0, int n, int lim,
+                             const double2* la) {
+    const double2* H = A.H + (size_t)r * A.hstride;
+    const int end = min(c0 + n, lim);
+    for (int l0 = c0; l0 < end; l0 += 4 * 64) {
+      if (l0 > 0) load(H, A.ldh, row, lane, l0, end);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int l = l0 + t * 64 + lane;
+        if (l < end) ha = cfma(hv[t], la[l - c0], ha);
+      }
+    }
+  }
+  __device__ inline void store(const KrylovArgs& A, int r, int j, int row, int lane, double2 b_row, double2 a_row,
+                               double2 a_last, const StepScalars& st) {
+    const int J = A.m + j;
+    double2* H = A.H + (size_t)r * A.hstride;
+    ha = wsum2(ha);
+    if (lane != 0) return;
+    const double2 g = (row < J) ? b_row : st.gam;
+    if (j > 0) {
+      const double2 h1 = (row < J) ? cadd(hl, a_row) : make_double2(st.rho, 0.0);
+      ha = cfma(h1, a_last, ha);
+      H[(size_t)(J - 1) * A.ldh + row] = h1;
+    } else if (row < A.m) {
+      A.c0[(size_t)r * A.c0stride + row] = cadd(c0, a_row);
+    }
+    H[(size_t)J * A.ldh + row] = cscale(csub(g, ha), st.inv);
+  }
+};
+
+// sa += sum_c q_c[i] coef_c over the columns c = c0, c0 + NW, ... < cend, in
+// that order; column c sits at base + (c - cofs) ldq.  Each batch of KB column
+// loads (and their coefficients) is issued before its arithmetic, the last,
+// partial batch too: a slot past cend reloads column cend - 1 (a cache hit)
+// and adds it with coefficient zero, which leaves the sums unchanged since
+// basis vectors are finite.
 // (rows past N load row N-1 and are never written: unconditional loads; c
 // is wavefront-uniform, so the coefficients come through scalar loads)
-template <typename QT, bool HasB, int KB, int NW>
-__device__ inline void sweep_cols(const QT* __restrict__ base, int cofs, size_t ldq, int c, int cend, int i,
-                                  const double2* __restrict__ av, const double2* __restrict__ bv, double2& sa,
-                                  double2& sb) {
+template <typename QT, int KB, int NW>
+__device__ inline void combine_cols(const QT* __restrict__ base, int cofs, size_t ldq, int c, int cend, int i,
+                                    const double2* __restrict__ cf, double2& sa) {
   const double2 zero = make_double2(0.0, 0.0);
   for (; c < cend; c += KB * NW) {
-    double2 qv[KB], ca[KB], cb[KB];
+    double2 qv[KB], ca[KB];
 #pragma unroll
     for (int t = 0; t < KB; ++t) {
       const int cc = c + t * NW, cl = min(cc, cend - 1);
       qv[t] = ld2(base + (size_t)(cl - cofs) * ldq, i);
-      ca[t] = av[cl];
-      if constexpr (HasB) cb[t] = bv[cl];
-      if (cc >= cend) {
-        ca[t] = zero;
-        if constexpr (HasB) cb[t] = zero;
-      }
+      ca[t] = cf[cl];
+      if (cc >= cend) ca[t] = zero;
     }
 #pragma unroll
-    for (int t = 0; t < KB; ++t) {
-      sa = cfma(qv[t], ca[t], sa);
-      if constexpr (HasB) sb = cfma(qv[t], cb[t], sb);
-    }
+    for (int t = 0; t < KB; ++t) sa = cfma(qv[t], ca[t], sa);
   }
 }
 
+// KB column entries of a lane's R rows, as loaded
+template <typename QT, int KB, int R>
+struct SweepBuf {
+  double2 q[KB][R];
+  __device__ inline void load(const QT* __restrict__ p, int t, int i) {
+#pragma unroll
+    for (int k = 0; k < R; ++k) q[t][k] = p[i + k];
+  }
+  __device__ inline double2 at(int t, int k) const { return q[t][k]; }
+};
+template <int KB>
+struct SweepBuf<float2, KB, 2> {
+  float4 q[KB];
+  __device__ inline void load(const float2* __restrict__ p, int t, int i) {
+    q[t] = *reinterpret_cast<const float4*>(p + i);
+  }
+  __device__ inline double2 at(int t, int k) const {
+    return k ? make_double2((double)q[t].z, (double)q[t].w) : make_double2((double)q[t].x, (double)q[t].y);
+  }
+};
 
-// sweep_cols for two adjacent rows per lane: each row's sums take the same
-// columns in the same order as sweep_cols, so the results are bitwise those
-// of one row per lane
-template <typename QT, int KB, int NW>
-__device__ inline void sweep_cols_pair(const QT* __restrict__ base, int cofs, size_t ldq, int c, int cend, int il,
-                                       const double2* __restrict__ av, const double2* __restrict__ bv,
-                                       double2 (&sa)[2], double2 (&sb)[2]) {
+// sa += sum_c q_c a_c, sb += sum_c q_c b_c for a lane's R rows over the
+// columns c, c + NW, ... < cend of one base (column c at base + (c - cofs)
+// ldq), in that order, KB columns at a time with the next batch's loads issued
+// before the current batch's sums (two register sets).  start() issues the
+// first batch, before the coefficients are needed.  A slot past cend reloads
+// column cend - 1 (a cache hit) and adds it with coefficient zero, which
+// leaves the sums unchanged since basis vectors are finite.
+template <typename QT, int KB, int NW, int R>
+struct Sweep {
+  SweepBuf<QT, KB, R> x, y;
+  const QT* base;
+  size_t ldq;
+  int cofs, c, cend, i;
+  __device__ inline void fill(SweepBuf<QT, KB, R>& b, int cb) {
+#pragma unroll
+    for (int t = 0; t < KB; ++t) b.load(base + (size_t)(min(cb + t * NW, cend - 1) - cofs) * ldq, t, i);
+  }
+  __device__ inline void start() {
+    if (c < cend) fill(x, c);
+  }
+  // the columns of one batch; LAST (the Schur part, which other columns'
+  // coefficients follow): those past cend weigh nothing
+  template <bool LAST>
+  __device__ inline void add(const SweepBuf<QT, KB, R>& b, int cb, const Coefs& cf, double2 (&sa)[R],
+                             double2 (&sb)[R]) {
+    const double2 zero = make_double2(0.0, 0.0);
+    const double2 *pa = cf.a + (cb - cf.c0), *pb = cf.b + (cb - cf.c0);
+#pragma unroll
+    for (int t = 0; t < KB; ++t) {
+      double2 ca = pa[t * NW], cb2 = pb[t * NW];
+      if (LAST && cb + t * NW >= cend) ca = cb2 = zero;
+#pragma unroll
+      for (int k = 0; k < R; ++k) {
+        sa[k] = cfma(b.at(t, k), ca, sa[k]);
+        sb[k] = cfma(b.at(t, k), cb2, sb[k]);
+      }
+    }
+  }
+  // one register set (the Schur columns, a batch or two per wavefront)
+  __device__ inline void run_single(const Coefs& cf, double2 (&sa)[R], double2 (&sb)[R]) {
+    while (c < cend) {
+      add<true>(x, c, cf, sa, sb);
+      c += KB * NW;
+      if (c < cend) fill(x, c);
+    }
+  }
+  __device__ inline void run(const Coefs& cf, double2 (&sa)[R], double2 (&sb)[R]) {
+    for (; c < cend; c += 2 * KB * NW) {
+      const int c1 = c + KB * NW, c2 = c + 2 * KB * NW;
+      if (c1 < cend) fill(y, c1);
+      add<false>(x, c, cf, sa, sb);
+      if (c1 >= cend) return;
+      if (c2 < cend) fill(x, c2);
+      add<false>(y, c1, cf, sa, sb);
+    }
+  }
+};
+
+// sa += sum_c q_c a_c, sb += sum_c q_c b_c as Sweep forms them, with the
+// reduced coefficients read from memory (c is wavefront-uniform, so they come
+// through scalar loads): one batch of KB column loads and their coefficients
+// at a time, the last, partial batch too
+template <typename QT, int KB, int NW, int R>
+__device__ inline void sweep_mem(const QT* __restrict__ base, int cofs, size_t ldq, int c, int cend, int i,
+                                 const double2* __restrict__ av, const double2* __restrict__ bv, double2 (&sa)[R],
+                                 double2 (&sb)[R]) {
   const double2 zero = make_double2(0.0, 0.0);
   for (; c < cend; c += KB * NW) {
-    double2 q0[KB], q1[KB], ca[KB], cb[KB];
+    SweepBuf<QT, KB, R> q;
+    double2 ca[KB], cb[KB];
 #pragma unroll
     for (int t = 0; t < KB; ++t) {
       const int cc = c + t * NW, cl = min(cc, cend - 1);
-      ld_pair(base + (size_t)(cl - cofs) * ldq, il, q0[t], q1[t]);
+      q.load(base + (size_t)(cl - cofs) * ldq, t, i);
       ca[t] = av[cl];
       cb[t] = bv[cl];
-      if (cc >= cend) {
-        ca[t] = zero;
-        cb[t] = zero;
-      }
+      if (cc >= cend) ca[t] = cb[t] = zero;
     }
 #pragma unroll
-    for (int t = 0; t < KB; ++t) {
-      sa[0] = cfma(q0[t], ca[t], sa[0]);
-      sb[0] = cfma(q0[t], cb[t], sb[0]);
-      sa[1] = cfma(q1[t], ca[t], sa[1]);
-      sb[1] = cfma(q1[t], cb[t], sb[1]);
-    }
+    for (int t = 0; t < KB; ++t)
+#pragma unroll
+      for (int k = 0; k < R; ++k) {
+        sa[k] = cfma(q.at(t, k), ca[t], sa[k]);
+        sb[k] = cfma(q.at(t, k), cb[t], sb[k]);
+      }
   }
 }
 
@@ -429,79 +844,143 @@ __device__ inline void sweep_cols_pair(const QT* __restrict__ base, int cofs, si
 template <int NW>
 __device__ inline int first_col(int m, int w) { return m + ((w - m % NW) + NW) % NW; }
 
-// update pass.  Per slot, the first nh workgroups compute the Hessenberg
-// column J (one row per wavefront), the next nblk each own 64 R rows and all
-// J columns: their NW wavefronts take interleaved columns, combined in LDS in
-// a fixed order.  R = 1 for FP64 columns; R = 2 for FP32 columns, whose lanes
-// then take two adjacent rows each, so that a column load is 16 bytes per
-// lane (every row's sums are the same as with R = 1).  Workgroup id = z + nb b
-// (batch position fastest).  Both kinds compute the step scalars; the
-// Hessenberg rows, a strided gather, so run beside the sweeps instead of
-// after them.
-template <typename VT, int KB, int NW>
-__global__ void __launch_bounds__(64 * NW) kupdate_kernel(KrylovArgs A, int nh) {
+// update pass.  The first workgroups (nh per slot, padded to whole rounds of
+// the XCDs) compute the Hessenberg column J (one row per wavefront), the
+// others each own 64 R rows and all J columns: their NW wavefronts take
+// interleaved columns, combined in LDS in a fixed order.  R = 1 for FP64
+// columns; R = 2 for FP32 columns, whose lanes then take two adjacent rows
+// each, so that a column load is 16 bytes per lane (every row's sums are the
+// same as with R = 1).  Both kinds compute the step scalars; the Hessenberg
+// rows, a strided gather, run beside the sweeps.  Every operand that does not
+// depend on the coefficients is loaded first.  Small launches are bound by the
+// chain of waits (4^4, 20 columns: 4.8 us, of them 2.45 an empty launch), large
+// ones by memory (8^4 x 6 slots, 30 + 150 columns, 732 MB: 140 us, 5.2 TB/s;
+// 148 us before the rows of a tile stayed on one XCD).
+// PARTS (small launches): every workgroup adds the dot pass's eight parts
+// itself and keeps the step's coefficients in LDS (steps of more than
+// kCoefCap columns in spans of that many); two register sets of KB columns.
+// Else the coefficients are reduced in memory (kred_kernel).
+template <typename VT, int KB, int NW, bool PARTS>
+__global__ void __launch_bounds__(64 * NW, 4) kupdate_kernel(KrylovArgs A, int nh, unsigned nhess) {
   constexpr int NT = 64 * NW;
   constexpr int R = rows_per_lane<VT>();
-  const int zb = blockIdx.x % A.nb, bb = blockIdx.x / A.nb;
+  constexpr int kSub = kDRows / (64 * R);  // workgroups per row tile
+  static_assert(kCoefCap % NT == 0, "spans hold whole rounds of the threads");
+  const bool hess = blockIdx.x < nhess;
+  int zb, bb;
+  if (hess) {
+    bb = blockIdx.x / A.nb;
+    zb = blockIdx.x - bb * A.nb;
+    if (bb >= nh) return;
+  } else {
+    int rt;
+    unsigned in;
+    if (!tile_of(blockIdx.x - nhess, A.nb * kSub, A.nrt_dot, rt, in)) return;
+    const int sub = (int)(in / A.nb);
+    zb = (int)(in - (unsigned)sub * A.nb);
+    bb = rt * kSub + sub;
+    if (bb * 64 * R >= A.N) return;
+  }
   const int r = slot_of(A, zb);
   const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
   const int N = A.N, j = step_of(A, zb), J = A.m + j;
+  const double2 zero = make_double2(0.0, 0.0);
+  const double ref = A.sc[(size_t)r * kScStride + kScRef + (j & 1)];
   const double2* av = A.a + (size_t)r * A.abstride;
   const double2* bv = A.b + (size_t)r * A.abstride;
-  const double2 zero = make_double2(0.0, 0.0);
-  // this thread's first two coefficients for the step scalars (loaded after
-  // the sweep in the sweep workgroups, whose registers the sweep needs)
-  double2 a0 = zero, b0 = zero, a1 = zero, b1 = zero;
-  auto load_coef = [&]() {
-    if (tid < J) {
-      a0 = av[tid];
-      b0 = bv[tid];
-    }
-    if (tid + NT < J) {
-      a1 = av[tid + NT];
-      b1 = bv[tid + NT];
-    }
-  };
   __shared__ double red[3 * NW];
-  double s0;
-  double2 s12;
-  if (bb < nh) {
-    load_coef();
-    scalar_partials<NT>(av, bv, J, a0, b0, a1, b1, s0, s12);
-    const StepScalars st = step_scalars<NW>(A, r, j, s0, s12, red);
-    const int row = bb * NW + wave;
-    if (row <= J) hcol_row_wave(A, r, j, row, lane, st);
+  __shared__ double raw_lds[4];
+  const double* raw = PARTS ? raw_lds : A.sc + (size_t)r * kScStride + kScRawC;
+  __shared__ double2 ps[2][NW][64 * R];
+  extern __shared__ double2 coef_lds[];  // PARTS: a, then b, of a span
+  static_assert(!PARTS || NW * KB <= kCoefPad, "the padding covers a batch");
+  double2* la = coef_lds;
+  double2* lb = coef_lds + min(J, kCoefCap) + kCoefPad;
+  double s0 = 0.0;
+  double2 s12 = zero;
+  if (hess) {
+    const int row = bb * NW + wave, lim = (j > 0) ? J - 1 : J;
+    if constexpr (PARTS) {
+      HRow h;
+      h.start(A, r, j, row, lane, lim);
+      fetch_raw(A, r, raw_lds);
+      double2 a_row = zero, b_row = zero, a_last = zero;
+      for (int c0 = 0; c0 < J; c0 += kCoefCap) {
+        const int n = min(J - c0, kCoefCap);
+        if (c0) __syncthreads();
+        fetch_coefs(A, r, c0, n, la, lb);
+        __syncthreads();
+        scalar_partials<NT>(la, lb, n, s0, s12);
+        if (row < J) {  // row J of columns < J-1 is below the subdiagonal (zero)
+          h.sum(A, r, row, lane, c0, n, lim, la);
+          if (row >= c0 && row < c0 + n) {
+            a_row = la[row - c0];
+            b_row = lb[row - c0];
+          }
+        }
+        if (J - 1 < c0 + n) a_last = la[J - 1 - c0];
+      }
+      __syncthreads();  // raw, where J = 0
+      const StepScalars st = step_scalars<NW>(A, r, ref, s0, s12, red, raw);
+      if (row <= J) h.store(A, r, j, row, lane, b_row, a_row, a_last, st);
+    } else {
+      scalar_partials<NT>(av, bv, J, s0, s12);
+      const StepScalars st = step_scalars<NW>(A, r, ref, s0, s12, red, raw);
+      if (row <= J) hcol_row_wave(A, r, j, row, lane, st);
+    }
     return;
   }
-  const int blk = bb - nh;
+  const int blk = bb;
   const int i = blk * 64 * R + R * lane;  // this lane's first row
   const bool ok = i < N;                  // N is even: with R = 2, row i + 1 < N too
-  // sweep: sa = Q a, sb = Q b (the step scalars enter only afterwards:
-  // Q (b - gr a) = sb - gr sa)
-  __shared__ double2 ps[2][NW][64 * R];
   const int il = ok ? i : N - R;
-  if constexpr (R == 1) {
-    double2 sa = zero, sb = zero;
-    sweep_cols<double2, true, KB, NW>(A.S, 0, A.ldq, wave, min(J, A.m), il, av, bv, sa, sb);
-    sweep_cols<VT, true, KB, NW>(static_cast<const VT*>(A.V) + (size_t)r * A.vstride, A.m, A.ldq,
-                                 first_col<NW>(A.m, wave), J, il, av, bv, sa, sb);
-    ps[0][wave][lane] = sa;
-    ps[1][wave][lane] = sb;
-  } else {
-    // FP64 Schur columns take two loads per lane: half the batch keeps the
-    // bytes in flight (the batch size does not change any sum)
-    double2 sa[2] = {zero, zero}, sb[2] = {zero, zero};
-    sweep_cols_pair<double2, (KB > 4 ? KB / 2 : 2), NW>(A.S, 0, A.ldq, wave, min(J, A.m), il, av, bv, sa, sb);
-    sweep_cols_pair<VT, KB, NW>(static_cast<const VT*>(A.V) + (size_t)r * A.vstride, A.m, A.ldq,
-                                first_col<NW>(A.m, wave), J, il, av, bv, sa, sb);
-    ps[0][wave][2 * lane] = sa[0];
-    ps[0][wave][2 * lane + 1] = sa[1];
-    ps[1][wave][2 * lane] = sb[0];
-    ps[1][wave][2 * lane + 1] = sb[1];
+  // u may be updated in place (unext == u): each lane reads its u[i] before
+  // writing u'[i], and no other thread of the step touches row i of u
+  const double2* u = A.u + (size_t)r * A.ustride;
+  const VT* __restrict__ z = static_cast<const VT*>(A.z) + (size_t)r * A.zstride;
+  double2 ui[R], zi[R];
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    ui[k] = u[il + k];
+    zi[k] = ld2(z, il + k);
   }
-  load_coef();
-  scalar_partials<NT>(av, bv, J, a0, b0, a1, b1, s0, s12);
-  const StepScalars st = step_scalars<NW>(A, r, j, s0, s12, red);  // contains __syncthreads
+  // sweep: sa = Q a, sb = Q b (the step scalars enter only afterwards:
+  // Q (b - gr a) = sb - gr sa).  FP64 Schur columns of a row pair take two
+  // loads per lane: half the batch keeps the bytes in flight (the batch size
+  // does not change any sum)
+  double2 sa[R], sb[R];
+#pragma unroll
+  for (int k = 0; k < R; ++k) sa[k] = sb[k] = zero;
+  constexpr int KS = R == 1 || KB == 2 ? KB : KB / 2;
+  const VT* V = static_cast<const VT*>(A.V) + (size_t)r * A.vstride;
+  if constexpr (PARTS) {
+    for (int c0 = 0; c0 < J || c0 == 0; c0 += kCoefCap) {
+      const int n = min(J - c0, kCoefCap), ce = c0 + n;
+      if (c0) __syncthreads();
+      fetch_coefs(A, r, c0, n, la, lb);
+      // this wavefront's columns of the span: c = wave mod NW (c0 is a multiple of NW)
+      Sweep<double2, KS, NW, R> ws{{}, {}, A.S, A.ldq, 0, c0 + wave, min(ce, A.m), il};
+      Sweep<VT, KB, NW, R> wv{{}, {}, V, A.ldq, A.m, max(c0 + wave, first_col<NW>(A.m, wave)), ce, il};
+      ws.start();
+      wv.start();
+      if (c0 == 0) fetch_raw(A, r, raw_lds);
+      __syncthreads();
+      const Coefs cf{la, lb, c0};
+      ws.run_single(cf, sa, sb);
+      wv.run(cf, sa, sb);
+      scalar_partials<NT>(la, lb, n, s0, s12);
+    }
+  } else {
+    sweep_mem<double2, KS, NW, R>(A.S, 0, A.ldq, wave, min(J, A.m), il, av, bv, sa, sb);
+    sweep_mem<VT, KB, NW, R>(V, A.m, A.ldq, first_col<NW>(A.m, wave), J, il, av, bv, sa, sb);
+    scalar_partials<NT>(av, bv, J, s0, s12);
+  }
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    ps[0][wave][R * lane + k] = sa[k];
+    ps[1][wave][R * lane + k] = sb[k];
+  }
+  const StepScalars st = step_scalars<NW>(A, r, ref, s0, s12, red, raw);  // contains __syncthreads
   if (blk == 0 && tid == 0) {
     double* sc = A.sc + (size_t)r * kScStride;
     sc[kScRho] = st.rho;
@@ -525,10 +1004,6 @@ __global__ void __launch_bounds__(64 * NW) kupdate_kernel(KrylovArgs A, int nh) 
   }
   // combine the wavefronts (fixed order) and write v_J and u'
   if (wave == 0 && ok) {
-    // u may be updated in place (unext == u): each lane reads its u[i]
-    // before writing u'[i], and no other thread of the step touches row i of u
-    const double2* u = A.u + (size_t)r * A.ustride;
-    const VT* __restrict__ z = static_cast<const VT*>(A.z) + (size_t)r * A.zstride;
     VT* vout = static_cast<VT*>(A.V) + (size_t)r * A.vstride + (size_t)(J - A.m) * A.ldq;
     double2 vo[R], nx[R];
 #pragma unroll
@@ -541,9 +1016,8 @@ __global__ void __launch_bounds__(64 * NW) kupdate_kernel(KrylovArgs A, int nh) 
         tb = cadd(tb, ps[1][w][row]);
       }
       const double2 te = csub(tb, cmul(st.gr, ta));
-      const double2 ui = u[i + q];
-      vo[q] = cscale(csub(ui, ta), st.inv);
-      nx[q] = cscale(csub(csub(ld2(z, i + q), cmul(st.gr, ui)), te), st.inv);
+      vo[q] = cscale(csub(ui[q], ta), st.inv);
+      nx[q] = cscale(csub(csub(zi[q], cmul(st.gr, ui[q])), te), st.inv);
     }
 #pragma unroll
     for (int q = 0; q < R; ++q) {
@@ -565,11 +1039,11 @@ __global__ void __launch_bounds__(kUThreads) kcombine_kernel(KrylovArgs A, const
   const int i = blockIdx.x * 64 + lane;
   const bool ok = i < A.N;
   const double2* cf = coef + (size_t)r * cstride;
-  double2 acc = make_double2(0.0, 0.0), unused = make_double2(0.0, 0.0);
+  double2 acc = make_double2(0.0, 0.0);
   const int il = ok ? i : A.N - 1;
-  sweep_cols<double2, false, kCBatch, kUWaves>(A.S, 0, A.ldq, wave, min(ncol, A.m), il, cf, nullptr, acc, unused);
-  sweep_cols<VT, false, kCBatch, kUWaves>(static_cast<const VT*>(A.V) + (size_t)r * A.vstride, A.m, A.ldq,
-                                          first_col<kUWaves>(A.m, wave), ncol, il, cf, nullptr, acc, unused);
+  combine_cols<double2, kCBatch, kUWaves>(A.S, 0, A.ldq, wave, min(ncol, A.m), il, cf, acc);
+  combine_cols<VT, kCBatch, kUWaves>(static_cast<const VT*>(A.V) + (size_t)r * A.vstride, A.m, A.ldq,
+                                     first_col<kUWaves>(A.m, wave), ncol, il, cf, acc);
   __shared__ double2 ps[kUWaves][64];
   ps[wave][lane] = acc;
   __syncthreads();
@@ -609,7 +1083,7 @@ void krylov_alloc(KrylovWork& w, int N, size_t ldq, int ncol_cap, int nslots) {
   w.ncol_cap = ncol_cap;
   w.nslots = nslots;
   w.ldp = ncol_cap;
-  w.pstride = (size_t)w.nrt_dot * ncol_cap;
+  w.pstride = (size_t)std::max(w.nrt_dot, kParts) * ncol_cap;
   w.cdstride = (size_t)4 * w.nrt_dot;
   w.abstride = (size_t)ncol_cap;
   const size_t S = (size_t)nslots;
@@ -666,27 +1140,40 @@ bool krylov_tune_valid(const KrylovTune& t) {
          (t.uw == 8 || t.uw == 16);
 }
 
-template <typename VT>
-static auto dot_kernel_for(int cpw) {
-  switch (cpw) {
-    case 1: return kdot_kernel<VT, 1>;
-    case 2: return kdot_kernel<VT, 2>;
-    default: return kdot_kernel<VT, 4>;
-  }
-}
-
-template <typename VT, int NW>
+template <typename VT, int NW, bool PARTS>
 static auto update_kernel_nw(int ub) {
+  // ub column loads in flight per lane (PARTS: two register sets of half as
+  // many, at most four columns each: 128 registers keep two workgroups per CU)
   switch (ub) {
-    case 4: return kupdate_kernel<VT, 4, NW>;
-    case 16: return kupdate_kernel<VT, 16, NW>;
-    default: return kupdate_kernel<VT, 8, NW>;
+    case 4: return kupdate_kernel<VT, (PARTS ? 2 : 4), NW, PARTS>;
+    case 16: return kupdate_kernel<VT, (PARTS ? 4 : 16), NW, PARTS>;
+    default: return kupdate_kernel<VT, (PARTS ? 4 : 8), NW, PARTS>;
   }
 }
 
-template <typename VT>
+template <typename VT, bool PARTS>
 static auto update_kernel_for(const KrylovTune& t) {
-  return t.uw == 16 ? update_kernel_nw<VT, 16>(t.ub) : update_kernel_nw<VT, 8>(t.ub);
+  return t.uw == 16 ? update_kernel_nw<VT, 16, PARTS>(t.ub) : update_kernel_nw<VT, 8, PARTS>(t.ub);
+}
+
+// wavefronts that fill the chip in the dot pass by parts
+constexpr size_t kDotWaves = 2048;
+
+// How a launch forms the dot pass's sums (the same sums in the same order).
+// Dot and update of one step back to back, by form (us; the general one with
+// its reduction): 4^4, 60 / 280 columns: Whole 9.1 / 13.6, Parts 11.5 / 15.9,
+// the former kernels 15.1 / 19.1.  6^4, 80 / 320 columns: Parts 13.2 / 34.8,
+// Whole 21.2 / 43.0, former 18.4 / 38.0.  Three slots of 1350 sites, 150
+// columns: Parts 43.5, Tiles 47.4, former 46.9.  8^4, 160 columns, FP64:
+// Tiles 52.7, Parts 52.4, former 55.7; FP32: Tiles 36.7, Parts 38.2 (56.7
+// against 47.5 at 260 columns), former 36.7.  8^4 x 6 slots, 180 columns:
+// Tiles 283.5, former 301.7.
+enum class DotForm { Whole, Parts, Tiles };
+static DotForm dot_form(const KrylovWork& w, const KrylovArgs& A) {
+  const long long work = (long long)w.nrt_dot * A.nb;
+  if (w.nrt_dot <= kParts && work <= kPartTiles) return DotForm::Whole;
+  if (w.nrt_dot <= kPartTiles && work <= 2 * kPartTiles) return DotForm::Parts;
+  return DotForm::Tiles;
 }
 
 // 16-byte loads of row pairs of the FP32 columns (dot and update passes)
@@ -700,31 +1187,67 @@ static void check_pairs(const KrylovArgs& A) {
 }
 
 template <typename VT>
-void krylov_dot(const KrylovWork& w, const KrylovArgs& Ain, bool with_z, hipStream_t s, Profiler* prof) {
+void krylov_dot(const KrylovWork& w, const KrylovArgs& Ain, bool with_z, bool reduce, hipStream_t s, Profiler* prof) {
   KrylovArgs A = Ain;
   krylov_bind(w, A);
   check_args(w, A);
   check_pairs<VT>(A);
   SGN_REQUIRE(krylov_tune_valid(A.tune), SGN_EINVAL, "krylov: invalid launch shape");
-  const int Jmax = A.m + A.jmax();
-  const int gcols = 4 * A.tune.cpw;
-  const int ngroups = Jmax > 0 ? (Jmax + gcols - 1) / gcols : 1;
+  const int kmax = A.jmax(), Jmax = A.m + kmax;
   const double vb = (double)sizeof(VT);
   double sm, sk;
   col_sums(A, sm, sk);
   const double qbytes = (double)A.N * (16.0 * sm + vb * sk);
-  // algorithmic bytes: Q, u, z read once; a, b written
-  const size_t nwg = (size_t)w.nrt_dot * ngroups * A.nb;
-  SGN_REQUIRE(nwg * 256 < (size_t(1) << 32), SGN_EINVAL, "krylov: dot grid too large");
   // per-slot work counts S for every slot
   const double cols = A.nb * (double)A.m + sk;
-  prof_launch(prof, K_KDOT, qbytes + A.nb * A.N * (16.0 + (with_z ? vb : 0.0)) + 32.0 * cols,
-              16.0 * (double)A.N * cols, dot_kernel_for<VT>(A.tune.cpw), dim3((unsigned)nwg), dim3(256), 0, s,
-              A, with_z ? 1 : 0);
-  // partial sums of every row tile read, a, b written
-  prof_launch(prof, K_KRED, 32.0 * cols * (w.nrt_dot + 1.0) + 32.0 * A.nb * w.nrt_dot,
-              4.0 * cols * w.nrt_dot, kred_kernel, dim3(std::max(1, (Jmax + 31) / 32), 1, A.nb), dim3(256), 0, s,
-              A);
+  // algorithmic bytes: Q, u, z read once; a, b written
+  const double bytes = qbytes + A.nb * A.N * (16.0 + (with_z ? vb : 0.0)) + 32.0 * cols;
+  const double flops = 16.0 * (double)A.N * cols;
+  const DotForm form = dot_form(w, A);
+  auto groups = [&](int width, int& ng) {
+    ColGroups G{(A.m + width - 1) / width, width};
+    ng = std::max(1, G.gs + (kmax + width - 1) / width);
+    return G;
+  };
+  int ngroups = 0;
+  if (form == DotForm::Whole) {
+    const ColGroups G = groups(1, ngroups);
+    const size_t nwg = (size_t)A.nb * ngroups;
+    SGN_REQUIRE(nwg * 64 * w.nrt_dot < (size_t(1) << 32), SGN_EINVAL, "krylov: dot grid too large");
+    prof_launch(prof, K_KDOT, bytes, flops, kdot_whole_kernel<VT, 1>, dim3((unsigned)nwg), dim3(64 * w.nrt_dot), 0, s,
+                A, with_z ? 1 : 0, G);
+    return;
+  }
+  const bool parts = form == DotForm::Parts;
+  if (parts) {
+    // two columns per workgroup, or one where two would leave the chip short
+    // of wavefronts
+    const int C = A.tune.cpw > 1 && (size_t)w.nrt_dot * A.nb * ((Jmax + 1) / 2) >= kDotWaves ? 2 : 1;
+    const ColGroups G = groups(C, ngroups);
+    const size_t nwg = (size_t)kParts * A.nb * ngroups;
+    const int nw = (w.nrt_dot + kParts - 1) / kParts;
+    SGN_REQUIRE(nwg * 64 * nw < (size_t(1) << 32), SGN_EINVAL, "krylov: dot grid too large");
+    prof_launch(prof, K_KDOT, bytes, flops,
+                C == 1 ? kdot_parts_kernel<VT, 1> : kdot_parts_kernel<VT, 2>,
+                dim3((unsigned)nwg), dim3(64 * nw), 0, s, A, with_z ? 1 : 0, G, ngroups);
+  } else {
+    // columns whose loads a wavefront issues together, and batches of them per
+    // wavefront.  8^4, 130 FP32 columns: 21.3 us with the reduction for two
+    // columns by four batches, 22.5 for four by one, 26.4 for one by one (and
+    // four by four as two by four); 8^4 x 6 slots, 130 FP64 columns: 123.8 for
+    // two by two, 128.7 for two by four, 133.6 for one by one
+    const int C = std::min(A.tune.cpw, 2), batches = sizeof(VT) == 16 ? 2 : 4;
+    const ColGroups G = groups(4 * C * batches, ngroups);
+    const size_t nwg = tile_grid((size_t)A.nb * ngroups, w.nrt_dot);
+    SGN_REQUIRE(nwg * 256 < (size_t(1) << 32), SGN_EINVAL, "krylov: dot grid too large");
+    prof_launch(prof, K_KDOT, bytes, flops, C == 1 ? kdot_kernel<VT, 1> : kdot_kernel<VT, 2>, dim3((unsigned)nwg),
+                dim3(256), 0, s, A, with_z ? 1 : 0, G, batches, ngroups);
+  }
+  if (parts && !reduce) return;
+  // partial sums read, a, b written
+  const double np = parts ? kParts : w.nrt_dot;
+  prof_launch(prof, K_KRED, 32.0 * cols * (np + 1.0) + 32.0 * A.nb * w.nrt_dot, 4.0 * cols * np, kred_kernel,
+              dim3(std::max(1, (Jmax + 31) / 32), 1, A.nb), dim3(256), 0, s, A, parts ? 1 : 0);
 }
 
 template <typename VT>
@@ -734,12 +1257,13 @@ void krylov_update(const KrylovWork& w, const KrylovArgs& Ain, hipStream_t s, Pr
   check_args(w, A);
   SGN_REQUIRE(A.m + A.jmax() + 1 <= A.ldh, SGN_EINVAL, "krylov: H too small");
   SGN_REQUIRE(krylov_tune_valid(A.tune), SGN_EINVAL, "krylov: invalid launch shape");
-  // per slot: Hessenberg-row workgroups for rows 0..m+jmax, then the blocks
-  // of 64 R rows
-  const int nh = (A.m + A.jmax() + 1 + A.tune.uw - 1) / A.tune.uw;
-  const int rows = 64 * rows_per_lane<VT>();
+  // Hessenberg-row workgroups for rows 0..m+jmax of every slot, then the
+  // blocks of 64 R rows by row tile
+  const int Jmax = A.m + A.jmax();
+  const int nh = (Jmax + 1 + A.tune.uw - 1) / A.tune.uw;
   check_pairs<VT>(A);
-  const size_t nwg = ((size_t)((A.N + rows - 1) / rows) + nh) * A.nb;
+  const unsigned nhess = ((unsigned)nh * A.nb + kXcds - 1) / kXcds * kXcds;
+  const size_t nwg = nhess + tile_grid((size_t)A.nb * (kDRows / (64 * rows_per_lane<VT>())), w.nrt_dot);
   const int nthr = 64 * A.tune.uw;
   SGN_REQUIRE(nwg * nthr < (size_t(1) << 32), SGN_EINVAL, "krylov: update grid too large");
   const double vb = (double)sizeof(VT);
@@ -749,8 +1273,11 @@ void krylov_update(const KrylovWork& w, const KrylovArgs& Ain, hipStream_t s, Pr
   // read Q, u, z; write v_J, u' (+ its low-precision copy)
   const double vec = A.N * (16.0 + vb + vb + 16.0 + (A.ulonext ? vb : 0.0));
   const double cols = A.nb * (double)A.m + sk;  // per-slot work counts S for every slot
+  const uint32_t lds =
+      dot_form(w, A) == DotForm::Parts ? (uint32_t)(2 * sizeof(double2)) * (uint32_t)(std::min(Jmax, kCoefCap) + kCoefPad) : 0;
   prof_launch(prof, K_KUPDATE, qbytes + A.nb * vec + 32.0 * cols, 16.0 * (double)A.N * cols,
-              update_kernel_for<VT>(A.tune), dim3((unsigned)nwg), dim3(nthr), 0, s, A, nh);
+              dot_form(w, A) == DotForm::Parts ? update_kernel_for<VT, true>(A.tune) : update_kernel_for<VT, false>(A.tune),
+              dim3((unsigned)nwg), dim3(nthr), lds, s, A, nh, nhess);
 }
 
 template <typename VT>
@@ -784,8 +1311,8 @@ void krylov_patch(const KrylovWork& w, const KrylovArgs& Ain, int n, double2* ds
   SGN_HIP(hipGetLastError());
 }
 
-template void krylov_dot<double2>(const KrylovWork&, const KrylovArgs&, bool, hipStream_t, Profiler*);
-template void krylov_dot<float2>(const KrylovWork&, const KrylovArgs&, bool, hipStream_t, Profiler*);
+template void krylov_dot<double2>(const KrylovWork&, const KrylovArgs&, bool, bool, hipStream_t, Profiler*);
+template void krylov_dot<float2>(const KrylovWork&, const KrylovArgs&, bool, bool, hipStream_t, Profiler*);
 template void krylov_update<double2>(const KrylovWork&, const KrylovArgs&, hipStream_t, Profiler*);
 template void krylov_update<float2>(const KrylovWork&, const KrylovArgs&, hipStream_t, Profiler*);
 template void krylov_combine<double2>(const KrylovWork&, const KrylovArgs&, const double2*, int, double2*, size_t,

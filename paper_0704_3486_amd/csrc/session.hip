@@ -257,9 +257,9 @@ struct sgn_session {
         }
         if (k > 0) {
           if (mixed)
-            krylov_dot<float2>(kw, kc, false, s, prof);
+            krylov_dot<float2>(kw, kc, false, true, s, prof);
           else
-            krylov_dot<double2>(kw, kc, false, s, prof);
+            krylov_dot<double2>(kw, kc, false, true, s, prof);
         }
         krylov_patch(kw, kc, n, Apat, nn, k > 0, s);
         const int it = dense_sign_batched(dense, n, nb, Apat, n, nn, Fout, n, nn, s, prof);
@@ -365,11 +365,11 @@ struct sgn_session {
       if (mixed) {
         wilson_apply_slots<float2>(c->lat, c->links32, static_cast<float2*>(ulo), ldq, static_cast<float2*>(z), ldq,
                                    map, s, prof);
-        krylov_dot<float2>(kw, ka, true, s, prof);
+        krylov_dot<float2>(kw, ka, true, false, s, prof);
         krylov_update<float2>(kw, ka, s, prof);
       } else {
         wilson_apply_slots<double2>(c->lat, c->links, u, ldq, static_cast<double2*>(z), ldq, map, s, prof);
-        krylov_dot<double2>(kw, ka, true, s, prof);
+        krylov_dot<double2>(kw, ka, true, false, s, prof);
         krylov_update<double2>(kw, ka, s, prof);
       }
       std::vector<int> due;

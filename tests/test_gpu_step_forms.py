@@ -1,0 +1,64 @@
+"""The one-vector step's dot and update passes choose their form by the number
+of row tiles (512 rows) and sources: every form adds the same numbers in the
+same order, so a source alone and the same source in a large batch (the
+general form) agree bitwise."""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+M_W = -1.6
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_0704_3486_amd as sg
+
+    return sg, torch
+
+
+# row tiles: 1, 8 (the last lattice of whole columns), 9 (the first of parts),
+# 24 (three tiles a part), 64 (the last of parts), 65
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("dims,m,k,nrhs", [
+    ((2, 2, 2, 4), 0, 30, 64), ((4, 4, 4, 5), 6, 70, 12), ((2, 2, 2, 43), 0, 45, 16), ((4, 4, 8, 8), 5, 40, 6),
+    ((2, 5, 13, 21), 3, 20, 3), ((2, 8, 9, 19), 0, 20, 2)])
+def test_forms_bitwise_equal(env, dims, m, k, nrhs, prec):
+    sg, torch = env
+    print("forms", dims, m, k, nrhs, prec, flush=True)
+    ctx = sg.sgn_create(synth.random_links(dims, 7), dims, 0.3, M_W)
+    try:
+        if prec == "mixed":
+            sg.sgn_set_precision(ctx, sg.SGN_PREC_MIXED)
+        if m:
+            sg.sgn_deflate(ctx, m)
+        X = torch.from_numpy(np.stack([synth.gaussian_source(dims, 90 + r) for r in range(nrhs)])).cuda()
+        Y, y = torch.empty_like(X), torch.empty_like(X[0])
+        sg.sgn_apply_batched_fixed(ctx, X, Y, k)
+        for r in {0, nrhs - 1}:
+            sg.sgn_apply_fixed(ctx, X[r], y, k)
+            assert torch.equal(y, Y[r]), r
+    finally:
+        sg.sgn_destroy(ctx)
+
+
+def test_long_basis_spans(env):
+    # more columns than the update pass by parts keeps coefficients of at once
+    sg, torch = env
+    print("long basis", flush=True)
+    dims, k, nrhs = (2, 2, 2, 43), 1045, 15
+    ctx = sg.sgn_create(synth.random_links(dims, 8), dims, 0.3, M_W)
+    try:
+        X = torch.from_numpy(np.stack([synth.gaussian_source(dims, 30 + r) for r in range(nrhs)])).cuda()
+        Y, y = torch.empty_like(X), torch.empty_like(X[0])
+        sg.sgn_apply_batched_fixed(ctx, X, Y, k)
+        sg.sgn_apply_fixed(ctx, X[0], y, k)
+        assert torch.equal(y, Y[0])
+    finally:
+        sg.sgn_destroy(ctx)
