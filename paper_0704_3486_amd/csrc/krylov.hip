@@ -148,13 +148,21 @@ __device__ inline int step_of(const KrylovArgs& A, int z) { return A.jdev ? *A.j
 // into an XCD's 4 MB of L2 are still there for the update pass, and the other
 // way round, as far as they fit (the L2 keeps its contents from one kernel to
 // the next: 32 MB read twice by the same XCDs take no longer than an empty
-// kernel, read by other XCDs 5.8 us).  i -> (tile t, index in [0, per)):
-// false for the padding.
+// kernel, read by other XCDs 5.8 us).  A launch of few tiles would leave some
+// XCDs with a tile more than others (ten tiles: twice as much), so launch
+// position z counts its tiles on from z ntiles.
+// i -> (tile t, index in [0, per) with position z = in mod nb): false for the
+// padding.
 constexpr int kXcds = 8;
-__device__ inline bool tile_of(unsigned i, unsigned per, int ntiles, int& t, unsigned& in) {
-  const unsigned l = i / kXcds, q = l / per;
-  in = l - q * per;
-  t = (int)(q * kXcds + i % kXcds);
+constexpr int kEvenTiles = 128;  // tiles from which their shares are even enough
+__device__ inline int rotate_tile(int t, int z, int ntiles) {
+  return ntiles < kEvenTiles ? (t & ~(kXcds - 1)) | ((t - z * ntiles) & (kXcds - 1)) : t;
+}
+__device__ inline bool tile_of(unsigned i, unsigned per, unsigned nb, int ntiles, int& t, int& z, int& in) {
+  const unsigned l = i / kXcds, q = l / per, k = l - q * per;
+  in = (int)(k / nb);
+  z = (int)(k - (unsigned)in * nb);
+  t = rotate_tile((int)(q * kXcds + i % kXcds), z, ntiles);
   return t < ntiles;
 }
 inline size_t tile_grid(size_t per, int ntiles) { return (size_t)kXcds * per * ((ntiles + kXcds - 1) / kXcds); }
@@ -307,10 +315,8 @@ struct ColGroups {
 template <typename VT, int C>
 __global__ void __launch_bounds__(256) kdot_kernel(KrylovArgs A, int with_z, ColGroups G, int ng, int ngroups) {
   constexpr int R = rows_per_lane<VT>();
-  int rt;
-  unsigned in;
-  if (!tile_of(blockIdx.x, A.nb * ngroups, A.nrt_dot, rt, in)) return;
-  const int cg = (int)(in / A.nb), zb = (int)(in - (unsigned)cg * A.nb);
+  int rt, zb, cg;
+  if (!tile_of(blockIdx.x, A.nb * ngroups, A.nb, A.nrt_dot, rt, zb, cg)) return;
   const int r = slot_of(A, zb);
   const int lane = threadIdx.x & 63, wave = wave_id();
   const int N = A.N, kcols = step_of(A, zb), J = A.m + kcols;
@@ -360,9 +366,10 @@ template <typename VT, int C>
 __global__ void __launch_bounds__(64 * kPartTiles / kParts) kdot_parts_kernel(KrylovArgs A, int with_z, ColGroups G,
                                                                       int ngroups) {
   constexpr int R = rows_per_lane<VT>();
-  const int part = blockIdx.x % kParts;  // tiles of one part: one XCD
+  static_assert(kParts == kXcds, "the tiles of a part run on one XCD");
   const unsigned l = blockIdx.x / kParts;
   const int cg = (int)(l / A.nb), zb = (int)(l - (unsigned)cg * A.nb);
+  const int part = rotate_tile(blockIdx.x % kParts, zb, A.nrt_dot);
   const int r = slot_of(A, zb);
   const int lane = threadIdx.x & 63, wave = wave_id();
   const int kcols = step_of(A, zb);
@@ -873,11 +880,8 @@ __global__ void __launch_bounds__(64 * NW, 4) kupdate_kernel(KrylovArgs A, int n
     zb = blockIdx.x - bb * A.nb;
     if (bb >= nh) return;
   } else {
-    int rt;
-    unsigned in;
-    if (!tile_of(blockIdx.x - nhess, A.nb * kSub, A.nrt_dot, rt, in)) return;
-    const int sub = (int)(in / A.nb);
-    zb = (int)(in - (unsigned)sub * A.nb);
+    int rt, sub;
+    if (!tile_of(blockIdx.x - nhess, A.nb * kSub, A.nb, A.nrt_dot, rt, zb, sub)) return;
     bb = rt * kSub + sub;
     if (bb * 64 * R >= A.N) return;
   }
@@ -1168,11 +1172,18 @@ constexpr size_t kDotWaves = 2048;
 // Tiles 52.7, Parts 52.4, former 55.7; FP32: Tiles 36.7, Parts 38.2 (56.7
 // against 47.5 at 260 columns), former 36.7.  8^4 x 6 slots, 180 columns:
 // Tiles 283.5, former 301.7.
+// Every workgroup of the update adds the parts for itself, J times 256 bytes:
+// with several slots of few tiles that costs more than the reduction saves.
+// 256 sites x 16 slots, 50 / 150 / 260 columns: Parts 22.4 / 49.7 / 84.1, Tiles
+// 21.9 / 47.2 / 72.3; 600 sites x 8, 260 columns: 91.7 and 84.7; 400 sites x 5:
+// 47.4 and 44.3; 900 sites x 4: Parts 65.4, former 69.5; 1296 sites x 4: 92.4
+// and 94.0.
+constexpr int kPartSlots = 4;
 enum class DotForm { Whole, Parts, Tiles };
 static DotForm dot_form(const KrylovWork& w, const KrylovArgs& A) {
   const long long work = (long long)w.nrt_dot * A.nb;
   if (w.nrt_dot <= kParts && work <= kPartTiles) return DotForm::Whole;
-  if (w.nrt_dot <= kPartTiles && work <= 2 * kPartTiles) return DotForm::Parts;
+  if (w.nrt_dot <= kPartTiles && A.nb <= kPartSlots && work <= 2 * kPartTiles) return DotForm::Parts;
   return DotForm::Tiles;
 }
 
