@@ -63,17 +63,28 @@ __device__ inline double2 gload(gptr p) {
 
 // k-steps whose loads a lane issues together in the block products
 constexpr int kUnroll = 8;
-// fewest rows per wavefront of the dot pass, and its tiles of 16 columns
-// per wavefront (sharing the block-vector loads)
-constexpr int kMinRowsPerWave = 128;
+// tiles of 16 columns per wavefront of the packed dot pass (sharing the
+// block-vector loads)
 constexpr int kDotTiles = 2;
 // tiles per wavefront of the three-multiplication dot pass in a launch of
 // kWideFrom or more slots (the block-vector loads shared by four tiles);
-// launches of fewer slots keep two, for twice the workgroups
+// launches of fewer slots take two, or one where two would leave CUs idle
 constexpr int kDot3Tiles = 4;
-constexpr int kDot3TilesSingle = 2;
-// slots from which a launch takes the wide tiles (dot) and row blocks (update)
+// workgroups that fill the chip
+constexpr int kFullChip = 512;
+// slots from which a launch takes the wide tiles
 constexpr int kWideFrom = 4;
+// rows below which the dot pass takes shorter row chunks
+constexpr int kSmallRows = 12288;
+// blocks of 16 rows per wavefront of the three-multiplication update pass, and
+// the basis (entries over all slots) from which its wavefronts take whole
+// rows: past the 256 MB of the Infinity Cache, where reading 2048 adjacent
+// bytes of a column per workgroup instead of 256 counts.  us by events, split
+// / whole: 6^4 x 8 slots, 116 columns, 14.5 M entries 50 / 55, 196 columns,
+// 24.5 M 91 / 86, 340 columns 152 / 139; x 4, 340 columns, 21.2 M 73 / 71; x 3,
+// 15.9 M 48 / 55
+constexpr int kRowBlocks = 2;
+constexpr double kWholeEntries = 20e6;
 
 // the composite basis of one launch: column c < m is S[c], column c >= m of
 // slot r is V_r[c - m] (V_r = V + r vstride), all with leading dimension ldq
@@ -88,15 +99,24 @@ struct BlockGeo {
 };
 
 // Workgroup i runs on XCD i % 8 (round-robin dispatch).  Map i to (tile b,
-// index z within the tile, z < per) so that the workgroups of one tile run on
-// one XCD, whose L2 then serves what they share (the rows of the Schur
-// columns for every slot, the slot's block vectors for every column group):
-// i = 8 (z + per q) + x -> b = 8 q + x.  A grid of 8 per ceil(ntiles / 8)
-// workgroups covers every (b, z) once; false for the padding (b >= ntiles).
-__device__ inline bool xcd_tile(int i, int per, int ntiles, int& b, int& z) {
-  const int x = i & 7, l = i >> 3;
-  z = l % per;
-  b = (l / per) * 8 + x;
+// launch position z, index k) so that the workgroups of one tile and position
+// run on one XCD, whose L2 then serves what they share (the slot's block
+// vectors for every column group, and the rows of the Schur columns for every
+// slot where all positions have the same tile there): with j = z + nb k,
+// i = 8 (j + nb nk q) + x -> b = 8 q + x.  With few tiles some XCDs would have
+// one more than others, so position z counts its tiles on from z ntiles.  The
+// update passes take the tiles downwards, so that what the dot pass read last
+// is still in the caches (and what they read last, for the next dot pass).  A
+// grid of 8 nb nk ceil(ntiles / 8) workgroups covers every (b, z, k) once;
+// false for the padding (b >= ntiles).
+constexpr int kEvenTiles = 128;
+template <bool DOWN>
+__device__ inline bool xcd_tile(int i, int nb, int nk, int ntiles, int& b, int& z, int& k) {
+  const int x = i & 7, l = i >> 3, up = l / (nb * nk), j = l - up * nb * nk;
+  const int q = DOWN ? ((ntiles - 1) >> 3) - up : up;
+  k = j / nb;
+  z = j - k * nb;
+  b = 8 * q + (ntiles < kEvenTiles ? (x - z * ntiles) & 7 : x);
   return b < ntiles;
 }
 inline unsigned xcd_grid(int per, int ntiles) { return 8u * (unsigned)per * (unsigned)((ntiles + 7) / 8); }
@@ -153,9 +173,8 @@ struct BDot {
 
 __global__ void __launch_bounds__(256) bdot_kernel(BlockGeo g, BDot a) {
   // tile = row chunk: all slots and column groups of a chunk on one XCD
-  int chunk, inner;
-  if (!xcd_tile(blockIdx.x, g.nb * a.ncg, a.nch, chunk, inner)) return;
-  const int z = inner % g.nb, cg = inner / g.nb;
+  int chunk, z, cg;
+  if (!xcd_tile<false>(blockIdx.x, g.nb, a.ncg, a.nch, chunk, z, cg)) return;
   const int r = g.act[z];
   const double2* Vr = g.V + (size_t)r * g.vstride;
   const double2* Wr = a.W + (size_t)r * a.wstride;
@@ -282,9 +301,8 @@ __global__ void __launch_bounds__(256) bdot_kernel(BlockGeo g, BDot a) {
 // a quarter fewer matrix-core instructions than two halves of 8.
 template <int T>
 __global__ void __launch_bounds__(256) bdot3_kernel(BlockGeo g, BDot a) {
-  int chunk, inner;
-  if (!xcd_tile(blockIdx.x, g.nb * a.ncg, a.nch, chunk, inner)) return;
-  const int z = inner % g.nb, cg = inner / g.nb;
+  int chunk, z, cg;
+  if (!xcd_tile<false>(blockIdx.x, g.nb, a.ncg, a.nch, chunk, z, cg)) return;
   const int r = g.act[z];
   const double2* Vr = g.V + (size_t)r * g.vstride;
   const double2* Wr = a.W + (size_t)r * a.wstride;
@@ -312,7 +330,7 @@ __global__ void __launch_bounds__(256) bdot3_kernel(BlockGeo g, BDot a) {
   }
   // groups of U k-steps, the loads of the next group issued before the
   // products of the current one (two register sets)
-  constexpr int U = kUnroll / 4;
+  constexpr int U = T == 1 ? kUnroll / 2 : kUnroll / 4;
   auto load = [&](double2 (&qv)[U][T], double2 (&wv)[U]) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -510,15 +528,13 @@ __device__ inline void qc_steps(const double2* __restrict__ S, const double2* __
 //   Re(Q C) = T1 - T2,  Im(Q C) = T3 - T1 - T2
 // for the 16 rows (rows lk + 4 t in item t) and vector li.  RB blocks of 16
 // rows (rows[b]: this lane's row of block b) share each coefficient load.
-template <int RB>
+template <int RB, int U>
 __device__ inline void qc_steps3(const double2* __restrict__ S, const double2* __restrict__ Vr, int m, size_t ldq,
                                  const int (&rows)[RB], int ncol, const double2* __restrict__ C, int s, int li,
-                                 int lk, int k0, int dk, v4d (&t1)[RB], v4d (&t2)[RB], v4d (&t3)[RB]) {
+                                 int lk, int k0, int dk, int nk, v4d (&t1)[RB], v4d (&t2)[RB], v4d (&t3)[RB]) {
   const gptr zero = to_global(&sgn_block_zero_entry);
-  const int nk = (ncol + 3) >> 2;
   const bool vok = li < s;
   int ks = k0;
-  constexpr int U = kUnroll / (2 * RB);
   for (; ks + (U - 1) * dk < nk; ks += U * dk) {
     double2 qv[U][RB], cv[U];
 #pragma unroll
@@ -612,10 +628,11 @@ __device__ void hess_entry(const BlockGeo& g, const BHess& h, int r_slot, int id
 }
 
 // ---------------------------------------------------------------------------
-// update pass: Wout = (Win - Q C) [Rinv].  Wavefront: 16 rows x all p
-// columns.  With Rinv (the second pass) the workgroups past the rows also
-// write the block's Hessenberg columns (hess).  Tile = row block; the slots
-// of a row block run on one XCD.
+// update pass: Wout = (Win - Q C) [Rinv].  With Rinv (the second pass) the
+// first workgroups (padded to whole rounds of the XCDs) write the block's
+// Hessenberg columns (hess).  The others take the rows by the dot pass's row
+// chunks, a chunk on the XCD that read it there: on small lattices the columns
+// are then still in that XCD's L2.
 struct BUpd {
   const double2* C;
   size_t cstride;
@@ -625,23 +642,32 @@ struct BUpd {
   size_t woutstride;
   const double2* Rinv;  // per slot [kBlockMax][kBlockMax] upper triangular at rstride, or null
   size_t rstride;
-  int nrowblk;  // workgroups on rows
-  int nhess;    // workgroups on the Hessenberg columns (with Rinv)
+  int nch, crows;  // row chunks and rows of one (a multiple of 64)
+  int nhess;       // workgroups on the Hessenberg columns (with Rinv), a multiple of 8
   BHess hess;
 };
 
-template <bool G, int RB>
-__global__ void __launch_bounds__(256) bupdate_kernel(BlockGeo g, BUpd a) {
-  // RB blocks of 16 rows per wavefront, sharing each coefficient load (the
-  // three-multiplication form only; the packed form takes one)
-  static_assert(G || RB == 1, "row blocks need the three-multiplication form");
-  int z, bid;
-  if (!xcd_tile(blockIdx.x, g.nb, a.nrowblk + a.nhess, bid, z)) return;
-  const int rs = g.act[z];
-  if (bid >= a.nrowblk) {
-    hess_entry(g, a.hess, rs, (bid - a.nrowblk) * 256 + threadIdx.x);
-    return;
+// workgroup -> slot position z and first row; false: no rows (padding, or a
+// Hessenberg workgroup, done here)
+__device__ inline bool upd_rows(const BlockGeo& g, const BUpd& a, int rows, int& z, int& r0) {
+  int i = blockIdx.x;
+  if (i < a.nhess) {
+    const int t = i / g.nb;
+    hess_entry(g, a.hess, g.act[i - t * g.nb], t * 256 + threadIdx.x);
+    return false;
   }
+  const int subs = a.crows / rows;
+  int chunk, sub;
+  if (!xcd_tile<true>(i - a.nhess, g.nb, subs, a.nch, chunk, z, sub)) return false;
+  r0 = chunk * a.crows + sub * rows;
+  return r0 < g.N;
+}
+
+// s <= 8, the packed form.  Wavefront: 16 rows x all p columns.
+__global__ void __launch_bounds__(256) bupdate_kernel(BlockGeo g, BUpd a) {
+  int z, wg0;
+  if (!upd_rows(g, a, 64, z, wg0)) return;
+  const int rs = g.act[z];
   const double2* Vr = g.V + (size_t)rs * g.vstride;
   const double2* Cr = a.C + (size_t)rs * a.cstride;
   const double2* Win = a.Win + (size_t)rs * a.winstride;
@@ -649,68 +675,43 @@ __global__ void __launch_bounds__(256) bupdate_kernel(BlockGeo g, BUpd a) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int li = lane & 15, lk = lane >> 4;
-  const int r0 = (bid * 4 + wave) * 16 * RB;
+  const int r0 = wg0 + wave * 16;
   const bool active = r0 < g.N;  // wavefront-uniform
   const int v = li & 7;
-  // res[b][h][t]: (Q C)[row r0 + 16 b + lk + 4 t][vector vec(h)] in the lanes
-  // that own one
-  double2 res[RB][kHalves][4];
+  const int row = min(r0 + li, g.N - 1);
+  v4d d[kHalves];
+#pragma unroll
+  for (int h = 0; h < kHalves; ++h) d[h] = v4d{0.0, 0.0, 0.0, 0.0};
+  if (active) qc_steps(g.S, Vr, g.m, g.ldq, row, g.p, Cr, v, li >= 8, g.s, lk, 0, 1, d);
+  // res[h][t]: (Q C)[row r0 + lk + 4 t][vector vec(h)] in the lanes that own one
+  double2 res[kHalves][4];
   bool own[kHalves];
   int vec[kHalves];
-  if constexpr (G) {
-    v4d t1[RB], t2[RB], t3[RB];
-    int rows[RB];
 #pragma unroll
-    for (int b = 0; b < RB; ++b) {
-      t1[b] = v4d{0.0, 0.0, 0.0, 0.0};
-      t2[b] = t1[b];
-      t3[b] = t1[b];
-      rows[b] = min(r0 + 16 * b + li, g.N - 1);
-    }
-    if (active) qc_steps3<RB>(g.S, Vr, g.m, g.ldq, rows, g.p, Cr, g.s, li, lk, 0, 1, t1, t2, t3);
-#pragma unroll
-    for (int b = 0; b < RB; ++b)
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-        res[b][0][t] = make_double2(t1[b][t] - t2[b][t], t3[b][t] - t1[b][t] - t2[b][t]);
-    own[0] = li < g.s;
-    vec[0] = li;
-#pragma unroll
-    for (int h = 1; h < kHalves; ++h) own[h] = false;
-  } else {
-    const int row = min(r0 + li, g.N - 1);
-    v4d d[kHalves];
-#pragma unroll
-    for (int h = 0; h < kHalves; ++h) d[h] = v4d{0.0, 0.0, 0.0, 0.0};
-    if (active) qc_steps(g.S, Vr, g.m, g.ldq, row, g.p, Cr, v, li >= 8, g.s, lk, 0, 1, d);
-#pragma unroll
-    for (int h = 0; h < kHalves; ++h) {
-      qc_pairs(d[h], res[0][h]);
-      vec[h] = 8 * h + v;
-      own[h] = li < 8 && vec[h] < g.s;
-    }
+  for (int h = 0; h < kHalves; ++h) {
+    qc_pairs(d[h], res[h]);
+    vec[h] = 8 * h + v;
+    own[h] = li < 8 && vec[h] < g.s;
   }
   if (!a.Rinv) {
     if (active)
 #pragma unroll
-      for (int b = 0; b < RB; ++b)
+      for (int h = 0; h < kHalves; ++h) {
+        if (!own[h]) continue;
 #pragma unroll
-        for (int h = 0; h < kHalves; ++h) {
-          if (!own[h]) continue;
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            const int rr = r0 + 16 * b + lk + 4 * t;
-            if (rr < g.N) {
-              const size_t o = (size_t)vec[h] * g.ldq + rr;
-              Wout[o] = csub(Win[o], res[b][h][t]);
-            }
+        for (int t = 0; t < 4; ++t) {
+          const int rr = r0 + lk + 4 * t;
+          if (rr < g.N) {
+            const size_t o = (size_t)vec[h] * g.ldq + rr;
+            Wout[o] = csub(Win[o], res[h][t]);
           }
         }
+      }
     return;
   }
   // second pass: W'' = Win - Q C, then W'' Rinv per row (through LDS; the
   // workgroup's slot is the same for all four wavefronts)
-  __shared__ double2 tile[4][16 * RB][kBlockMax];
+  __shared__ double2 tile[4][16][kBlockMax];
   __shared__ double2 ri[kBlockMax * kBlockMax];
   {
     const double2* Ri = a.Rinv + (size_t)rs * a.rstride;
@@ -718,23 +719,159 @@ __global__ void __launch_bounds__(256) bupdate_kernel(BlockGeo g, BUpd a) {
   }
   // every (row, vector) of the tile: vectors past s and rows past N as zero
 #pragma unroll
-  for (int b = 0; b < RB; ++b)
+  for (int h = 0; h < kHalves; ++h) {
+    if (li >= 8) continue;
+    const int vv = 8 * h + v;
 #pragma unroll
-    for (int h = 0; h < kHalves; ++h) {
-      const bool writer = G ? h == 0 : li < 8;
-      if (!writer) continue;
-      const int vv = G ? li : 8 * h + v;
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int rl = 16 * b + lk + 4 * t, rr = r0 + rl;
-        double2 val = make_double2(0.0, 0.0);
-        if (active && own[h] && rr < g.N) val = csub(Win[(size_t)vv * g.ldq + rr], res[b][h][t]);
-        tile[wave][rl][vv] = val;
-      }
+    for (int t = 0; t < 4; ++t) {
+      const int rl = lk + 4 * t, rr = r0 + rl;
+      double2 val = make_double2(0.0, 0.0);
+      if (active && own[h] && rr < g.N) val = csub(Win[(size_t)vv * g.ldq + rr], res[h][t]);
+      tile[wave][rl][vv] = val;
     }
+  }
   __syncthreads();
   if (!active) return;
-  constexpr int kOut = 16 * RB * kBlockMax / 64;  // outputs per lane
+  constexpr int kOut = 16 * kBlockMax / 64;  // outputs per lane
+  // (not unrolled: this epilogue would otherwise set the kernel's register
+  // count, and with it the occupancy of the sweep above)
+#pragma unroll 1
+  for (int q = 0; q < kOut; ++q) {
+    const int idx = lane + 64 * q;
+    const int rl = idx / kBlockMax, vv = idx % kBlockMax;
+    double2 acc = make_double2(0.0, 0.0);
+#pragma unroll 4
+    for (int u = 0; u < kBlockMax; ++u) acc = cfma(tile[wave][rl][u], ri[u * kBlockMax + vv], acc);
+    const int rr = r0 + rl;
+    if (vv < g.s && rr < g.N) Wout[(size_t)vv * g.ldq + rr] = acc;
+  }
+}
+
+// s > 8, the three-multiplication form.  A row's sums run over the k-steps of
+// four quarters of the columns, one chain of products each, which are then
+// added in order; the two kernels below differ in who runs the chains.
+__device__ inline int quarter(int p) { return (((p + 3) >> 2) + 3) >> 2; }  // k-steps of a quarter
+
+// Small launches: a workgroup takes 16 rows and each of its wavefronts a
+// quarter, whose sums meet in LDS.  The chain of waits is a quarter of the
+// other form's and the launch has four times the wavefronts: 4x4x4x6, 268
+// columns, 1 slot: 13 us (events), 28 us with whole rows per wavefront; 6^4,
+// 176 columns: 16 against 24 us.
+__global__ void __launch_bounds__(256) bupdate3_split_kernel(BlockGeo g, BUpd a) {
+  int z, r0;
+  if (!upd_rows(g, a, 16, z, r0)) return;
+  const int rs = g.act[z];
+  const double2* Vr = g.V + (size_t)rs * g.vstride;
+  const double2* Cr = a.C + (size_t)rs * a.cstride;
+  const double2* Win = a.Win + (size_t)rs * a.winstride;
+  double2* Wout = a.Wout + (size_t)rs * a.woutstride;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int li = lane & 15, lk = lane >> 4;
+  // this thread's output: row r0 + rl of vector v
+  const int rl = threadIdx.x & 15, v = threadIdx.x >> 4;
+  const bool own = v < g.s && r0 + rl < g.N;
+  const size_t o = (size_t)min(v, g.s - 1) * g.ldq + min(r0 + rl, g.N - 1);
+  double2 w = Win[o];
+  v4d t1[1] = {v4d{0.0, 0.0, 0.0, 0.0}}, t2[1] = {t1[0]}, t3[1] = {t1[0]};
+  const int rows[1] = {min(r0 + li, g.N - 1)};
+  const int qk = quarter(g.p), nk = (g.p + 3) >> 2;
+  qc_steps3<1, 4>(g.S, Vr, g.m, g.ldq, rows, g.p, Cr, g.s, li, lk, wave * qk, 1, min((wave + 1) * qk, nk), t1, t2,
+                  t3);
+  // rows padded to 17 entries, so that a column of them spreads over the banks
+  __shared__ double2 part[4][16][kBlockMax + 1];
+  __shared__ double2 ri[kBlockMax * kBlockMax];
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+    part[wave][lk + 4 * t][li] = make_double2(t1[0][t] - t2[0][t], t3[0][t] - t1[0][t] - t2[0][t]);
+  if (a.Rinv) ri[threadIdx.x] = a.Rinv[(size_t)rs * a.rstride + threadIdx.x];
+  static_assert(kBlockMax * kBlockMax == 256, "one output and one entry of Rinv per thread");
+  __syncthreads();
+  double2 sum = part[0][rl][v];
+#pragma unroll
+  for (int q = 1; q < 4; ++q) sum = cadd(sum, part[q][rl][v]);
+  w = csub(w, sum);
+  if (!a.Rinv) {
+    if (own) Wout[o] = w;
+    return;
+  }
+  // second pass: W'' Rinv per row, W'' in place of the first quarter's sums
+  // (each thread replaces the entry that it alone has read)
+  part[0][rl][v] = w;
+  __syncthreads();
+  if (!own) return;
+  double2 acc = make_double2(0.0, 0.0);
+  for (int u = 0; u <= v; ++u) acc = cfma(part[0][rl][u], ri[u * kBlockMax + v], acc);
+  Wout[o] = acc;
+}
+
+// Large launches: a wavefront owns RB blocks of 16 rows and runs the four
+// chains itself, RB blocks sharing each coefficient load, and keeps the sum of
+// the finished quarters in LDS.  Bound by memory: 6^4 x 8 slots, 340 columns,
+// 650 MB: 139 us (events), 4.7 TB/s.
+template <int RB>
+__global__ void __launch_bounds__(256) bupdate3_kernel(BlockGeo g, BUpd a) {
+  constexpr int kRows = 16 * RB;
+  int z, wg0;
+  if (!upd_rows(g, a, 4 * kRows, z, wg0)) return;
+  const int rs = g.act[z];
+  const double2* Vr = g.V + (size_t)rs * g.vstride;
+  const double2* Cr = a.C + (size_t)rs * a.cstride;
+  const double2* Win = a.Win + (size_t)rs * a.winstride;
+  double2* Wout = a.Wout + (size_t)rs * a.woutstride;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int li = lane & 15, lk = lane >> 4;
+  const int r0 = wg0 + wave * kRows;
+  const bool active = r0 < g.N;  // wavefront-uniform
+  __shared__ double2 tile[4][kRows][kBlockMax];
+  __shared__ double2 ri[kBlockMax * kBlockMax];
+  if (a.Rinv) ri[threadIdx.x] = a.Rinv[(size_t)rs * a.rstride + threadIdx.x];
+  static_assert(kBlockMax * kBlockMax == 256, "one entry of Rinv per thread");
+  int rows[RB];
+#pragma unroll
+  for (int b = 0; b < RB; ++b) rows[b] = min(r0 + 16 * b + li, g.N - 1);
+  const int qk = quarter(g.p), nk = (g.p + 3) >> 2;
+  if (active)
+    for (int q = 0; q < 4; ++q) {
+      v4d t1[RB], t2[RB], t3[RB];
+#pragma unroll
+      for (int b = 0; b < RB; ++b) {
+        t1[b] = v4d{0.0, 0.0, 0.0, 0.0};
+        t2[b] = t1[b];
+        t3[b] = t1[b];
+      }
+      qc_steps3<RB, kUnroll / (2 * RB)>(g.S, Vr, g.m, g.ldq, rows, g.p, Cr, g.s, li, lk, q * qk, 1,
+                                        min((q + 1) * qk, nk), t1, t2, t3);
+      // each lane owns its entries of the tile
+#pragma unroll
+      for (int b = 0; b < RB; ++b)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const double2 x = make_double2(t1[b][t] - t2[b][t], t3[b][t] - t1[b][t] - t2[b][t]);
+          double2& e = tile[wave][16 * b + lk + 4 * t][li];
+          e = q ? cadd(e, x) : x;
+        }
+    }
+  const bool own = li < g.s;
+#pragma unroll
+  for (int b = 0; b < RB; ++b)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int rl = 16 * b + lk + 4 * t, rr = r0 + rl;
+      const size_t o = (size_t)li * g.ldq + rr;
+      double2 val = make_double2(0.0, 0.0);
+      if (active && own && rr < g.N) {
+        val = csub(Win[o], tile[wave][rl][li]);
+        if (!a.Rinv) Wout[o] = val;
+      }
+      if (a.Rinv) tile[wave][rl][li] = val;  // every entry: vectors past s and rows past N as zero
+    }
+  if (!a.Rinv) return;
+  // second pass: W'' Rinv per row
+  __syncthreads();
+  if (!active) return;
+  constexpr int kOut = kRows * kBlockMax / 64;  // outputs per lane
   // (not unrolled: this epilogue would otherwise set the kernel's register
   // count, and with it the occupancy of the sweep above)
 #pragma unroll 1
@@ -788,11 +925,11 @@ __device__ void block_factor(const BlockGeo& gg, const BSmall& a, int rs) {
   const double2* Ct = a.Ct + (size_t)rs * a.cstride;
   const double2* G = a.G + (size_t)rs * a.gstride;
   double2* Rout = a.R + (size_t)rs * a.rstride;
-  __shared__ v4d red[4][4][64];
+  __shared__ v4d red[4][2][64];
   __shared__ double redn[4][64];
-  __shared__ double2 g[B][B], R[B][B], Ri[B][B], Rb[B][B], Rbi[B][B];
-  __shared__ double piv[B], ref_s;
-  __shared__ int bad;
+  static_assert(B * B == 256, "one entry per thread");
+  __shared__ double2 g[B][B], Ri[B][B], X[B][B], cl[B];
+  __shared__ double ref_s;
   // C2^dag C2 (16 x 16 complex) on the matrix cores: A = C2^dag (row u, k = c),
   // B = C2 (k = c, column v); lane (li, lk) loads C2[c][li] for c = 4 ks + lk.
   // Re += Re A Re B + Im A Im B... with A = conj(C2)^T:
@@ -838,100 +975,92 @@ __device__ void block_factor(const BlockGeo& gg, const BSmall& a, int rs) {
     red[wave][1][lane] = dim;
     redn[wave][lane] = nn;
   }
-  if (tid < B * B) {
-    const int u = tid / B, v = tid % B;
-    R[u][v] = make_double2(0.0, 0.0);
-    Ri[u][v] = make_double2(0.0, 0.0);
-    Rb[u][v] = make_double2(0.0, 0.0);
-    Rbi[u][v] = make_double2(0.0, 0.0);
-  }
+  const int u0 = tid / B, v0 = tid % B;  // this thread's entry of the 16 x 16 matrices
   __syncthreads();
-  if (tid < 64) {
+  double2 gv = make_double2(0.0, 0.0);  // G - C2^dag C2, then the trailing block
+  if (u0 < s && v0 < s) {
     // D[u][v] sits in lane v + 16 (u % 4), item u / 4
-    const int v = tid & 15, u0 = tid >> 4;
-    v4d sre = red[0][0][tid], sim = red[0][1][tid];
+    const int l = v0 + 16 * (u0 & 3), it = u0 >> 2;
+    double sre = red[0][0][l][it], sim = red[0][1][l][it];
 #pragma unroll
     for (int w = 1; w < 4; ++w) {
-      sre += red[w][0][tid];
-      sim += red[w][1][tid];
+      sre += red[w][0][l][it];
+      sim += red[w][1][l][it];
+    }
+    gv = csub(G[tid], make_double2(sre, sim));
+  }
+  if (tid < 64) {
+    // the block vectors' size before projection, G[v][v] + |Ct[:, v]|^2
+    // (redn: over the lanes holding v, li = v, and the wavefronts), its largest
+    double rf = 0.0;
+    if (tid < s) {
+      rf = 0.0;
+      for (int w = 0; w < 4; ++w)
+        for (int q = 0; q < 4; ++q) rf += redn[w][tid + 16 * q];
+      rf += G[tid * B + tid].x;
     }
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int u = u0 + 4 * t;
-      g[u][v] = (u < s && v < s) ? csub(G[u * B + v], make_double2(sre[t], sim[t])) : make_double2(0.0, 0.0);
+    for (int off = 8; off > 0; off >>= 1) {
+      const double o = __shfl_xor(rf, off, 64);
+      rf = (o > rf || !(o == o)) ? o : rf;  // a NaN stays
     }
+    if (tid == 0) ref_s = rf;
   }
-  if (tid == 0) {
-    bad = 0;
-    // |Ct[:, v]|^2 summed over the lanes holding v (li = v) and the wavefronts
-    double rf = 0.0;
-    for (int v = 0; v < s; ++v) {
-      double t = 0.0;
-      for (int w = 0; w < 4; ++w)
-        for (int q = 0; q < 4; ++q) t += redn[w][v + 16 * q];
-      rf = fmax(rf, G[v * B + v].x + t);
-    }
-    ref_s = rf;
-  }
+  // Right-looking Cholesky of G = R^dag R with the identity beside it: step j
+  // forms row j of R and of E = R^-dag and updates the rows below, each thread
+  // its entry of both (one barrier per step: row j of both goes through LDS
+  // and step j leaves it alone).
+  double2 ev = make_double2(u0 == v0 ? 1.0 : 0.0, 0.0), rv = make_double2(0.0, 0.0);
+  double dmin = HUGE_VAL, dmax = 0.0;
+  bool bad = false;
+  g[u0][v0] = gv;
+  Ri[u0][v0] = ev;  // E while it forms
   __syncthreads();
-  // right-looking Cholesky: step j forms row j of R and updates the trailing
-  // block.  Every thread takes the pivot from g[j][j] itself and row j of R
-  // from row j of g (which step j leaves alone), so a step needs one barrier.
   for (int j = 0; j < s; ++j) {
     double dj = g[j][j].x;
     const bool okp = dj > 0.0 && isfinite(dj);
     if (!okp) dj = 1.0;
-    const double pj = sqrt(dj), ip = 1.0 / pj;
-    if (tid == 0) {
-      piv[j] = pj;
-      if (!okp) bad = 1;
-    }
-    if (tid < B && tid >= j && tid < s) R[j][tid] = tid == j ? make_double2(pj, 0.0) : cscale(g[j][tid], ip);
-    if (tid < B * B) {
-      const int u = tid / B, v = tid % B;
-      if (u > j && v > j && u < s && v < s) g[u][v] = csub(g[u][v], cmulc(cscale(g[j][u], ip), cscale(g[j][v], ip)));
+    const double ip = rsqrt(dj), pj = dj * ip;
+    bad = bad || !okp;
+    dmin = fmin(dmin, pj);
+    dmax = fmax(dmax, pj);
+    if (u0 == j) {
+      // row j of R and of E, each thread its entry
+      if (v0 >= j && v0 < s) rv = v0 == j ? make_double2(pj, 0.0) : cscale(g[j][v0], ip);
+      ev = cscale(Ri[j][v0], ip);
+    } else if (u0 > j && u0 < s) {
+      const double2 f = cscale(g[j][u0], ip);  // R[j][u0]
+      if (v0 > j && v0 < s) {
+        gv = csub(gv, cmulc(f, cscale(g[j][v0], ip)));
+        g[u0][v0] = gv;
+      }
+      if (v0 <= j) {
+        ev = csub(ev, cmulc(f, cscale(Ri[j][v0], ip)));
+        Ri[u0][v0] = ev;
+      }
     }
     __syncthreads();
   }
-  // Rb from R and the last basis column's coefficients
-  if (tid < B * B) {
-    const int u = tid / B, v = tid % B;
-    if (u < s && v < s) {
-      if (u == 0)
-        Rb[0][v] = v == 0 ? make_double2(1.0, 0.0) : Ct[(size_t)(p - 1) * B + v - 1];
-      else if (v >= u)
-        Rb[u][v] = R[u - 1][v - 1];
+  // R^-1 = E^dag (upper); Rb^-1 = [1, -c R'^-1; 0, R'^-1] with R' the leading
+  // (s - 1) x (s - 1) block of R and c the last basis column's coefficients
+  const bool in = u0 < s && v0 < s;
+  X[v0][u0] = (in && v0 <= u0) ? make_double2(ev.x, -ev.y) : make_double2(0.0, 0.0);
+  if (tid < B) cl[tid] = tid + 1 < s ? Ct[(size_t)(p - 1) * B + tid] : make_double2(0.0, 0.0);
+  __syncthreads();
+  double2 rb = make_double2(0.0, 0.0);
+  if (in) {
+    if (u0 > 0) {
+      if (v0 >= u0) rb = X[u0 - 1][v0 - 1];
+    } else if (v0 == 0) {
+      rb = make_double2(1.0, 0.0);
+    } else {
+      for (int l = 0; l < v0; ++l) rb = csub(rb, cmul(cl[l], X[l][v0 - 1]));
     }
   }
-  __syncthreads();
-  // inverses of the two upper triangular factors, one column per thread
-  if (tid < 2 * B) {
-    const int col = tid % B;
-    const bool second = tid >= B;
-    auto& M = second ? Rb : R;
-    auto& X = second ? Rbi : Ri;
-    if (col < s) {
-      X[col][col] = make_double2(1.0 / M[col][col].x, 0.0);
-      for (int i = col - 1; i >= 0; --i) {
-        double2 t = make_double2(0.0, 0.0);
-        for (int l = i + 1; l <= col; ++l) t = cfma(M[i][l], X[l][col], t);
-        X[i][col] = cscale(cneg(t), 1.0 / M[i][i].x);
-      }
-    }
-  }
-  __syncthreads();
-  if (tid < B * B) {
-    const int u = tid / B, v = tid % B;
-    Rout[tid] = R[u][v];
-    Rout[B * B + tid] = Ri[u][v];
-    Rout[2 * B * B + tid] = Rbi[u][v];
-  }
+  Rout[tid] = in ? rv : make_double2(0.0, 0.0);
+  Rout[B * B + tid] = X[u0][v0];
+  Rout[2 * B * B + tid] = rb;
   if (tid == 0) {
-    double dmin = HUGE_VAL, dmax = 0.0;
-    for (int j = 0; j < s; ++j) {
-      dmin = fmin(dmin, piv[j]);
-      dmax = fmax(dmax, piv[j]);
-    }
     const double rf = ref_s;
     if (bad || !(rf > 0.0) || !isfinite(rf) || dmin * dmin < 1e-24 * rf || dmin < 1e-7 * dmax) a.flag[rs] = 1;
   }
@@ -960,7 +1089,7 @@ __global__ void __launch_bounds__(256) bsmall_kernel(BlockGeo g, BSmall a) {
   if constexpr (G) {
     v4d t1[1] = {v4d{0.0, 0.0, 0.0, 0.0}}, t2[1] = {t1[0]}, t3[1] = {t1[0]};
     const int rows[1] = {row};
-    qc_steps3<1>(H, H, 0, (size_t)a.ldh, rows, p - 1, Ct, g.s - 1, li, lk, (c0 >> 2) + wave, 4, t1, t2, t3);
+    qc_steps3<1, kUnroll / 2>(H, H, 0, (size_t)a.ldh, rows, p - 1, Ct, g.s - 1, li, lk, (c0 >> 2) + wave, 4, (p + 2) >> 2, t1, t2, t3);
     __shared__ v4d red3[4][3][64];
     red3[wave][0][lane] = t1[0];
     red3[wave][1][lane] = t2[0];
@@ -1007,11 +1136,14 @@ __global__ void __launch_bounds__(256) bsmall_kernel(BlockGeo g, BSmall a) {
   }
 }
 
+// Rows per wavefront of the dot pass, a multiple of 16, and its row chunks of
+// four wavefronts.  By N alone (never by the slots, so that a source's sums are
+// the same alone and in a batch): 128 rows, so that the partial sums stay at 3
+// per cent of the basis, and 64 on lattices whose chunks of 512 rows are too
+// few to fill the chip; at most 128 chunks.
 int nchunks_for(int N, int& rpw) {
-  // rows per wavefront: kMinRowsPerWave or more, so that at most 128 chunks
-  // of four wavefronts cover N
   const int want = (N + 4 * 128 - 1) / (4 * 128);
-  rpw = std::max(kMinRowsPerWave, (want + 3) & ~3);
+  rpw = std::max(N < kSmallRows ? 64 : 128, (want + 15) & ~15);
   return (N + 4 * rpw - 1) / (4 * rpw);
 }
 
@@ -1103,13 +1235,24 @@ void block_step(const BlockSpan& sp, BlockWork& b, const Lattice& lat, const dou
   // blocks of 16 rows per update wavefront (three-multiplication form); the
   // arithmetic of every entry is the same either way
   const bool wide = gauss && nb >= kWideFrom;
-  const int tiles = !gauss ? kDotTiles : wide ? kDot3Tiles : kDot3TilesSingle;
-  void (*dot_kernel)(BlockGeo, BDot) =
-      !gauss ? bdot_kernel : wide ? bdot3_kernel<kDot3Tiles> : bdot3_kernel<kDot3TilesSingle>;
-  const int rb = wide ? 2 : 1;
+  auto tiles_for = [&](int ncol) {
+    if (!gauss) return kDotTiles;
+    if (wide) return kDot3Tiles;
+    return nb * nch * ((ncol + 31) / 32) >= kFullChip ? 2 : 1;
+  };
+  // rows per workgroup of the update pass: whole rows per wavefront, or in
+  // small launches the columns split over the wavefronts
+  const bool whole = !gauss || (double)N * nb * p >= kWholeEntries;
+  const int upd_rows_wg = !whole ? 16 : gauss ? 64 * kRowBlocks : 64;
   void (*upd_kernel)(BlockGeo, BUpd) =
-      !gauss ? bupdate_kernel<false, 1> : wide ? bupdate_kernel<true, 2> : bupdate_kernel<true, 1>;
+      !gauss ? bupdate_kernel : whole ? bupdate3_kernel<kRowBlocks> : bupdate3_split_kernel;
   auto dot = [&](double2* C, int ncol, const double2* C1, double2* Ct) {
+    const int tiles = tiles_for(ncol);
+    void (*dot_kernel)(BlockGeo, BDot) = !gauss       ? bdot_kernel
+                                         : tiles == 4 ? bdot3_kernel<4>
+                                         : tiles == 2 ? bdot3_kernel<2>
+                                                      : bdot3_kernel<1>;
+    static_assert(kDot3Tiles == 4, "the instances above");
     const int ncg = (ncol + 16 * tiles - 1) / (16 * tiles);
     BDot d{b.W, b.wstride, ncol, rpw, ncg, nch, b.part, b.pstride};
     // the basis read once (S once for the launch, the slots' own columns and
@@ -1123,15 +1266,15 @@ void block_step(const BlockSpan& sp, BlockWork& b, const Lattice& lat, const dou
     prof_launch(prof, K_BRED, (16.0 * (double)nch * nent + 16.0 * nent) * nb, 2.0 * nch * nent * nb, bred_kernel,
                 dim3(nblk * nb), dim3(256), 0, s, g, rd);
   };
-  const int nrowblk = (N + 64 * rb - 1) / (64 * rb);
+  const int crows = 4 * rpw;
+  const unsigned ugrid = xcd_grid(nb * (crows / upd_rows_wg), nch);
   // the basis (S once for the launch), W read and written, the coefficients
   const double upd_bytes = 16.0 * N * ((double)m + (double)nb * (p - m + 2.0 * sb)) + 16.0 * p * sb * (double)nb;
   // pass 1
   dot(b.C1, p, nullptr, nullptr);
   {
-    BUpd u{b.C1, b.cstride, b.W, b.wstride, b.W, b.wstride, nullptr, 0, nrowblk, 0, BHess{}};
-    prof_launch(prof, K_BUPDATE, upd_bytes, 8.0 * N * p * sb * nb, upd_kernel, dim3(xcd_grid(nb, nrowblk)), dim3(256),
-                0, s, g, u);
+    BUpd u{b.C1, b.cstride, b.W, b.wstride, b.W, b.wstride, nullptr, 0, nch, crows, 0, BHess{}};
+    prof_launch(prof, K_BUPDATE, upd_bytes, 8.0 * N * p * sb * nb, upd_kernel, dim3(ugrid), dim3(256), 0, s, g, u);
   }
   // pass 2 with the Gram matrix of the projected block
   dot(b.C2, p + sb, b.C1, b.Ct);
@@ -1144,10 +1287,10 @@ void block_step(const BlockSpan& sp, BlockWork& b, const Lattice& lat, const dou
   {
     BHess h{e, b.Ct, b.P, b.cstride, sp.ncap, b.R, b.R + 2 * kBlockMax * kBlockMax, b.rstride, sp.H, sp.hstride,
             sp.ldh};
-    const int nh = ((p + sb) * kBlockMax + 255) / 256;
+    const int nh = (((p + sb) * kBlockMax + 255) / 256 * nb + 7) / 8 * 8;
     BUpd u{b.C2, b.cstride, b.W, b.wstride, const_cast<double2*>(sp.V) + (size_t)(p - m) * ldq, sp.vstride,
-           b.R + kBlockMax * kBlockMax, b.rstride, nrowblk, nh, h};
-    prof_launch(prof, K_BUPDATE, upd_bytes, 8.0 * N * p * sb * nb, upd_kernel, dim3(xcd_grid(nb, nrowblk + nh)),
-                dim3(256), 0, s, g, u);
+           b.R + kBlockMax * kBlockMax, b.rstride, nch, crows, nh, h};
+    prof_launch(prof, K_BUPDATE, upd_bytes, 8.0 * N * p * sb * nb, upd_kernel, dim3(nh + ugrid), dim3(256), 0, s, g,
+                u);
   }
 }
