@@ -41,28 +41,6 @@ void dev_scale(const double2* in, double2* out, int n, const double* inv, hipStr
   SGN_HIP(hipGetLastError());
 }
 
-// one step of the Chebyshev recurrence on L = (A^2 - c) / e:
-// out = a (hy - c y) - b yp, with hy = A^2 y (out may alias yp)
-__global__ void cheb_step_kernel(const double2* hy, const double2* y, const double2* yp, double2* out, double a,
-                                 double c, double b, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const double2 h = hy[i], v = y[i];
-  double2 r = make_double2(a * (h.x - c * v.x), a * (h.y - c * v.y));
-  if (b != 0.0) {
-    const double2 q = yp[i];
-    r.x -= b * q.x;
-    r.y -= b * q.y;
-  }
-  out[i] = r;
-}
-
-void dev_cheb_step(const double2* hy, const double2* y, const double2* yp, double2* out, double a, double c, double b,
-                   int n, hipStream_t s) {
-  hipLaunchKernelGGL(cheb_step_kernel, dim3((n + 255) / 256), dim3(256), 0, s, hy, y, yp, out, a, c, b, n);
-  SGN_HIP(hipGetLastError());
-}
-
 struct DevBuf {
   void* p = nullptr;
   explicit DevBuf(size_t bytes) { SGN_HIP(hipMalloc(&p, bytes)); }
@@ -141,11 +119,8 @@ static DeflateStats deflate_run(sgn_ctx* c, int m, int nev, int ncv, int max_res
 
   DevBuf bV(sizeof(double2) * ldq * (size_t)(ncv + 1)), bVt(sizeof(double2) * ldq * (size_t)(ncv + 1));
   DevBuf bt(sizeof(double2) * ldq), bw(sizeof(double2) * ldq);
-  std::unique_ptr<DevBuf> bya, byb;  // Chebyshev recurrence
-  if (op.degree > 0) {
-    bya = std::make_unique<DevBuf>(sizeof(double2) * ldq);
-    byb = std::make_unique<DevBuf>(sizeof(double2) * ldq);
-  }
+  std::unique_ptr<DevBuf> by;  // Chebyshev recurrence: three vectors in turn
+  if (op.degree > 0) by = std::make_unique<DevBuf>(sizeof(double2) * 3 * ldq);
   DevBuf bH(sizeof(double2) * (size_t)ldh * ldh), bcoef(sizeof(double2) * (size_t)ldh * ldh);
   DevBuf bh1(sizeof(double2) * ldh), bh2(sizeof(double2) * ldh);
   DevBuf bsc(sizeof(double) * 8), bflag(sizeof(int) * 4);
@@ -184,30 +159,17 @@ static DeflateStats deflate_run(sgn_ctx* c, int m, int nev, int ncv, int max_res
   // w = operator(v): A^2 v, or T_d((A^2 - c) / e) v by the three-term
   // recurrence y_{j+1} = 2 L y_j - y_{j-1}, y_1 = L v, y_0 = v
   auto apply_op = [&](const double2* v) {
-    auto sq = [&](const double2* in, double2* out) {
-      wilson_apply(c->lat, c->links, in, t1, nullptr, nullptr, s, nullptr);
-      wilson_apply(c->lat, c->links, t1, out, nullptr, nullptr, s, nullptr);
-      st.matvecs += 2;
-    };
+    st.matvecs += 2 * std::max(1, op.degree);
     if (op.degree == 0) {
-      sq(v, w);
+      wilson_apply(c->lat, c->links, v, t1, nullptr, nullptr, s, nullptr);
+      wilson_apply(c->lat, c->links, t1, w, nullptr, nullptr, s, nullptr);
       return;
     }
-    double2* ya = bya->as<double2>();
-    double2* yb = byb->as<double2>();
     const double ie = 1.0 / op.e;
-    sq(v, w);
-    if (op.degree == 1) {
-      dev_cheb_step(w, v, v, w, ie, op.c, 0.0, N, s);
-      return;
-    }
-    dev_cheb_step(w, v, v, ya, ie, op.c, 0.0, N, s);  // y_1
-    const double2* prev = v;
-    double2* cur = ya;
-    for (int d = 2; d <= op.degree; ++d) {
-      sq(cur, w);
-      double2* out = (d == op.degree) ? w : (prev == v ? yb : const_cast<double2*>(prev));
-      dev_cheb_step(w, cur, prev, out, 2.0 * ie, op.c, 1.0, N, s);
+    const double2 *prev = nullptr, *cur = v;
+    for (int d = 1; d <= op.degree; ++d) {
+      double2* out = d == op.degree ? w : by->as<double2>() + (size_t)(d % 3) * ldq;
+      wilson_apply_square(c->lat, c->links, cur, t1, out, d == 1 ? ie : 2.0 * ie, op.c, 1.0, prev, s, nullptr);
       prev = cur;
       cur = out;
     }

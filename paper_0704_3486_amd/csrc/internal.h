@@ -255,6 +255,12 @@ void wilson_apply_cheb_slots(const Lattice& lat, const double2* links, const dou
                              double2* out, size_t ostride, const double2* prev, size_t pstride, double ca, double cb,
                              const SlotMap& map, hipStream_t s, Profiler* prof);
 
+// out = a (H_w^2 y - c y) - b yp (yp null: without it), a step of the
+// Chebyshev recurrence on (H_w^2 - c) / e; tmp takes H_w y.  out
+// is none of the other vectors.
+void wilson_apply_square(const Lattice& lat, const double2* links, const double2* y, double2* tmp, double2* out,
+                         double a, double c, double b, const double2* yp, hipStream_t s, Profiler* prof);
+
 // dense kernels (dense.hip)
 struct DenseWork {
   int method = 0;         // 0: Newton-Schulz with Roberts/Gauss-Jordan fallback; 1: Roberts only

@@ -189,9 +189,13 @@ __device__ inline Halves<double> halves(double v) {
 // entries for the second phase are loaded with the hop operands, so a
 // workgroup waits on memory once.
 // blockIdx.y = right-hand side (slot map).  Optional: scale = *inv_beta on
-// input and output, copy_out = In * scale; with CHEB, Out_r = ca H_w In_r +
+// input and output, copy_out = In * scale; with TERMS 1, Out_r = ca H_w In_r +
 // cb Prev_r (Prev_r = prev + slot pstride; prev null: cb ignored), a step of
-// a three-term polynomial recurrence.
+// a three-term recurrence in H_w; with TERMS 2, + cc Prev2_r (null: cc
+// ignored) as well, one in H_w^2 with In = H_w Prev.  The terms come with the
+// stencil's own operands, so a step of the recurrence in H_w^2 takes two
+// launches (6^4: 3.8 and 3.9 us; a third one that adds the terms took 2.4, and
+// the deflation setup of m = 20 121 instead of 101 ms).
 // ABI: in and out are in the interface layout (component 12 n + c).  A
 // site's 12 entries are then contiguous, so the wavefront reads its neighbour
 // sites' entries in that order and turns them through LDS.
@@ -204,11 +208,19 @@ __device__ inline Halves<double> halves(double v) {
 // and 242 us in the interface layout with S = 16 (272 us with S = 32, whose
 // 53 KB of LDS leave two wavefronts per SIMD less); packing, applying and
 // unpacking took 415 us.
-template <typename C, int S, bool CHEB, bool ABI>
+// the terms that a launch adds to ca H_w In
+template <typename C>
+struct Terms {
+  const C *prev = nullptr, *prev2 = nullptr;
+  size_t pstride = 0;  // slot stride of both
+  double ca = 1.0, cb = 0.0, cc = 0.0;
+};
+
+template <typename C, int S, int TERMS, bool ABI>
 __global__ void __launch_bounds__(256)
 wilson_hw_dir_kernel(const C* __restrict__ links, const C* __restrict__ in, size_t istride, C* __restrict__ out,
                      size_t ostride, const double* __restrict__ inv_beta, C* __restrict__ copy_out, Geom g,
-                     SlotMap map, SiteOrder order, const C* __restrict__ prev, size_t pstride, double ca, double cb) {
+                     SlotMap map, SiteOrder order, Terms<C> terms) {
   using R = typename Real<C>::type;
   static_assert(S == 32 || S == 16, "sites per workgroup");
   constexpr int kThreads = 256, kOut = 12 * S;
@@ -283,16 +295,18 @@ wilson_hw_dir_kernel(const C* __restrict__ links, const C* __restrict__ in, size
   load_link<C>(links, V, nu, ls, u);
   // second-phase outputs of this thread: p = tid + q kThreads < kOut, i.e.
   // component p / S of site n0 + p % S (ABI: component p % 12 of site n0 + p / 12)
-  C self[kRounds], pv[kRounds];
-  const C* __restrict__ pr = (CHEB && prev) ? prev + (size_t)slot * pstride : nullptr;
+  C self[kRounds], pv[kRounds], pv2[kRounds];
+  const C* __restrict__ pr = (TERMS > 0 && terms.prev) ? terms.prev + (size_t)slot * terms.pstride : nullptr;
+  const C* __restrict__ pr2 = (TERMS > 1 && terms.prev2) ? terms.prev2 + (size_t)slot * terms.pstride : nullptr;
 #pragma unroll
   for (int q = 0; q < kRounds; ++q) {
     const int p = threadIdx.x + q * kThreads, s2 = ABI ? p / 12 : p % S, nn = n0 + s2;
     const bool ok = p < kOut && nn < V;
     const size_t idx = ABI ? (size_t)n0 * 12 + p : (size_t)(p / S) * V + nn;
     self[q] = ok ? v[idx] : mk<C>(0, 0);
-    // the recurrence's previous term, loaded with the operands (one wait)
-    if constexpr (CHEB) pv[q] = (ok && pr) ? pr[idx] : mk<C>(0, 0);
+    // the recurrence's other terms, loaded with the operands (one wait)
+    if constexpr (TERMS > 0) pv[q] = (ok && pr) ? pr[idx] : mk<C>(0, 0);
+    if constexpr (TERMS > 1) pv2[q] = (ok && pr2) ? pr2[idx] : mk<C>(0, 0);
   }
   // the matrix applied to the half spinor: U (forward) or U^dag (backward)
   const R sg = fwd ? (R)1 : (R)-1;
@@ -363,10 +377,12 @@ wilson_hw_dir_kernel(const C* __restrict__ links, const C* __restrict__ in, size
     // gamma5 (psi - kappa * hops), all times 1/beta
     const R g5 = comp < 6 ? (R)1 : (R)-1;
     C val = tscale(tsub(self[q], tscale(acc, kappa)), g5 * scale);
-    if constexpr (CHEB) {
-      val = tscale(val, (R)ca);
-      if (pr) val = tadd(val, tscale(pv[q], (R)cb));
+    if constexpr (TERMS > 0) {
+      val = tscale(val, (R)terms.ca);
+      if (pr) val = tadd(val, tscale(pv[q], (R)terms.cb));
     }
+    if constexpr (TERMS > 1)
+      if (pr2) val = tadd(val, tscale(pv2[q], (R)terms.cc));
     w[idx] = val;
     if (copy_out) copy_out[idx] = tscale(self[q], scale);
   }
@@ -573,23 +589,23 @@ bool wilson_blocks_valid(const Lattice& lat, int By, int Bz, int Bt) {
 // 1024: 9.3 against 8.9).
 constexpr long long kSplitBelow = 512;
 
-template <typename C, int S, bool CHEB, bool ABI>
+template <typename C, int S, int TERMS, bool ABI>
 static void hw_launch_as(const Lattice& lat, const C* links, const C* in, size_t istride, C* out, size_t ostride,
-                         const double* inv_beta, C* copy_out, const SlotMap& map, const C* prev, size_t pstride,
-                         double ca, double cb, double bytes, hipStream_t s, Profiler* prof) {
+                         const double* inv_beta, C* copy_out, const SlotMap& map, const Terms<C>& terms, double bytes,
+                         hipStream_t s, Profiler* prof) {
   const int nblk = (lat.V + S - 1) / S;
-  prof_launch(prof, K_WILSON, bytes, 1392.0 * lat.V * map.n, wilson_hw_dir_kernel<C, S, CHEB, ABI>,
+  prof_launch(prof, K_WILSON, bytes, 1392.0 * lat.V * map.n, wilson_hw_dir_kernel<C, S, TERMS, ABI>,
               dim3(nblk, map.n), dim3(256), 0, s, links, in, istride, out, ostride, inv_beta, copy_out,
-              geom(lat, nblk), map, site_order(lat, S), prev, pstride, ca, cb);
+              geom(lat, nblk), map, site_order(lat, S), terms);
 }
 
-template <typename C, bool CHEB>
+template <typename C, int TERMS>
 static void hw_launch(const Lattice& lat, const C* links, const C* in, size_t istride, C* out, size_t ostride,
-                      const double* inv_beta, C* copy_out, const SlotMap& map, const C* prev, size_t pstride,
-                      double ca, double cb, double bytes, hipStream_t s, Profiler* prof) {
+                      const double* inv_beta, C* copy_out, const SlotMap& map, const Terms<C>& terms, double bytes,
+                      hipStream_t s, Profiler* prof) {
   const bool fine = (long long)((lat.V + 31) / 32) * map.n < kSplitBelow;
-  (fine ? hw_launch_as<C, 16, CHEB, false> : hw_launch_as<C, 32, CHEB, false>)(
-      lat, links, in, istride, out, ostride, inv_beta, copy_out, map, prev, pstride, ca, cb, bytes, s, prof);
+  (fine ? hw_launch_as<C, 16, TERMS, false> : hw_launch_as<C, 32, TERMS, false>)(
+      lat, links, in, istride, out, ostride, inv_beta, copy_out, map, terms, bytes, s, prof);
 }
 
 static SlotMap one_slot() {
@@ -603,20 +619,20 @@ void wilson_apply(const Lattice& lat, const double2* links, const double2* in, d
   // algorithmic bytes: read v (12), write w (12), 4 links of 6 stored entries
   // (24) per site; + copy (12)
   const double per_site = (48.0 + (copy_out ? 12.0 : 0.0)) * 16.0;
-  hw_launch<double2, false>(lat, links, in, 0, out, 0, inv_beta, copy_out, one_slot(), nullptr, 0, 1.0, 0.0,
-                            per_site * lat.V, s, prof);
+  hw_launch<double2, 0>(lat, links, in, 0, out, 0, inv_beta, copy_out, one_slot(), Terms<double2>{},
+                        per_site * lat.V, s, prof);
 }
 
 void wilson_apply32(const Lattice& lat, const float2* links, const float2* in, float2* out, hipStream_t s,
                     Profiler* prof) {
-  hw_launch<float2, false>(lat, links, in, 0, out, 0, nullptr, nullptr, one_slot(), nullptr, 0, 1.0, 0.0,
-                           48.0 * 8.0 * lat.V, s, prof);
+  hw_launch<float2, 0>(lat, links, in, 0, out, 0, nullptr, nullptr, one_slot(), Terms<float2>{}, 48.0 * 8.0 * lat.V,
+                       s, prof);
 }
 
 void wilson_apply_abi(const Lattice& lat, const double2* links, const double2* x, double2* y, hipStream_t s,
                       Profiler* prof) {
-  hw_launch_as<double2, 16, false, true>(lat, links, x, 0, y, 0, nullptr, nullptr, one_slot(), nullptr, 0, 1.0, 0.0,
-                                         48.0 * 16.0 * lat.V, s, prof);
+  hw_launch_as<double2, 16, 0, true>(lat, links, x, 0, y, 0, nullptr, nullptr, one_slot(), Terms<double2>{},
+                                     48.0 * 16.0 * lat.V, s, prof);
 }
 
 void wilson_apply_cheb_slots(const Lattice& lat, const double2* links, const double2* in, size_t istride,
@@ -626,8 +642,25 @@ void wilson_apply_cheb_slots(const Lattice& lat, const double2* links, const dou
   // per site: the links (24 stored entries) once, per slot read v and
   // prev, write w (12 each)
   const double bytes = (24.0 + (24.0 + (prev ? 12.0 : 0.0)) * map.n) * 16.0 * lat.V;
-  hw_launch<double2, true>(lat, links, in, istride, out, ostride, nullptr, nullptr, map, prev, pstride, ca, cb, bytes,
-                           s, prof);
+  Terms<double2> t;
+  t.prev = prev;
+  t.pstride = pstride;
+  t.ca = ca;
+  t.cb = cb;
+  hw_launch<double2, 1>(lat, links, in, istride, out, ostride, nullptr, nullptr, map, t, bytes, s, prof);
+}
+
+void wilson_apply_square(const Lattice& lat, const double2* links, const double2* y, double2* tmp, double2* out,
+                         double a, double c, double b, const double2* yp, hipStream_t s, Profiler* prof) {
+  wilson_apply(lat, links, y, tmp, nullptr, nullptr, s, prof);
+  Terms<double2> t;
+  t.prev = y;
+  t.prev2 = yp;
+  t.ca = a;
+  t.cb = -a * c;
+  t.cc = -b;
+  const double per_site = (60.0 + (yp ? 12.0 : 0.0)) * 16.0;
+  hw_launch<double2, 2>(lat, links, tmp, 0, out, 0, nullptr, nullptr, one_slot(), t, per_site * lat.V, s, prof);
 }
 
 template <typename C>
@@ -636,8 +669,8 @@ void wilson_apply_slots(const Lattice& lat, const C* links, const C* in, size_t 
   SGN_REQUIRE(map.n >= 1 && map.n <= kMaxBatch, SGN_EINVAL, "wilson: slot map must hold 1..64 slots");
   // per site: the links (24 stored entries) once, per slot read v (12) and write w (12)
   const double b = (double)sizeof(C);
-  hw_launch<C, false>(lat, links, in, istride, out, ostride, nullptr, nullptr, map, nullptr, 0, 1.0, 0.0,
-                      (24.0 + 24.0 * map.n) * b * lat.V, s, prof);
+  hw_launch<C, 0>(lat, links, in, istride, out, ostride, nullptr, nullptr, map, Terms<C>{},
+                  (24.0 + 24.0 * map.n) * b * lat.V, s, prof);
 }
 template void wilson_apply_slots<double2>(const Lattice&, const double2*, const double2*, size_t, double2*, size_t,
                                           const SlotMap&, hipStream_t, Profiler*);
