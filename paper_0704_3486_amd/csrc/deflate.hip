@@ -255,20 +255,11 @@ static DeflateStats deflate_run(sgn_ctx* c, int m, int nev, int ncv, int max_res
       kk = w2;
     }
     // T_k = Yq^H H Yq, b = beta * Yq[ncv-1, :]
-    std::vector<cplx> HY((size_t)ncv * kk, cplx(0.0, 0.0));
-    for (int i = 0; i < kk; ++i)
-      for (int l = 0; l < ncv; ++l) {
-        const cplx y = Yq[(size_t)i * ncv + l];
-        if (y == cplx(0.0, 0.0)) continue;
-        for (int r = 0; r < ncv; ++r) HY[(size_t)i * ncv + r] += Hn[(size_t)l * ncv + r] * y;
-      }
+    std::vector<cplx> Tk((size_t)kk * kk);
+    hostla::project(ncv, kk, Hn.data(), Yq.data(), Tk.data(), kk);
     std::fill(Hh.begin(), Hh.end(), make_double2(0.0, 0.0));
     for (int i = 0; i < kk; ++i) {
-      for (int r = 0; r < kk; ++r) {
-        cplx sacc = 0.0;
-        for (int l = 0; l < ncv; ++l) sacc += std::conj(Yq[(size_t)r * ncv + l]) * HY[(size_t)i * ncv + l];
-        Hh[(size_t)i * ldh + r] = to_d2(sacc);
-      }
+      for (int r = 0; r < kk; ++r) Hh[(size_t)i * ldh + r] = to_d2(Tk[(size_t)i * kk + r]);
       Hh[(size_t)i * ldh + kk] = to_d2(beta * Yq[(size_t)i * ncv + (ncv - 1)]);
     }
     std::vector<double2> cf((size_t)ncv * kk);

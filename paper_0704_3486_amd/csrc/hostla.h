@@ -26,4 +26,7 @@ bool eig(int n, const cplx* A, cplx* w, cplx* V);
 // original norm are zeroed.  Returns the numerical rank.
 int thin_qr(int rows, int cols, cplx* A, double rank_tol);
 
+// T = Q^H H Q (k x k, leading dimension ldt) for H n x n and Q n x k
+void project(int n, int k, const cplx* H, const cplx* Q, cplx* T, int ldt);
+
 }  // namespace hostla
