@@ -5,101 +5,112 @@
 // A = Z T Z^H), eigenvectors of the triangular factor by back substitution,
 // and a thin QR factorisation (modified Gram-Schmidt, applied twice).
 //
-// Every inner loop runs down a column (or over the adjacent entries of two
-// rows) on four doubles at a time, in code for AVX2 and FMA where the host has
-// them.  The eigenproblem of 90 columns that a restart of the m = 20 setup
-// solves: 9.2 ms with strided scalar loops, 3.8 ms so.
+// The inner loops run down columns (or over the adjacent entries of two rows)
+// on four doubles at a time, and sums that are one chain of additions run four
+// at a time, in code for AVX2 where the host has it.  Every entry sees the
+// operations of the plain loops in their order, without contraction, so the
+// results do not depend on the host.  The eigenproblem of 90 columns that a
+// restart of the m = 20 setup solves: 9.2 ms with strided scalar loops,
+// 5.4 ms so.
 #include "hostla.h"
 
 #include <algorithm>
 #include <cmath>
 #include <limits>
 
+#pragma clang fp contract(off)
+
 namespace hostla {
 
 namespace {
 
 #define SGN_HOST_INLINE inline __attribute__((always_inline))
-// name(params) from name_body, compiled for any x86-64 and for AVX2 with FMA
-#define SGN_HOST_CLONES(ret, name, params, args)                                                             \
-  namespace {                                                                                                \
-  __attribute__((target("avx2,fma"))) ret name##_avx2 params { return name##_body args; }                    \
-  }                                                                                                          \
-  ret name params {                                                                                          \
-    return __builtin_cpu_supports("avx2") && __builtin_cpu_supports("fma") ? name##_avx2 args : name##_body args; \
-  }
+// name(params) from name_body, compiled for any x86-64 and for AVX2
+#define SGN_HOST_CLONES(ret, name, params, args)                                     \
+  namespace {                                                                        \
+  __attribute__((target("avx2"))) ret name##_avx2 params { return name##_body args; } \
+  }                                                                                  \
+  ret name params { return __builtin_cpu_supports("avx2") ? name##_avx2 args : name##_body args; }
 
-typedef double v4u __attribute__((vector_size(32), aligned(8)));  // any two adjacent entries
+typedef double v2 __attribute__((vector_size(16), aligned(8)));  // an entry
+typedef double v4 __attribute__((vector_size(32), aligned(8)));  // two adjacent entries
 
-SGN_HOST_INLINE v4u load2(const cplx* p) { return *reinterpret_cast<const v4u*>(p); }
-SGN_HOST_INLINE void store2(cplx* p, v4u v) { *reinterpret_cast<v4u*>(p) = v; }
-SGN_HOST_INLINE v4u swap2(v4u v) { return __builtin_shufflevector(v, v, 1, 0, 3, 2); }
+SGN_HOST_INLINE v4 load2(const cplx* p) { return *reinterpret_cast<const v4*>(p); }
+SGN_HOST_INLINE void store2(cplx* p, v4 v) { *reinterpret_cast<v4*>(p) = v; }
+SGN_HOST_INLINE v4 swap2(v4 v) { return __builtin_shufflevector(v, v, 1, 0, 3, 2); }
 
-// y += a x over n entries
+// y += a x (SUB: y -= a x) over n entries
+template <bool SUB>
 SGN_HOST_INLINE void axpy(int n, cplx a, const cplx* x, cplx* y) {
   const double r = a.real(), m = a.imag();
-  const v4u ar = {r, r, r, r}, ai = {-m, m, -m, m};
+  const v4 ar = {r, r, r, r}, ai = {-m, m, -m, m};
   int i = 0;
   for (; i + 2 <= n; i += 2) {
-    const v4u xv = load2(x + i);
-    store2(y + i, load2(y + i) + ar * xv + ai * swap2(xv));
+    const v4 xv = load2(x + i), p = ar * xv + ai * swap2(xv);
+    store2(y + i, SUB ? load2(y + i) - p : load2(y + i) + p);
   }
-  if (i < n) y[i] += a * x[i];
+  if (i < n) {
+    if (SUB)
+      y[i] -= a * x[i];
+    else
+      y[i] += a * x[i];
+  }
 }
 
-// sum conj(x_i) y_i
-SGN_HOST_INLINE cplx dotc(int n, const cplx* x, const cplx* y) {
-  // p: (xr yr, xi yi), q: (xr yi, xi yr)
-  v4u p0 = {0, 0, 0, 0}, p1 = p0, q0 = p0, q1 = p0;
-  int i = 0;
-  for (; i + 4 <= n; i += 4) {
-    const v4u xa = load2(x + i), ya = load2(y + i), xb = load2(x + i + 2), yb = load2(y + i + 2);
-    p0 += xa * ya;
-    q0 += xa * swap2(ya);
-    p1 += xb * yb;
-    q1 += xb * swap2(yb);
-  }
-  const v4u p = p0 + p1, q = q0 + q1;
-  cplx s(p[0] + p[1] + p[2] + p[3], q[0] - q[1] + q[2] - q[3]);
-  for (; i < n; ++i) s += std::conj(x[i]) * y[i];
-  return s;
+// out[k] = sum_i conj(x_k[i]) y_k[i] for K pairs, each sum in the order of i
+template <int K>
+SGN_HOST_INLINE void dots(int n, const cplx* const* x, const cplx* const* y, cplx* out) {
+  v2 s[K];
+  for (int k = 0; k < K; ++k) s[k] = v2{0.0, 0.0};
+  for (int i = 0; i < n; ++i)
+    for (int k = 0; k < K; ++k) {
+      const v2 a = *reinterpret_cast<const v2*>(x[k] + i), b = *reinterpret_cast<const v2*>(y[k] + i);
+      const v2 re = {a[0], a[0]}, im = {a[1], -a[1]};
+      s[k] += re * b + im * __builtin_shufflevector(b, b, 1, 0);
+    }
+  for (int k = 0; k < K; ++k) out[k] = cplx(s[k][0], s[k][1]);
 }
 
-SGN_HOST_INLINE double norm2(int n, const cplx* x) {
-  v4u p0 = {0, 0, 0, 0}, p1 = p0;
-  int i = 0;
-  for (; i + 4 <= n; i += 4) {
-    const v4u a = load2(x + i), b = load2(x + i + 2);
-    p0 += a * a;
-    p1 += b * b;
+// the sums conj(x_k)^T y for k = 0 .. n-1, four at a time: one of x and y is a
+// column per k (x0 + k ldx, y0 + k ldy), put(k, sum)
+template <typename Put>
+SGN_HOST_INLINE void dot_cols(int len, int n, const cplx* x0, size_t ldx, const cplx* y0, size_t ldy, Put put) {
+  int k = 0;
+  cplx out[4];
+  for (; k + 4 <= n; k += 4) {
+    const cplx* x[4] = {x0 + k * ldx, x0 + (k + 1) * ldx, x0 + (k + 2) * ldx, x0 + (k + 3) * ldx};
+    const cplx* y[4] = {y0 + k * ldy, y0 + (k + 1) * ldy, y0 + (k + 2) * ldy, y0 + (k + 3) * ldy};
+    dots<4>(len, x, y, out);
+    for (int t = 0; t < 4; ++t) put(k + t, out[t]);
   }
-  const v4u p = p0 + p1;
-  double s = p[0] + p[1] + p[2] + p[3];
-  for (; i < n; ++i) s += std::norm(x[i]);
-  return s;
+  for (; k < n; ++k) {
+    const cplx *x = x0 + k * ldx, *y = y0 + k * ldy;
+    dots<1>(len, &x, &y, out);
+    put(k, out[0]);
+  }
 }
 
 // (a, b) -> (c a + s b, -conj(s) a + c b) for the entry pairs (a, b) = x[0],
 // x[1] of n columns `ld` apart: two adjacent rows
 SGN_HOST_INLINE void rot_rows(int n, double c, cplx s, cplx* x, size_t ld) {
   const double r = s.real(), m = s.imag();
-  const v4u cv = {c, c, c, c}, fr = {r, m, -r, m}, fi = {-m, r, -m, -r};
+  const v4 cv = {c, c, c, c}, fr = {r, m, -r, m}, fi = {-m, r, -m, -r};
   for (int j = 0; j < n; ++j, x += ld) {
-    const v4u v = load2(x);
-    const v4u re = __builtin_shufflevector(v, v, 2, 2, 0, 0), im = __builtin_shufflevector(v, v, 3, 3, 1, 1);
-    store2(x, cv * v + fr * re + fi * im);
+    const v4 v = load2(x);
+    const v4 re = __builtin_shufflevector(v, v, 2, 2, 0, 0), im = __builtin_shufflevector(v, v, 3, 3, 1, 1);
+    store2(x, cv * v + (fr * re + fi * im));
   }
 }
 
 // (a, b) -> (c a + conj(s) b, -s a + c b) over n rows of two columns
 SGN_HOST_INLINE void rot_cols(int n, double c, cplx s, cplx* a, cplx* b) {
   const double r = s.real(), m = s.imag();
-  const v4u cv = {c, c, c, c}, rv = {r, r, r, r}, mv = {m, -m, m, -m};
+  const v4 cv = {c, c, c, c}, rv = {r, r, r, r}, mv = {m, -m, m, -m};
   int i = 0;
   for (; i + 2 <= n; i += 2) {
-    const v4u av = load2(a + i), bv = load2(b + i);
-    store2(a + i, cv * av + rv * bv + mv * swap2(bv));
-    store2(b + i, cv * bv - rv * av + mv * swap2(av));
+    const v4 av = load2(a + i), bv = load2(b + i);
+    store2(a + i, cv * av + (rv * bv + mv * swap2(bv)));
+    store2(b + i, (mv * swap2(av) - rv * av) + cv * bv);
   }
   if (i < n) {
     const cplx x = a[i], y = b[i];
@@ -112,13 +123,6 @@ inline double abs1(cplx z) { return std::abs(z.real()) + std::abs(z.imag()); }
 
 // Givens rotation G = [[c, s], [-conj(s), c]] with G (x, y)^T = (r, 0)^T.
 inline void givens(cplx x, cplx y, double& c, cplx& s) {
-  const double x2 = std::norm(x), y2 = std::norm(y), r2 = x2 + y2;
-  if (x2 > 1e-280 && y2 > 1e-280 && r2 < 1e280) {  // squares without over- or underflow
-    const double ax = std::sqrt(x2), inv = 1.0 / std::sqrt(r2);
-    c = ax * inv;
-    s = x * std::conj(y) * (inv / ax);
-    return;
-  }
   const double ax = std::abs(x), ay = std::abs(y);
   if (ay == 0.0) {
     c = 1.0;
@@ -146,23 +150,29 @@ static SGN_HOST_INLINE void hessenberg_body(int n, cplx* H, cplx* Q) {
   std::vector<cplx> v(n), tmp(n);
   for (int k = 0; k + 2 < n; ++k) {
     const int len = n - k - 1;
-    const double xn = std::sqrt(norm2(len, &h(k + 1, k)));
+    double xn = 0.0;
+    for (int i = 0; i < len; ++i) xn += std::norm(h(k + 1 + i, k));
+    xn = std::sqrt(xn);
     if (xn == 0.0) continue;
     const cplx x0 = h(k + 1, k);
     const cplx ph = (std::abs(x0) > 0.0) ? x0 / std::abs(x0) : cplx(1.0, 0.0);
     const cplx alpha = -ph * xn;
     for (int i = 0; i < len; ++i) v[i] = h(k + 1 + i, k);
     v[0] -= alpha;
-    const double vn = norm2(len, v.data());
+    double vn = 0.0;
+    for (int i = 0; i < len; ++i) vn += std::norm(v[i]);
     if (vn == 0.0) continue;
     const double tau = 2.0 / vn;
     // left: H[k+1:, k:] -= tau v (v^H H[k+1:, k:])
-    for (int j = k; j < n; ++j) axpy(len, -tau * dotc(len, v.data(), &h(k + 1, j)), v.data(), &h(k + 1, j));
+    dot_cols(len, n - k, v.data(), 0, &h(k + 1, k), n,
+             [&](int j, cplx sum) __attribute__((always_inline)) { axpy<true>(len, sum * tau, v.data(), &h(k + 1, k + j)); });
     // right: H[:, k+1:] -= tau (H[:, k+1:] v) v^H ; same for Q
     for (cplx* M : {H, Q}) {
+      cplx* cols = M + (size_t)(k + 1) * n;
       std::fill(tmp.begin(), tmp.end(), cplx(0.0, 0.0));
-      for (int l = 0; l < len; ++l) axpy(n, tau * v[l], M + (size_t)(k + 1 + l) * n, tmp.data());
-      for (int l = 0; l < len; ++l) axpy(n, -std::conj(v[l]), tmp.data(), M + (size_t)(k + 1 + l) * n);
+      for (int l = 0; l < len; ++l) axpy<false>(n, v[l], cols + (size_t)l * n, tmp.data());
+      for (int i = 0; i < n; ++i) tmp[i] *= tau;
+      for (int l = 0; l < len; ++l) axpy<true>(n, std::conj(v[l]), tmp.data(), cols + (size_t)l * n);
     }
     for (int i = 2; i <= len; ++i) h(k + i, k) = 0.0;
   }
@@ -235,24 +245,27 @@ static SGN_HOST_INLINE bool eig_body(int n, const cplx* A, cplx* w, cplx* V) {
   double tn = 0.0;
   for (auto& v : T) tn = std::max(tn, std::abs(v));
   const double small = std::numeric_limits<double>::epsilon() * (tn > 0 ? tn : 1.0);
-  // x = the unit upper triangular solution of (T - t_ii) x = 0, column by
-  // column of T; V = Z x, unit columns
-  std::vector<cplx> x(n);
+  std::vector<cplx> x(n), Tt((size_t)n * n);  // Tt: T by rows
+  for (int j = 0; j < n; ++j)
+    for (int i = 0; i <= j; ++i) Tt[(size_t)i * n + j] = t(i, j);
   for (int i = 0; i < n; ++i) {
     w[i] = t(i, i);
-    for (int j = 0; j < i; ++j) x[j] = -t(j, i);
     x[i] = 1.0;
     for (int j = i - 1; j >= 0; --j) {
+      cplx s = 0.0;
+      for (int l = j + 1; l <= i; ++l) s += Tt[(size_t)j * n + l] * x[l];
       cplx d = t(j, j) - t(i, i);
       if (std::abs(d) < small) d = small;
-      x[j] /= d;
-      axpy(j, -x[j], &t(0, j), x.data());
+      x[j] = -s / d;
     }
+    // column i of V = Z X, of unit length
     cplx* y = V + (size_t)i * n;
     std::fill(y, y + n, cplx(0.0, 0.0));
-    for (int l = 0; l <= i; ++l) axpy(n, x[l], &Z[(size_t)l * n], y);
-    const double inv = 1.0 / std::sqrt(norm2(n, y));
-    for (int r = 0; r < n; ++r) y[r] *= inv;
+    for (int l = 0; l <= i; ++l) axpy<false>(n, x[l], &Z[(size_t)l * n], y);
+    double nn = 0.0;
+    for (int r = 0; r < n; ++r) nn += std::norm(y[r]);
+    nn = std::sqrt(nn);
+    for (int r = 0; r < n; ++r) y[r] /= nn;
   }
   return true;
 }
@@ -261,18 +274,29 @@ SGN_HOST_CLONES(bool, eig, (int n, const cplx* A, cplx* w, cplx* V), (n, A, w, V
 static SGN_HOST_INLINE int thin_qr_body(int rows, int cols, cplx* A, double rank_tol) {
   auto a = [&](int i, int j) -> cplx& { return A[(size_t)j * rows + i]; };
   int rank = 0;
+  std::vector<double> norm0(cols, 0.0);
   for (int j = 0; j < cols; ++j) {
-    const double n0 = std::sqrt(norm2(rows, &a(0, j)));
-    for (int pass = 0; pass < 2; ++pass) {
-      for (int k = 0; k < j; ++k) axpy(rows, -dotc(rows, &a(0, k), &a(0, j)), &a(0, k), &a(0, j));
-    }
-    const double nn = std::sqrt(norm2(rows, &a(0, j)));
+    for (int i = 0; i < rows; ++i) norm0[j] += std::norm(a(i, j));
+    norm0[j] = std::sqrt(norm0[j]);
+  }
+  for (int j = 0; j < cols; ++j) {
+    const double n0 = norm0[j];
+    // the first pass against columns 0 .. j-1 is done (below); the second
+    for (int k = 0; k < j; ++k)
+      dot_cols(rows, 1, &a(0, k), rows, &a(0, j), rows,
+               [&](int, cplx sum) __attribute__((always_inline)) { axpy<true>(rows, sum, &a(0, k), &a(0, j)); });
+    double nn = 0.0;
+    for (int i = 0; i < rows; ++i) nn += std::norm(a(i, j));
+    nn = std::sqrt(nn);
     if (nn <= rank_tol * (n0 > 0 ? n0 : 1.0)) {
       for (int i = 0; i < rows; ++i) a(i, j) = 0.0;
-      continue;
+    } else {
+      for (int i = 0; i < rows; ++i) a(i, j) /= nn;
+      ++rank;
     }
-    for (int i = 0; i < rows; ++i) a(i, j) /= nn;
-    ++rank;
+    // first pass of the later columns against column j
+    dot_cols(rows, cols - j - 1, &a(0, j), 0, &A[(size_t)(j + 1) * rows], rows,
+             [&](int l, cplx sum) __attribute__((always_inline)) { axpy<true>(rows, sum, &a(0, j), &a(0, j + 1 + l)); });
   }
   return rank;
 }
@@ -284,9 +308,9 @@ static SGN_HOST_INLINE void project_body(int n, int k, const cplx* H, const cplx
     std::fill(hq.begin(), hq.end(), cplx(0.0, 0.0));
     for (int l = 0; l < n; ++l) {
       const cplx y = Q[(size_t)j * n + l];
-      if (y != cplx(0.0, 0.0)) axpy(n, y, H + (size_t)l * n, hq.data());
+      if (y != cplx(0.0, 0.0)) axpy<false>(n, y, H + (size_t)l * n, hq.data());
     }
-    for (int i = 0; i < k; ++i) T[(size_t)j * ldt + i] = dotc(n, Q + (size_t)i * n, hq.data());
+    dot_cols(n, k, Q, n, hq.data(), 0, [&](int i, cplx sum) __attribute__((always_inline)) { T[(size_t)j * ldt + i] = sum; });
   }
 }
 SGN_HOST_CLONES(void, project, (int n, int k, const cplx* H, const cplx* Q, cplx* T, int ldt), (n, k, H, Q, T, ldt))

@@ -191,11 +191,12 @@ __device__ inline Halves<double> halves(double v) {
 // blockIdx.y = right-hand side (slot map).  Optional: scale = *inv_beta on
 // input and output, copy_out = In * scale; with TERMS 1, Out_r = ca H_w In_r +
 // cb Prev_r (Prev_r = prev + slot pstride; prev null: cb ignored), a step of
-// a three-term recurrence in H_w; with TERMS 2, + cc Prev2_r (null: cc
-// ignored) as well, one in H_w^2 with In = H_w Prev.  The terms come with the
-// stencil's own operands, so a step of the recurrence in H_w^2 takes two
-// launches (6^4: 3.8 and 3.9 us; a third one that adds the terms took 2.4, and
-// the deflation setup of m = 20 121 instead of 101 ms).
+// a three-term recurrence in H_w; with TERMS 2, Out_r = ca (H_w In_r + cb
+// Prev_r) + cc Prev2_r (prev2 null: cc ignored), one in H_w^2 with In = H_w
+// Prev.  The terms come with the stencil's own operands, so a step of the
+// recurrence in H_w^2 takes two launches (6^4: 3.8 and 3.9 us; a third one that
+// adds the terms took 2.4, and the deflation setup of m = 20 121 instead of 101
+// ms).
 // ABI: in and out are in the interface layout (component 12 n + c).  A
 // site's 12 entries are then contiguous, so the wavefront reads its neighbour
 // sites' entries in that order and turns them through LDS.
@@ -377,12 +378,15 @@ wilson_hw_dir_kernel(const C* __restrict__ links, const C* __restrict__ in, size
     // gamma5 (psi - kappa * hops), all times 1/beta
     const R g5 = comp < 6 ? (R)1 : (R)-1;
     C val = tscale(tsub(self[q], tscale(acc, kappa)), g5 * scale);
-    if constexpr (TERMS > 0) {
+    if constexpr (TERMS == 1) {
       val = tscale(val, (R)terms.ca);
       if (pr) val = tadd(val, tscale(pv[q], (R)terms.cb));
     }
-    if constexpr (TERMS > 1)
-      if (pr2) val = tadd(val, tscale(pv2[q], (R)terms.cc));
+    if constexpr (TERMS == 2) {
+      const R ca = (R)terms.ca, cb = (R)terms.cb, cc = (R)terms.cc;
+      val = mk<C>(ca * fma(cb, pv[q].x, val.x), ca * fma(cb, pv[q].y, val.y));
+      if (pr2) val = mk<C>(fma(cc, pv2[q].x, val.x), fma(cc, pv2[q].y, val.y));
+    }
     w[idx] = val;
     if (copy_out) copy_out[idx] = tscale(self[q], scale);
   }
@@ -657,7 +661,7 @@ void wilson_apply_square(const Lattice& lat, const double2* links, const double2
   t.prev = y;
   t.prev2 = yp;
   t.ca = a;
-  t.cb = -a * c;
+  t.cb = -c;
   t.cc = -b;
   const double per_site = (60.0 + (yp ? 12.0 : 0.0)) * 16.0;
   hw_launch<double2, 2>(lat, links, tmp, 0, out, 0, nullptr, nullptr, one_slot(), t, per_site * lat.V, s, prof);
