@@ -186,17 +186,37 @@ __device__ inline int dot_row(int row0, int t, int lane) {
   return R == 1 ? row0 + t * 64 + lane : row0 + (t >> 1) * 128 + 2 * lane + (t & 1);
 }
 
+// 16 bytes of a basis column: cached, or (NT) streamed past the caches
+typedef float f4v __attribute__((ext_vector_type(4)));
+typedef double d2v __attribute__((ext_vector_type(2)));
+template <bool NT>
+__device__ inline float4 col_load(const float4* p) {
+  if constexpr (NT) {
+    const f4v v = __builtin_nontemporal_load(reinterpret_cast<const f4v*>(p));
+    return make_float4(v.x, v.y, v.z, v.w);
+  }
+  return *p;
+}
+template <bool NT>
+__device__ inline double2 col_load(const double2* p) {
+  if constexpr (NT) {
+    const d2v v = __builtin_nontemporal_load(reinterpret_cast<const d2v*>(p));
+    return make_double2(v.x, v.y);
+  }
+  return *p;
+}
+
 // a lane's kRpl rows of one column, as loaded: FP64 entries, or FP32 pairs
 template <typename QT>
 struct ColBuf {
   double2 q[kRpl];
-  template <int R>
+  template <int R, bool NT>
   __device__ inline void load(const double2* __restrict__ p, int row0, int lane, int N) {
 #pragma unroll
     for (int t = 0; t < kRpl; t += R) {
       const int i = min(dot_row<R>(row0, t, lane), N - R);
 #pragma unroll
-      for (int k = 0; k < R; ++k) q[t + k] = p[i + k];
+      for (int k = 0; k < R; ++k) q[t + k] = col_load<NT>(p + i + k);
     }
   }
   __device__ inline double2 at(int t) const { return q[t]; }
@@ -204,13 +224,13 @@ struct ColBuf {
 template <>
 struct ColBuf<float2> {
   float4 q[kRpl / 2];
-  template <int R>
+  template <int R, bool NT>
   __device__ inline void load(const float2* __restrict__ p, int row0, int lane, int N) {
     static_assert(R == 2, "FP32 columns come in row pairs");
     // N is even, so a pair lies wholly below N or wholly at or above it
 #pragma unroll
     for (int t = 0; t < kRpl; t += 2)
-      q[t / 2] = *reinterpret_cast<const float4*>(p + min(dot_row<2>(row0, t, lane), N - 2));
+      q[t / 2] = col_load<NT>(reinterpret_cast<const float4*>(p + min(dot_row<2>(row0, t, lane), N - 2)));
   }
   __device__ inline double2 at(int t) const {
     const float4 v = q[t / 2];
@@ -275,17 +295,17 @@ struct Weights {
 
 // C columns from c0 on of the Schur (S) or Krylov part; columns past cend
 // reload the last one (their sums are not used)
-template <typename QT, int C, int R>
+template <typename QT, int C, int R, bool NT = false>
 __device__ inline void load_cols(ColBuf<QT> (&q)[C], const QT* __restrict__ base, size_t ldq, int c0, int cend,
                                  int row0, int lane, int N) {
 #pragma unroll
-  for (int cc = 0; cc < C; ++cc) q[cc].template load<R>(base + (size_t)min(c0 + cc, cend - 1) * ldq, row0, lane, N);
+  for (int cc = 0; cc < C; ++cc) q[cc].template load<R, NT>(base + (size_t)min(c0 + cc, cend - 1) * ldq, row0, lane, N);
 }
 
 // Columns [c0, c0 + C ng) of one base against the tile's weights, C at a time,
 // the next C loaded before the sums of the current ones; put(c, k, sum) takes
 // value k of column c (counted from the base)
-template <typename QT, int C, int R, typename W, typename Put>
+template <typename QT, int C, int R, bool NT, typename W, typename Put>
 __device__ inline void dot_walk(const W& w, const QT* __restrict__ base, size_t ldq, int c0, int ng, int cend,
                                 int row0, int lane, int N, Put put) {
   auto out = [&](int cb, double sum) {
@@ -294,15 +314,15 @@ __device__ inline void dot_walk(const W& w, const QT* __restrict__ base, size_t 
     if (lane % kLanes == 0 && cb + k / 4 < cend) put(cb + k / 4, k % 4, sum);
   };
   ColBuf<QT> qa[C], qb[C];
-  load_cols<QT, C, R>(qa, base, ldq, c0, cend, row0, lane, N);
+  load_cols<QT, C, R, NT>(qa, base, ldq, c0, cend, row0, lane, N);
   for (int g = 0; g < ng; g += 2) {
     const int cb = c0 + g * C;
     if (cb >= cend) return;
     const bool second = g + 1 < ng && cb + C < cend;
-    if (second) load_cols<QT, C, R>(qb, base, ldq, cb + C, cend, row0, lane, N);
+    if (second) load_cols<QT, C, R, NT>(qb, base, ldq, cb + C, cend, row0, lane, N);
     out(cb, w.template dot<QT, C>(qa, lane));
     if (!second) return;
-    if (g + 2 < ng && cb + 2 * C < cend) load_cols<QT, C, R>(qa, base, ldq, cb + 2 * C, cend, row0, lane, N);
+    if (g + 2 < ng && cb + 2 * C < cend) load_cols<QT, C, R, NT>(qa, base, ldq, cb + 2 * C, cend, row0, lane, N);
     out(cb + C, w.template dot<QT, C>(qb, lane));
   }
 }
@@ -321,7 +341,8 @@ struct ColGroups {
 // four sums); without Schur columns 4.9 TB/s, of the 6.1 that a plain read of
 // this size reaches.
 template <typename VT, int C>
-__global__ void __launch_bounds__(256) kdot_kernel(KrylovArgs A, int with_z, ColGroups G, int ng, int ngroups) {
+__global__ void __launch_bounds__(256) kdot_kernel(KrylovArgs A, int with_z, ColGroups G, int ng, int ngroups,
+                                                   int keep) {
   constexpr int R = rows_per_lane<VT>();
   int rt, zb, cg;
   if (!tile_of<false>(blockIdx.x, A.nb * ngroups, A.nb, A.nrt_dot, rt, zb, cg)) return;
@@ -343,11 +364,13 @@ __global__ void __launch_bounds__(256) kdot_kernel(KrylovArgs A, int with_z, Col
   auto put = [&](int c, int k, double sum) { (k < 2 ? pa : pb)[2 * (off + c) + (k & 1)] = sum; };
   // FP64 Schur columns beside FP32 Krylov columns: half the batch for the same bytes
   constexpr int CS = R == 2 && C > 1 ? C / 2 : C;
+  const VT* V = static_cast<const VT*>(A.V) + (size_t)r * A.vstride;
   if (schur)
-    dot_walk<double2, CS, R>(w, A.S, A.ldq, c0, ng * (C / CS), cend, row0, lane, N, put);
+    dot_walk<double2, CS, R, false>(w, A.S, A.ldq, c0, ng * (C / CS), cend, row0, lane, N, put);
+  else if (rt < A.nrt_dot - keep)
+    dot_walk<VT, C, R, true>(w, V, A.ldq, c0, ng, cend, row0, lane, N, put);
   else
-    dot_walk<VT, C, R>(w, static_cast<const VT*>(A.V) + (size_t)r * A.vstride, A.ldq, c0, ng, cend, row0, lane, N,
-                       put);
+    dot_walk<VT, C, R, false>(w, V, A.ldq, c0, ng, cend, row0, lane, N, put);
 }
 
 // lane's part of raw scalar q (0..3) over the row tiles: tiles lane, lane + 64, ...
@@ -750,17 +773,19 @@ __device__ inline void combine_cols(const QT* __restrict__ base, int cofs, size_
 template <typename QT, int KB, int R>
 struct SweepBuf {
   double2 q[KB][R];
+  template <bool NT>
   __device__ inline void load(const QT* __restrict__ p, int t, int i) {
 #pragma unroll
-    for (int k = 0; k < R; ++k) q[t][k] = p[i + k];
+    for (int k = 0; k < R; ++k) q[t][k] = col_load<NT>(p + i + k);
   }
   __device__ inline double2 at(int t, int k) const { return q[t][k]; }
 };
 template <int KB>
 struct SweepBuf<float2, KB, 2> {
   float4 q[KB];
+  template <bool NT>
   __device__ inline void load(const float2* __restrict__ p, int t, int i) {
-    q[t] = *reinterpret_cast<const float4*>(p + i);
+    q[t] = col_load<NT>(reinterpret_cast<const float4*>(p + i));
   }
   __device__ inline double2 at(int t, int k) const {
     return k ? make_double2((double)q[t].z, (double)q[t].w) : make_double2((double)q[t].x, (double)q[t].y);
@@ -782,7 +807,7 @@ struct Sweep {
   int cofs, c, cend, i;
   __device__ inline void fill(SweepBuf<QT, KB, R>& b, int cb) {
 #pragma unroll
-    for (int t = 0; t < KB; ++t) b.load(base + (size_t)(min(cb + t * NW, cend - 1) - cofs) * ldq, t, i);
+    for (int t = 0; t < KB; ++t) b.template load<false>(base + (size_t)(min(cb + t * NW, cend - 1) - cofs) * ldq, t, i);
   }
   __device__ inline void start() {
     if (c < cend) fill(x, c);
@@ -829,7 +854,7 @@ struct Sweep {
 // reduced coefficients read from memory (c is wavefront-uniform, so they come
 // through scalar loads): one batch of KB column loads and their coefficients
 // at a time, the last, partial batch too
-template <typename QT, int KB, int NW, int R>
+template <typename QT, int KB, int NW, int R, bool NT>
 __device__ inline void sweep_mem(const QT* __restrict__ base, int cofs, size_t ldq, int c, int cend, int i,
                                  const double2* __restrict__ av, const double2* __restrict__ bv, double2 (&sa)[R],
                                  double2 (&sb)[R]) {
@@ -840,7 +865,7 @@ __device__ inline void sweep_mem(const QT* __restrict__ base, int cofs, size_t l
 #pragma unroll
     for (int t = 0; t < KB; ++t) {
       const int cc = c + t * NW, cl = min(cc, cend - 1);
-      q.load(base + (size_t)(cl - cofs) * ldq, t, i);
+      q.template load<NT>(base + (size_t)(cl - cofs) * ldq, t, i);
       ca[t] = av[cl];
       cb[t] = bv[cl];
       if (cc >= cend) ca[t] = cb[t] = zero;
@@ -876,19 +901,19 @@ __device__ inline int first_col(int m, int w) { return m + ((w - m % NW) + NW) %
 // kCoefCap columns in spans of that many); two register sets of KB columns.
 // Else the coefficients are reduced in memory (kred_kernel).
 template <typename VT, int KB, int NW, bool PARTS>
-__global__ void __launch_bounds__(64 * NW, 4) kupdate_kernel(KrylovArgs A, int nh, unsigned nhess) {
+__global__ void __launch_bounds__(64 * NW, 4) kupdate_kernel(KrylovArgs A, int nh, unsigned nhess, int keep) {
   constexpr int NT = 64 * NW;
   constexpr int R = rows_per_lane<VT>();
   constexpr int kSub = kDRows / (64 * R);  // workgroups per row tile
   static_assert(kCoefCap % NT == 0, "spans hold whole rounds of the threads");
   const bool hess = blockIdx.x < nhess;
-  int zb, bb;
+  int zb, bb, rt = 0;
   if (hess) {
     bb = blockIdx.x / A.nb;
     zb = blockIdx.x - bb * A.nb;
     if (bb >= nh) return;
   } else {
-    int rt, sub;
+    int sub;
     if (!tile_of<true>(blockIdx.x - nhess, A.nb * kSub, A.nb, A.nrt_dot, rt, zb, sub)) return;
     bb = rt * kSub + sub;
     if (bb * 64 * R >= A.N) return;
@@ -983,8 +1008,12 @@ __global__ void __launch_bounds__(64 * NW, 4) kupdate_kernel(KrylovArgs A, int n
       scalar_partials<NT>(la, lb, n, s0, s12);
     }
   } else {
-    sweep_mem<double2, KS, NW, R>(A.S, 0, A.ldq, wave, min(J, A.m), il, av, bv, sa, sb);
-    sweep_mem<VT, KB, NW, R>(V, A.m, A.ldq, first_col<NW>(A.m, wave), J, il, av, bv, sa, sb);
+    sweep_mem<double2, KS, NW, R, false>(A.S, 0, A.ldq, wave, min(J, A.m), il, av, bv, sa, sb);
+    const int cv = first_col<NW>(A.m, wave);
+    if (rt >= keep)
+      sweep_mem<VT, KB, NW, R, true>(V, A.m, A.ldq, cv, J, il, av, bv, sa, sb);
+    else
+      sweep_mem<VT, KB, NW, R, false>(V, A.m, A.ldq, cv, J, il, av, bv, sa, sb);
     scalar_partials<NT>(av, bv, J, s0, s12);
   }
 #pragma unroll
@@ -1168,6 +1197,23 @@ static auto update_kernel_for(const KrylovTune& t) {
   return t.uw == 16 ? update_kernel_nw<VT, 16, PARTS>(t.ub) : update_kernel_nw<VT, 8, PARTS>(t.ub);
 }
 
+// Row tiles whose Krylov columns a pass leaves in the caches for the next pass,
+// which walks the other way: the last ones of its walk, as far as they fit
+// beside the Schur columns; the others are streamed past the caches.  us for
+// dot and update of a step, all cached / all streamed / by this rule: 8^4 x 6
+// slots, FP64, 70 columns 126 / 140 / 123, 100 columns 171 / 178 / 166, 200
+// columns 334 / 320 / 316; 12^4, 80 columns 146 / 140 / 133, 300 columns 437 /
+// 391 / 388; 12^4 x 16, FP32, 130 columns 1628 / 1522 / 1515 (the dot pass
+// alone 5.1 -> 5.6 TB/s).  128 or 256 MB instead of 200: within 2 per cent.
+constexpr double kKeepBytes = 200e6;
+template <typename VT>
+static int kept_tiles(const KrylovWork& w, const KrylovArgs& A) {
+  double sm, sk;
+  col_sums(A, sm, sk);
+  const double tile = (double)kDRows * sizeof(VT) * std::max(sk, 1.0);
+  return (int)std::min((double)w.nrt_dot, std::max(0.0, kKeepBytes - 16.0 * A.N * sm) / tile);
+}
+
 // wavefronts that fill the chip in the dot pass by parts
 constexpr size_t kDotWaves = 2048;
 
@@ -1260,7 +1306,7 @@ void krylov_dot(const KrylovWork& w, const KrylovArgs& Ain, bool with_z, bool re
     const size_t nwg = tile_grid((size_t)A.nb * ngroups, w.nrt_dot);
     SGN_REQUIRE(nwg * 256 < (size_t(1) << 32), SGN_EINVAL, "krylov: dot grid too large");
     prof_launch(prof, K_KDOT, bytes, flops, C == 1 ? kdot_kernel<VT, 1> : kdot_kernel<VT, 2>, dim3((unsigned)nwg),
-                dim3(256), 0, s, A, with_z ? 1 : 0, G, batches, ngroups);
+                dim3(256), 0, s, A, with_z ? 1 : 0, G, batches, ngroups, kept_tiles<VT>(w, A));
   }
   if (parts && !reduce) return;
   // partial sums read, a, b written
@@ -1292,11 +1338,11 @@ void krylov_update(const KrylovWork& w, const KrylovArgs& Ain, hipStream_t s, Pr
   // read Q, u, z; write v_J, u' (+ its low-precision copy)
   const double vec = A.N * (16.0 + vb + vb + 16.0 + (A.ulonext ? vb : 0.0));
   const double cols = A.nb * (double)A.m + sk;  // per-slot work counts S for every slot
-  const uint32_t lds =
-      dot_form(w, A) == DotForm::Parts ? (uint32_t)(2 * sizeof(double2)) * (uint32_t)(std::min(Jmax, kCoefCap) + kCoefPad) : 0;
+  const bool parts = dot_form(w, A) == DotForm::Parts;
+  const uint32_t lds = parts ? (uint32_t)(2 * sizeof(double2)) * (uint32_t)(std::min(Jmax, kCoefCap) + kCoefPad) : 0;
   prof_launch(prof, K_KUPDATE, qbytes + A.nb * vec + 32.0 * cols, 16.0 * (double)A.N * cols,
-              dot_form(w, A) == DotForm::Parts ? update_kernel_for<VT, true>(A.tune) : update_kernel_for<VT, false>(A.tune),
-              dim3((unsigned)nwg), dim3(nthr), lds, s, A, nh, nhess);
+              parts ? update_kernel_for<VT, true>(A.tune) : update_kernel_for<VT, false>(A.tune), dim3((unsigned)nwg),
+              dim3(nthr), lds, s, A, nh, nhess, kept_tiles<VT>(w, A));
 }
 
 template <typename VT>

@@ -62,3 +62,24 @@ def test_long_basis_spans(env):
         assert torch.equal(y, Y[0])
     finally:
         sg.sgn_destroy(ctx)
+
+
+@pytest.mark.parametrize("prec,k,nrhs", [("fp64", 40, 4), ("mixed", 60, 5)])
+def test_streamed_tiles(env, prec, k, nrhs):
+    # 12^4: the columns of the batch exceed the caches, so most of their tiles
+    # are streamed; those of one source do not
+    sg, torch = env
+    print("streamed", prec, k, nrhs, flush=True)
+    dims = (12, 12, 12, 12)
+    ctx = sg.sgn_create(synth.random_links(dims, 9), dims, 0.3, M_W)
+    try:
+        if prec == "mixed":
+            sg.sgn_set_precision(ctx, sg.SGN_PREC_MIXED)
+        X = torch.from_numpy(np.stack([synth.gaussian_source(dims, 50 + r) for r in range(nrhs)])).cuda()
+        Y, y = torch.empty_like(X), torch.empty_like(X[0])
+        sg.sgn_apply_batched_fixed(ctx, X, Y, k)
+        for r in (0, nrhs - 1):
+            sg.sgn_apply_fixed(ctx, X[r], y, k)
+            assert torch.equal(y, Y[r]), r
+    finally:
+        sg.sgn_destroy(ctx)
