@@ -573,8 +573,8 @@ static int dense_sign_newton_batched(DenseWork& d, int n, int nb, const double2*
 // this method (their Ritz values have |Im| well below |Re| once the critical
 // eigenvalues are deflated); growth of the small eigenvalues is 3/2 per step,
 // then quadratic.  Each step is two complex products on the matrix cores
-// (zgemm.hip), one launch each for the whole batch, and a per-matrix check
-// of |X^2 - I|_F / sqrt(n) on the device; a matrix stops once it is below
+// (zgemm.hip), one launch each for the whole batch; the second also checks
+// every matrix's |X^2 - I|_F / sqrt(n), and a matrix stops once it is below
 // 1e-7 (the next iterate is then at rounding level), or when it diverges or
 // has not settled within 60 steps (then the caller falls back to Roberts'
 // iteration with Gauss-Jordan inverses, which converges for any matrix
@@ -600,11 +600,14 @@ __global__ void __launch_bounds__(256) colsum_kernel(const double2* __restrict__
 }
 
 // X = A / |A|_1 (the 1-norm as the largest column sum; every workgroup takes
-// the maximum itself), or A / max(radius, |A|_1 / 1.5) for a smaller radius
+// the maximum itself), or A / max(radius, |A|_1 / 1.5) for a smaller radius;
+// also the matrix's first state word
 __global__ void __launch_bounds__(256) scale_by_norm1_kernel(const double2* __restrict__ A, int lda, size_t astride,
                                                              const double* __restrict__ cs, double2* __restrict__ X,
-                                                             int n, size_t nn, double radius) {
+                                                             int n, size_t nn, double radius, int* __restrict__ state,
+                                                             int* __restrict__ iters) {
   const int b = blockIdx.y;
+  if (blockIdx.x == 0 && threadIdx.x == 0) state[b] = iters[b] = 0;
   __shared__ double red[256];
   double mx = 0.0;
   for (int j = threadIdx.x; j < n; j += 256) mx = fmax(mx, cs[(size_t)b * n + j]);
@@ -627,14 +630,6 @@ __global__ void __launch_bounds__(256) scale_by_norm1_kernel(const double2* __re
   X[(size_t)b * nn + e] = cscale(A[(size_t)b * astride + (size_t)j * lda + i], inv);
 }
 
-__global__ void ns_init_kernel(int* state, int* iters, int nb) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b < nb) {
-    state[b] = 0;
-    iters[b] = 0;
-  }
-}
-
 }  // namespace
 
 // C = A B (column-major, complex) on the matrix cores
@@ -655,8 +650,8 @@ static void ns_reserve(DenseWork& d, int n, int nb) {
   if (d.nstate < nb) {
     if (d.ns_state) (void)hipFree(d.ns_state);
     if (d.host_state) (void)hipHostFree(d.host_state);
-    SGN_HIP(hipMalloc(&d.ns_state, sizeof(int) * 2 * (size_t)nb));
-    SGN_HIP(hipHostMalloc(&d.host_state, sizeof(int) * 2 * (size_t)nb, hipHostMallocDefault));
+    SGN_HIP(hipMalloc(&d.ns_state, sizeof(int) * 3 * (size_t)nb));
+    SGN_HIP(hipHostMalloc(&d.host_state, sizeof(int) * 3 * (size_t)nb, hipHostMallocDefault));
     d.nstate = nb;
   }
 }
@@ -671,53 +666,51 @@ static int dense_sign_ns_batched(DenseWork& d, int n, int nb, const double2* A, 
   dense_alloc(d, n, nb);
   const size_t nn = (size_t)n * n;
   ns_reserve(d, n, nb);
-  int* state = d.ns_state;
-  int* iters = d.ns_state + nb;
+  // the state words of odd and even iterations, and the final iterations
+  int* states[2] = {d.ns_state, d.ns_state + nb};
+  int* iters = d.ns_state + 2 * nb;
   // the column sums use the partial-sum buffer (sized above for both uses)
   hipLaunchKernelGGL(colsum_kernel, dim3((n + 3) / 4, nb), dim3(256), 0, s, A, lda, astride, d.spart, n);
   SGN_HIP(hipGetLastError());
   hipLaunchKernelGGL(scale_by_norm1_kernel, dim3((unsigned)((nn + 255) / 256), nb), dim3(256), 0, s, A, lda, astride,
-                     d.spart, d.S, n, nn, radius);
-  SGN_HIP(hipGetLastError());
-  hipLaunchKernelGGL(ns_init_kernel, dim3((nb + 63) / 64), dim3(64), 0, s, state, iters, nb);
+                     d.spart, d.S, n, nn, radius, states[0], iters);
   SGN_HIP(hipGetLastError());
   double2* X = d.S;
   double2* Y = d.Ma;
   double2* Xn = d.Mb;
-  const int nparts = zgemm_ns_parts(n, nb);
   const int maxit = 60;
   const int first_look = std::max(6, std::min(d.last_iters, maxit));
+  const int* host = d.host_state;  // the states after the last iteration
   int it = 0;
   for (it = 1; it <= maxit; ++it) {
+    const int* state = states[(it + 1) & 1];
+    int* next = states[it & 1];
     int idx = prof ? prof->begin(K_NS_GEMM) : -1;
     zgemm_ns_square(n, X, Y, nn, nb, state, d.spart, s);
     if (prof) prof->end(idx, 0.0, 0.0, 0);
-    ns_check(d.spart, nparts, n, state, iters, it, maxit, nb, s);
     idx = prof ? prof->begin(K_NS_GEMM) : -1;
-    zgemm_ns_update(n, X, Y, Xn, nn, nb, state, F, ldf, fstride, s);
+    zgemm_ns_update(n, X, Y, Xn, nn, nb, state, next, iters, d.spart, it, maxit, F, ldf, fstride, s);
     if (prof) prof->end(idx, 0.0, 0.0, 0);
     std::swap(X, Xn);
     if (it >= first_look && ((it - first_look) % 2 == 0 || it == maxit)) {
-      SGN_HIP(hipMemcpyAsync(d.host_state, state, sizeof(int) * 2 * (size_t)nb, hipMemcpyDeviceToHost, s));
+      SGN_HIP(hipMemcpyAsync(d.host_state, d.ns_state, sizeof(int) * 3 * (size_t)nb, hipMemcpyDeviceToHost, s));
       SGN_HIP(hipStreamSynchronize(s));
+      host = d.host_state + (it & 1) * nb;
       bool all = true;
-      for (int b = 0; b < nb; ++b) all = all && d.host_state[b] != 0;
+      for (int b = 0; b < nb; ++b) all = all && host[b] != 0;
       if (all) break;
     }
   }
   it = std::min(it, maxit);
-  // a final read (the loop may have ended at maxit without one)
-  SGN_HIP(hipMemcpyAsync(d.host_state, state, sizeof(int) * 2 * (size_t)nb, hipMemcpyDeviceToHost, s));
-  SGN_HIP(hipStreamSynchronize(s));
   done = 0;
   int most = 0;
   double gemm_matrices = 0.0;  // matrix products that did work
   for (int b = 0; b < nb; ++b) {
-    const int st = d.host_state[b];
+    const int st = host[b];
     if (st == 1 || st == 2) {
       done |= 1ull << b;
-      most = std::max(most, d.host_state[nb + b]);
-      gemm_matrices += 2.0 * d.host_state[nb + b];
+      most = std::max(most, d.host_state[2 * nb + b]);
+      gemm_matrices += 2.0 * d.host_state[2 * nb + b];
     } else {
       gemm_matrices += 2.0 * it;
     }

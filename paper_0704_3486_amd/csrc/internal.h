@@ -266,7 +266,7 @@ struct DenseWork {
   int method = 0;         // 0: Newton-Schulz with Roberts/Gauss-Jordan fallback; 1: Roberts only
   double* spart = nullptr;  // Newton-Schulz residual partials
   size_t nspart = 0;
-  int* ns_state = nullptr;  // Newton-Schulz per-matrix state [nb] and iterations [nb]
+  int* ns_state = nullptr;  // Newton-Schulz per matrix: two state words in turn [2][nb], iterations [nb]
   int* host_state = nullptr;  // pinned mirror
   int nstate = 0;
   int last_iters = 0;       // iterations the previous call needed (when the host first looks)
@@ -347,11 +347,11 @@ void zgemm(int M, int N, int K, double alpha, const double2* A, int lda, size_t 
 // skipped for matrices whose state is not 0
 void zgemm_ns_square(int n, const double2* X, double2* Y, size_t stride, int nb, const int* state, double* part,
                      hipStream_t s);
-// Xn = X Y / 2, also into F_b (ld ldf, stride fstride) where state == 1;
-// skipped where state > 1
+// iteration `it` of at most maxit: from the partials of the squaring, the state
+// after it into next (another array than state; iters for a matrix that is
+// final, state 1), Xn = X Y / 2 unless that state is 3, and into F_b (ld ldf,
+// stride fstride) where it is 1; matrices whose state is not 0 are skipped
 void zgemm_ns_update(int n, const double2* X, const double2* Y, double2* Xn, size_t stride, int nb, const int* state,
-                     double2* F, int ldf, size_t fstride, hipStream_t s);
+                     int* next, int* iters, double* part, int it, int maxit, double2* F, int ldf, size_t fstride,
+                     hipStream_t s);
 int zgemm_ns_parts(int n, int nb);
-// per matrix: residual from the partials and the state transition of iteration it
-void ns_check(const double* part, int nparts, int n, int* state, int* iters, int it, int maxit, int nb,
-              hipStream_t s);

@@ -22,12 +22,17 @@
 // Two epilogues serve the inverse-free Newton-Schulz iteration of the
 // small-matrix sign (step (v)), X <- X (3I - X^2) / 2:
 //   * NS_SQUARE: P = X X, writes Y = 3I - P and, per wavefront, the partial
-//     sum of |P - I|^2 (summed in a fixed order by ns_check_kernel);
+//     sum of |P - I|^2 (summed in a fixed order by the update);
 //   * NS_UPDATE: X' = X Y / 2, also into the caller's output F for a matrix
 //     whose iteration has just met its stopping test.
 // A per-matrix state word (0 running, 1 final, 2 done, 3 stopped unconverged)
 // lets finished matrices skip later launches, so the host looks at the
-// states only every few iterations.
+// states only every few iterations.  The update launch makes the stopping
+// test itself: every workgroup sums the partials (a few hundred doubles, loaded
+// with its first operands) in the same order, and one writes the state word
+// that the next iteration's launches read (two words in turn: this launch's
+// workgroups all read the other one).  A launch of its own for the test took
+// 2.6 us (one matrix) to 4.6 (eight) and a launch gap.
 #include "internal.h"
 
 typedef double v4d __attribute__((ext_vector_type(4)));
@@ -45,6 +50,7 @@ enum { ZG_PLAIN = 0, ZG_NS_SQUARE = 1, ZG_NS_UPDATE = 2 };
 
 struct ZgArgs {
   int M, N, K;
+  int gx, gy, nb;  // split-k launches: tiles of columns and of rows, matrices
   double alpha;
   const double2* A;
   int lda;
@@ -56,8 +62,11 @@ struct ZgArgs {
   int ldc;
   size_t cstride;
   const int* state;  // NS modes: per matrix
-  double* part;      // NS_SQUARE: per matrix, nparts partial sums of |P - I|^2
+  double* part;      // NS modes: per matrix, nparts partial sums of |P - I|^2
   int nparts;
+  int* next;         // NS_UPDATE: the next iteration's state words
+  int* iters;        // NS_UPDATE: per matrix, the iteration that was final
+  int it, maxit;     // NS_UPDATE: this iteration, the last one
   double2* F;        // NS_UPDATE: output of a final matrix
   int ldf;
   size_t fstride;
@@ -141,13 +150,12 @@ __device__ inline void finish3(v4d (&re)[TM][TN], v4d (&im)[TM][TN], const v4d (
     }
 }
 
-// The k-steps with NF - 1 in flight ahead of the one being multiplied (NF =
-// 3, or 2 where the register count would otherwise cost occupancy); the loop
-// body is unrolled NF times so the fragments rotate through NF register sets
-// without copies (a copy of a just-loaded register would wait for the load).
-// Steps past K multiply zeros, which leaves the sums unchanged; the k-steps
-// are multiplied in the same order for either NF.
-template <int TM, int TN, bool G3, int NF = 3>
+// The k-steps with NF - 1 in flight ahead of the one being multiplied; the
+// loop body is unrolled NF times so the fragments rotate through NF register
+// sets without copies (a copy of a just-loaded register would wait for the
+// load).  Steps past K multiply zeros, which leaves the sums unchanged; the
+// k-steps are multiplied in the same order for any NF.
+template <int TM, int TN, bool G3, int NF>
 __device__ inline void kloop(const ZgArgs& g, const double2* __restrict__ A, const double2* __restrict__ B,
                              const int* ar, const bool* aok, const int* bc, const bool* bok, int lk, int first,
                              int stride, v4d (&re)[TM][TN], v4d (&im)[TM][TN], v4d (&tx)[TM][TN]) {
@@ -169,37 +177,51 @@ __device__ inline void kloop(const ZgArgs& g, const double2* __restrict__ A, con
     w.pb[b] = B + (size_t)bc[b] * g.ldb + (4 * first + lk);
     w.bok[b] = bok[b];
   }
-  static_assert(NF == 2 || NF == 3, "two or three fragment sets");
-  if constexpr (NF == 3) {
-    Frag<TM, TN> f0, f1, f2;
-    w.load(f0);
+  Frag<TM, TN> f[NF];
+#pragma unroll
+  for (int i = 0; i < NF - 1; ++i) {
+    w.load(f[i]);
     w.advance();
-    w.load(f1);
-    w.advance();
-    for (int st = first; st < S; st += 3 * stride) {
-      w.load(f2);
+  }
+  for (int st = first; st < S; st += NF * stride) {
+#pragma unroll
+    for (int i = 0; i < NF; ++i) {
+      w.load(f[(i + NF - 1) % NF]);
       w.advance();
-      mma<TM, TN, G3>(f0, re, im, tx);
-      w.load(f0);
-      w.advance();
-      mma<TM, TN, G3>(f1, re, im, tx);
-      w.load(f1);
-      w.advance();
-      mma<TM, TN, G3>(f2, re, im, tx);
-    }
-  } else {
-    Frag<TM, TN> f0, f1;
-    w.load(f0);
-    w.advance();
-    for (int st = first; st < S; st += 2 * stride) {
-      w.load(f1);
-      w.advance();
-      mma<TM, TN, G3>(f0, re, im, tx);
-      w.load(f0);
-      w.advance();
-      mma<TM, TN, G3>(f1, re, im, tx);
+      mma<TM, TN, G3>(f[i], re, im, tx);
     }
   }
+}
+
+// the stopping test of an iteration: this thread's part of the sum of |P - I|^2
+__device__ inline double ns_part(const ZgArgs& g, int bz) {
+  double s = 0.0;
+  for (int t = threadIdx.x; t < g.nparts; t += 256) s += g.part[(size_t)bz * g.nparts + t];
+  return s;
+}
+// and the state after it, from every thread's part in LDS (written before a
+// barrier): r = sqrt(sum / n) in a fixed order; wavefront-uniform
+__device__ inline int ns_next(const ZgArgs& g, const double* red) {
+  const int lane = threadIdx.x & 63;
+  double v = (red[lane] + red[lane + 128]) + (red[lane + 64] + red[lane + 192]);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+  const double r = sqrt(__shfl(v, 0, 64) / g.M);  // |X^2 - I|_F / sqrt(n) of the iterate before this update
+  int st = 0;
+  if (!isfinite(r) || r > 1e3)
+    st = 3;  // diverging: left for the fallback
+  else if (r < 1e-7)
+    st = 1;  // the error after this update ~ (3/2) (r/2)^2 < 1e-14
+  else if (g.it >= g.maxit)
+    st = 3;
+  return __builtin_amdgcn_readfirstlane(st);
+}
+// the state word for the next iteration, by one thread of the matrix's first
+// workgroup
+__device__ inline void ns_write(const ZgArgs& g, int bz, bool first, int st) {
+  if (threadIdx.x != 0 || !first) return;
+  g.next[bz] = st;
+  if (st == 1) g.iters[bz] = g.it;
 }
 
 // epilogue of one 16 x 16 block (item r of a lane holds row lk + 4 r of
@@ -234,8 +256,17 @@ __device__ inline double store_block(const ZgArgs& g, double2* __restrict__ C, i
 template <int TM, int TN, int MODE>
 __global__ void __launch_bounds__(256) zgemm_kernel(ZgArgs g) {
   const int bz = blockIdx.z;
+  const bool first = blockIdx.x == 0 && blockIdx.y == 0;
   if (MODE == ZG_NS_SQUARE && g.state[bz] != 0) return;
-  if (MODE == ZG_NS_UPDATE && g.state[bz] > 1) return;
+  double stop = 0.0;
+  if (MODE == ZG_NS_UPDATE) {
+    const int st = g.state[bz];
+    if (st != 0) {
+      ns_write(g, bz, first, st == 1 ? 2 : st);
+      return;
+    }
+    stop = ns_part(g, bz);
+  }
   const double2* __restrict__ A = g.A + (size_t)bz * g.astride;
   const double2* __restrict__ B = g.B + (size_t)bz * g.bstride;
   double2* __restrict__ C = g.C + (size_t)bz * g.cstride;
@@ -269,11 +300,20 @@ __global__ void __launch_bounds__(256) zgemm_kernel(ZgArgs g) {
     bok[b] = j < g.N;
     bc[b] = min(j, g.N - 1);
   }
-  kloop<TM, TN, G3>(g, A, B, ar, aok, bc, bok, lk, 0, 1, re, im, tx);
+  kloop<TM, TN, G3, 3>(g, A, B, ar, aok, bc, bok, lk, 0, 1, re, im, tx);
   if constexpr (G3) finish3<TM, TN>(re, im, tx);
 
   double psum = 0.0;
-  const bool final_out = MODE == ZG_NS_UPDATE && g.state[bz] == 1;
+  bool final_out = false;
+  if (MODE == ZG_NS_UPDATE) {
+    __shared__ double sred[256];
+    sred[threadIdx.x] = stop;
+    __syncthreads();
+    const int st = ns_next(g, sred);
+    ns_write(g, bz, first, st);
+    if (st > 1) return;
+    final_out = st == 1;
+  }
 #pragma unroll
   for (int a = 0; a < TM; ++a)
 #pragma unroll
@@ -293,18 +333,37 @@ __global__ void __launch_bounds__(256) zgemm_kernel(ZgArgs g) {
 // wavefront; T = 2 shares each operand fragment between two blocks (half
 // the loads per matrix-core instruction).  Every entry's sum runs over the
 // same k-steps in the same order for either T.
+//
+// A product's operands come from the launch before it, on other XCDs, so each
+// XCD's L2 fetches what its workgroups read: with the tiles dealt out in turn,
+// nearly both whole matrices.  A launch of a multiple of eight matrices
+// therefore gives each XCD whole matrices (eight of 341: 98 us an iteration
+// instead of 106, of 130: 16.3 instead of 18.4).  A quarter of the rows by half
+// of the columns per XCD in the other launches was slower (six of 260: 59 us
+// instead of 46): the XCDs' shares are too uneven.
 template <int MODE, int T>
 __global__ void __launch_bounds__(256) zgemm_splitk_kernel(ZgArgs g) {
-  const int bz = blockIdx.z;
+  const int per = g.gx * g.gy, xcds = g.nb % 8 == 0 ? 8 : 1;
+  const int x = blockIdx.x % xcds, l = blockIdx.x / xcds, q = l / per, t = l - q * per;
+  const int bz = q * xcds + x, by = t / g.gx, bx = t - by * g.gx;
+  const bool first = bx == 0 && by == 0;
   if (MODE == ZG_NS_SQUARE && g.state[bz] != 0) return;
-  if (MODE == ZG_NS_UPDATE && g.state[bz] > 1) return;
+  double stop = 0.0;
+  if (MODE == ZG_NS_UPDATE) {
+    const int st = g.state[bz];
+    if (st != 0) {
+      ns_write(g, bz, first, st == 1 ? 2 : st);
+      return;
+    }
+    stop = ns_part(g, bz);
+  }
   const double2* __restrict__ A = g.A + (size_t)bz * g.astride;
   const double2* __restrict__ B = g.B + (size_t)bz * g.bstride;
   double2* __restrict__ C = g.C + (size_t)bz * g.cstride;
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: scalar loop control
   const int li = lane & 15, lk = lane >> 4;
-  const int i0 = blockIdx.y * 16 * T, j0 = blockIdx.x * 16 * T;
+  const int i0 = by * 16 * T, j0 = bx * 16 * T;
 
   constexpr bool G3 = MODE != ZG_PLAIN;
   v4d re[T][T], im[T][T], tx[T][T];
@@ -343,9 +402,17 @@ __global__ void __launch_bounds__(256) zgemm_splitk_kernel(ZgArgs g) {
           red[w - 1][a * T + b][4 + r][lane] = im[a][b][r];
         }
   }
+  __shared__ double sred[256];
+  if (MODE == ZG_NS_UPDATE) sred[threadIdx.x] = stop;
   __syncthreads();
   if (w != 0) return;
-  const bool final_out = MODE == ZG_NS_UPDATE && g.state[bz] == 1;
+  bool final_out = false;
+  if (MODE == ZG_NS_UPDATE) {
+    const int st = ns_next(g, sred);
+    ns_write(g, bz, first, st);
+    if (st > 1) return;
+    final_out = st == 1;
+  }
   // |P - I|^2 partials per 16 x 16 block (row-major over the blocks), the
   // same set for either T
   const int nbx = (g.N + 15) / 16;
@@ -362,47 +429,12 @@ __global__ void __launch_bounds__(256) zgemm_splitk_kernel(ZgArgs g) {
         }
       double psum = store_block<MODE>(g, C, bz, i0 + 16 * a, j0 + 16 * b + li, lk, re[a][b], im[a][b], final_out);
       if (MODE == ZG_NS_SQUARE) {
-        const int by = blockIdx.y * T + a, bx = blockIdx.x * T + b;
+        const int py = by * T + a, px = bx * T + b;
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) psum += __shfl_xor(psum, off, 64);
-        if (lane == 0 && by * 16 < g.M && bx * 16 < g.N) g.part[(size_t)bz * g.nparts + (size_t)by * nbx + bx] = psum;
+        if (lane == 0 && py * 16 < g.M && px * 16 < g.N) g.part[(size_t)bz * g.nparts + (size_t)py * nbx + px] = psum;
       }
     }
-}
-
-// per matrix: r = sqrt(sum |P - I|^2 / n) in a fixed order, then the state
-// transition of iteration `it` (see the file comment)
-__global__ void __launch_bounds__(256) ns_check_kernel(const double* __restrict__ part, int nparts, int n,
-                                                       int* __restrict__ state, int* __restrict__ iters, int it,
-                                                       int maxit) {
-  const int b = blockIdx.x, tid = threadIdx.x;
-  const int st = state[b];
-  __shared__ double red[256];
-  if (st == 1) {
-    if (tid == 0) state[b] = 2;
-    return;
-  }
-  if (st != 0) return;
-  double s = 0.0;
-  for (int t = tid; t < nparts; t += 256) s += part[(size_t)b * nparts + t];
-  red[tid] = s;
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if (tid < off) red[tid] += red[tid + off];
-    __syncthreads();
-  }
-  if (tid == 0) {
-    const double r = sqrt(red[0] / n);  // |X^2 - I|_F / sqrt(n) of the iterate before this update
-    if (!isfinite(r) || r > 1e3) {
-      state[b] = 3;  // diverging: left for the fallback
-    } else if (r < 1e-7) {
-      // the error after this update ~ (3/2) (r/2)^2 < 1e-14
-      state[b] = 1;
-      iters[b] = it;
-    } else if (it >= maxit) {
-      state[b] = 3;
-    }
-  }
 }
 
 template <int TM, int TN, int MODE>
@@ -415,10 +447,13 @@ void launch(const ZgArgs& g, int nb, hipStream_t s) {
 }
 
 template <int MODE, int T>
-void launch_splitk(const ZgArgs& g, int nb, hipStream_t s) {
-  const int gx = (g.N + 16 * T - 1) / (16 * T), gy = (g.M + 16 * T - 1) / (16 * T);
-  SGN_REQUIRE(gy <= 65535 && nb <= 65535, SGN_EINVAL, "zgemm: grid too large");
-  hipLaunchKernelGGL((zgemm_splitk_kernel<MODE, T>), dim3(gx, gy, nb), dim3(256), 0, s, g);
+void launch_splitk(ZgArgs g, int nb, hipStream_t s) {
+  g.gx = (g.N + 16 * T - 1) / (16 * T);
+  g.gy = (g.M + 16 * T - 1) / (16 * T);
+  g.nb = nb;
+  const size_t nwg = (size_t)g.gx * g.gy * nb;
+  SGN_REQUIRE(nwg * 256 < (size_t(1) << 32), SGN_EINVAL, "zgemm: grid too large");
+  hipLaunchKernelGGL((zgemm_splitk_kernel<MODE, T>), dim3((unsigned)nwg), dim3(256), 0, s, g);
   SGN_HIP(hipGetLastError());
 }
 
@@ -508,7 +543,8 @@ void zgemm_ns_square(int n, const double2* X, double2* Y, size_t stride, int nb,
 }
 
 void zgemm_ns_update(int n, const double2* X, const double2* Y, double2* Xn, size_t stride, int nb, const int* state,
-                     double2* F, int ldf, size_t fstride, hipStream_t s) {
+                     int* next, int* iters, double* part, int it, int maxit, double2* F, int ldf, size_t fstride,
+                     hipStream_t s) {
   ZgArgs g{};
   g.M = g.N = g.K = n;
   g.alpha = 0.5;
@@ -518,14 +554,14 @@ void zgemm_ns_update(int n, const double2* X, const double2* Y, double2* Xn, siz
   g.astride = g.bstride = g.cstride = stride;
   g.C = Xn;
   g.state = state;
+  g.next = next;
+  g.iters = iters;
+  g.part = part;
+  g.nparts = zgemm_ns_parts(n, nb);
+  g.it = it;
+  g.maxit = maxit;
   g.F = F;
   g.ldf = ldf;
   g.fstride = fstride;
   launch_auto<ZG_NS_UPDATE>(g, nb, s);
-}
-
-void ns_check(const double* part, int nparts, int n, int* state, int* iters, int it, int maxit, int nb,
-              hipStream_t s) {
-  hipLaunchKernelGGL(ns_check_kernel, dim3(nb), dim3(256), 0, s, part, nparts, n, state, iters, it, maxit);
-  SGN_HIP(hipGetLastError());
 }
