@@ -1222,11 +1222,25 @@ void block_step(const BlockSpan& sp, BlockWork& b, const Lattice& lat, const dou
   SlotMap map;
   map.n = nb;
   for (int z = 0; z < nb; ++z) map.slot[z] = sp.act[z];
-  wilson_apply_cheb_slots(lat, links, w0, sp.vstride, b.W, b.wstride, nullptr, 0, 1.0 / e, 0.0, map, s, prof);
-  for (int i = 1; i < sb; ++i)
-    wilson_apply_cheb_slots(lat, links, b.W + (size_t)(i - 1) * ldq, b.wstride, b.W + (size_t)i * ldq, b.wstride,
-                            i == 1 ? w0 : b.W + (size_t)(i - 2) * ldq, i == 1 ? sp.vstride : b.wstride, 2.0 / e,
-                            -1.0, map, s, prof);
+  struct Dir {
+    double2* p;
+    size_t stride;
+  };
+  auto dir = [&](int i) {  // W_i
+    return i == 0 ? Dir{const_cast<double2*>(w0), sp.vstride} : Dir{b.W + (size_t)(i - 1) * ldq, b.wstride};
+  };
+  const bool pairs = wilson_pairs(lat, nb);
+  for (int i = 1; i <= sb; ++i) {
+    const Dir in = dir(i - 1), out = dir(i), pv = i > 1 ? dir(i - 2) : Dir{nullptr, 0};
+    const double ca = (i == 1 ? 1.0 : 2.0) / e, cb = i == 1 ? 0.0 : -1.0;
+    if (pairs && i < sb) {
+      const Dir next = dir(++i);
+      wilson_apply_cheb_pair(lat, links, in.p, in.stride, out.p, out.stride, next.p, next.stride, pv.p, pv.stride, ca,
+                             cb, 2.0 / e, -1.0, map, s, prof);
+    } else {
+      wilson_apply_cheb_slots(lat, links, in.p, in.stride, out.p, out.stride, pv.p, pv.stride, ca, cb, map, s, prof);
+    }
+  }
   int rpw = 0;
   const int nch = nchunks_for(N, rpw);
   // more than 8 block vectors: the products in their three-multiplication form

@@ -255,9 +255,19 @@ void wilson_apply_cheb_slots(const Lattice& lat, const double2* links, const dou
                              double2* out, size_t ostride, const double2* prev, size_t pstride, double ca, double cb,
                              const SlotMap& map, hipStream_t s, Profiler* prof);
 
+// Two steps of a three-term recurrence, slot by slot: Mid = ca1 H_w In + cb1
+// Prev (prev null: without it), Out = ca2 H_w Mid + cb2 In, in one launch; for
+// the lattices and slot counts of wilson_pairs.  The results are those of two
+// wilson_apply_cheb_slots.  Mid and Out are none of the other vectors.
+bool wilson_pairs(const Lattice& lat, int slots);
+void wilson_apply_cheb_pair(const Lattice& lat, const double2* links, const double2* in, size_t istride, double2* mid,
+                            size_t mstride, double2* out, size_t ostride, const double2* prev, size_t pstride,
+                            double ca1, double cb1, double ca2, double cb2, const SlotMap& map, hipStream_t s,
+                            Profiler* prof);
+
 // out = a (H_w^2 y - c y) - b yp (yp null: without it), a step of the
-// Chebyshev recurrence on (H_w^2 - c) / e; tmp takes H_w y.  out
-// is none of the other vectors.
+// Chebyshev recurrence on (H_w^2 - c) / e; tmp is scratch
+// (H_w y, where it takes two launches).  out is none of the other vectors.
 void wilson_apply_square(const Lattice& lat, const double2* links, const double2* y, double2* tmp, double2* out,
                          double a, double c, double b, const double2* yp, hipStream_t s, Profiler* prof);
 

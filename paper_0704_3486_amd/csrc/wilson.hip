@@ -392,6 +392,148 @@ wilson_hw_dir_kernel(const C* __restrict__ links, const C* __restrict__ in, size
   }
 }
 
+// Two applications in one launch, for lattices that leave most of the chip
+// idle.  A launch of theirs is little more than the launch itself (2.45 us of
+// the 3.7 that one application of 4^3 x 6 sites takes), so a workgroup owns
+// four sites and nine wavefronts: wavefront 0 applies H_w at the sites
+// themselves, wavefront 1 + 2 nu + d at their neighbours along +-nu (d = 0, 1),
+// which makes the first application nine times over, and after one exchange
+// through LDS wavefront 0 applies H_w again.  Lane = site (4) x direction (4) x
+// hop (forward, backward) x colour vector of the half spinor (2).  Every sum
+// has the operations and the order of wilson_hw_dir_kernel.
+//   SQUARE: M = H_w In, Out = ca2 (H_w M + cb2 In) + cc Prev (M not written);
+//   else:   Mid = ca1 H_w In + cb1 Prev, Out = ca2 H_w Mid + cb2 In;
+// prev null: without its term.  One launch / two, us back to back: 4^4 4.6 /
+// 6.4, 4^3 x 6 two slots 4.8 / 6.5.
+template <bool SQUARE>
+__global__ void __launch_bounds__(576)
+wilson_pair_kernel(const double2* __restrict__ links, const double2* __restrict__ in, size_t istride,
+                   double2* __restrict__ mid, size_t mstride, double2* __restrict__ out, size_t ostride,
+                   const double2* __restrict__ prev, size_t pstride, Geom g, SlotMap map, double ca1, double cb1,
+                   double ca2, double cb2, double cc) {
+  using C = double2;
+  __shared__ C chis[9][8][6][4];  // [wavefront][2 nu + hop][3 su + colour][site]
+  __shared__ C mids[9][12][4];    // [wavefront][component][site]
+  const int V = g.V;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int site = lane & 3, nu = (lane >> 2) & 3, hop = (lane >> 4) & 1, su = lane >> 5;
+  const bool fwd = hop == 0;
+  const int slot = map.slot[blockIdx.y];
+  const int n0 = 4 * xcd_block(blockIdx.x, g.nblk) + site;
+  const bool own = n0 < V;
+  int n = own ? n0 : V - 1;  // lanes past the lattice work on a valid site, never written out
+  int c0, c1, c2, c3;
+  {
+    const int q1 = g.div[1].div(n), q2 = g.div[2].div(n), q3 = g.div[3].div(n);
+    c0 = n - q1 * g.L[0];
+    c1 = q1 - q2 * g.L[1];
+    c2 = q2 - q3 * g.L[2];
+    c3 = q3;
+  }
+  // this wavefront's site: the own one, or its neighbour (periodic wrap)
+  if (wave > 0) {
+    const int d = (wave - 1) >> 1, step = (wave - 1) & 1 ? -1 : 1, L = g.L[d];
+    const int c = d == 0 ? c0 : d == 1 ? c1 : d == 2 ? c2 : c3;
+    const int cn = c + step < 0 ? L - 1 : c + step == L ? 0 : c + step;
+    n += (cn - c) * g.stride[d];
+    if (d == 0) c0 = cn;
+    if (d == 1) c1 = cn;
+    if (d == 2) c2 = cn;
+    if (d == 3) c3 = cn;
+  }
+  const C* __restrict__ v = in + (size_t)slot * istride;
+  const int coord = nu == 0 ? c0 : nu == 1 ? c1 : nu == 2 ? c2 : c3;
+  const int L = nu == 0 ? g.L[0] : nu == 1 ? g.L[1] : nu == 2 ? g.L[2] : g.L[3];
+  const int stride = nu == 0 ? 1 : nu == 1 ? g.stride[1] : nu == 2 ? g.stride[2] : g.stride[3];
+  const bool wrap = coord == (fwd ? L - 1 : 0);
+  const int m = n + (fwd ? stride : -stride) * (wrap ? 1 - L : 1);
+  const SpinProj P = spin_proj(nu, su);
+  C pu[3], pl[3], u[9];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    pu[c] = v[(size_t)(3 * su + c) * V + m];
+    pl[c] = v[(size_t)(3 * P.partner + c) * V + m];
+  }
+  load_link<C>(links, V, nu, fwd ? n : m, u);
+  // component lane / 4 of site lane % 4 (lanes below 48), for both sums
+  const bool ok = lane < 48;
+  const int comp = ok ? lane >> 2 : 0;
+  const C self = v[(size_t)comp * V + n];
+  C pv = mk<C>(0, 0);
+  if (prev && (!SQUARE || wave == 0)) pv = prev[(size_t)slot * pstride + (size_t)comp * V + n];
+  const double sg = fwd ? 1.0 : -1.0;
+  C w9[9];
+#pragma unroll
+  for (int r = 0; r < 3; ++r)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const C a = u[3 * r + c], b = u[3 * c + r];
+      w9[3 * r + c] = mk<C>(fwd ? a.x : b.x, fwd ? a.y : -b.y);
+    }
+  const double phase = nu == 3 ? (fwd ? g.emu : g.emmu) * (wrap ? -1.0 : 1.0) : 1.0;
+  const double ar = sg * P.ar, ai = sg * P.ai;
+  // this lane's colour vector of its hop into chis[w]
+  auto hop_product = [&](const C (&x)[3], const C (&y)[3], int w) {
+    C hv[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      hv[c] = mk<C>(fma(ar, y[c].x, fma(-ai, y[c].y, x[c].x)), fma(ar, y[c].y, fma(ai, y[c].x, x[c].y)));
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      C s0 = mk<C>(0, 0);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) s0 = tfma(w9[3 * r + c], hv[c], s0);
+      chis[w][2 * nu + hop][3 * su + r][site] = tscale(s0, phase);
+    }
+  };
+  // gamma5 (psi - kappa hops) of this lane's component
+  auto apply = [&](C psi, int w) {
+    const int i = comp / 3, c = comp - 3 * i;
+    C acc = mk<C>(0, 0);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int s1 = i < 2 ? i : (k < 2 ? 3 - i : i - 2);  // the colour vector behind spin i
+      const C f = chis[w][2 * k][3 * s1 + c][site], b = chis[w][2 * k + 1][3 * s1 + c][site];
+      const SpinProj Q = spin_proj(k, s1);
+      const double br = Q.br, bi = Q.bi;
+      const C d = tsub(f, b), up = tadd(f, b), low = mk<C>(br * d.x - bi * d.y, br * d.y + bi * d.x);
+      acc = tadd(acc, mk<C>(i < 2 ? up.x : low.x, i < 2 ? up.y : low.y));
+    }
+    return tscale(tsub(psi, tscale(acc, g.kappa)), comp < 6 ? 1.0 : -1.0);
+  };
+  hop_product(pu, pl, wave);
+  __syncthreads();
+  if (ok) {
+    C val = apply(self, wave);
+    if constexpr (!SQUARE) {
+      val = tscale(val, ca1);
+      if (prev) val = tadd(val, tscale(pv, cb1));
+      if (wave == 0 && own) mid[(size_t)slot * mstride + (size_t)comp * V + n] = val;
+    }
+    mids[wave][comp][site] = val;
+  }
+  __syncthreads();
+  if (wave == 0) {
+    const int w = 1 + 2 * nu + hop;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      pu[c] = mids[w][3 * su + c][site];
+      pl[c] = mids[w][3 * P.partner + c][site];
+    }
+    hop_product(pu, pl, 0);
+  }
+  __syncthreads();
+  if (wave > 0 || !ok || !own) return;
+  C val = apply(mids[0][comp][site], 0);
+  if constexpr (SQUARE) {
+    val = mk<C>(ca2 * fma(cb2, self.x, val.x), ca2 * fma(cb2, self.y, val.y));
+    if (prev) val = mk<C>(fma(cc, pv.x, val.x), fma(cc, pv.y, val.y));
+  } else {
+    val = tadd(tscale(val, ca2), tscale(self, cb2));
+  }
+  out[(size_t)slot * ostride + (size_t)comp * V + n] = val;
+}
+
 __global__ void links_to_f32_kernel(const double2* __restrict__ a, float2* __restrict__ b, size_t n) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) b[i] = make_float2((float)a[i].x, (float)a[i].y);
@@ -639,6 +781,35 @@ void wilson_apply_abi(const Lattice& lat, const double2* links, const double2* x
                                      48.0 * 16.0 * lat.V, s, prof);
 }
 
+// Lattices and slots whose pairs of applications take one launch: those with
+// one of its workgroups (four sites) per CU or less.  A second one on a CU
+// costs more than the launch saved: 4^4 x 4 slots, 256 workgroups, 4.9 us (two
+// launches 6.5), 6^4, 324, 7.7 us (6.5).
+constexpr long long kPairWgs = 256;
+bool wilson_pairs(const Lattice& lat, int slots) { return (long long)((lat.V + 3) / 4) * slots <= kPairWgs; }
+
+template <bool SQUARE>
+static void pair_launch(const Lattice& lat, const double2* links, const double2* in, size_t istride, double2* mid,
+                        size_t mstride, double2* out, size_t ostride, const double2* prev, size_t pstride,
+                        const SlotMap& map, double ca1, double cb1, double ca2, double cb2, double cc, hipStream_t s,
+                        Profiler* prof) {
+  const int nblk = (lat.V + 3) / 4;
+  // per site: the links once, per slot read the input and prev, write the results
+  const double bytes = (24.0 + ((SQUARE ? 24.0 : 36.0) + (prev ? 12.0 : 0.0)) * map.n) * 16.0 * lat.V;
+  prof_launch(prof, K_WILSON, bytes, 2.0 * 1392.0 * lat.V * map.n, wilson_pair_kernel<SQUARE>, dim3(nblk, map.n),
+              dim3(576), 0, s, links, in, istride, mid, mstride, out, ostride, prev, pstride, geom(lat, nblk), map, ca1,
+              cb1, ca2, cb2, cc);
+}
+
+void wilson_apply_cheb_pair(const Lattice& lat, const double2* links, const double2* in, size_t istride, double2* mid,
+                            size_t mstride, double2* out, size_t ostride, const double2* prev, size_t pstride,
+                            double ca1, double cb1, double ca2, double cb2, const SlotMap& map, hipStream_t s,
+                            Profiler* prof) {
+  SGN_REQUIRE(map.n >= 1 && map.n <= kMaxBatch, SGN_EINVAL, "wilson: slot map must hold 1..64 slots");
+  pair_launch<false>(lat, links, in, istride, mid, mstride, out, ostride, prev, pstride, map, ca1, cb1, ca2, cb2, 0.0,
+                     s, prof);
+}
+
 void wilson_apply_cheb_slots(const Lattice& lat, const double2* links, const double2* in, size_t istride,
                              double2* out, size_t ostride, const double2* prev, size_t pstride, double ca, double cb,
                              const SlotMap& map, hipStream_t s, Profiler* prof) {
@@ -656,6 +827,10 @@ void wilson_apply_cheb_slots(const Lattice& lat, const double2* links, const dou
 
 void wilson_apply_square(const Lattice& lat, const double2* links, const double2* y, double2* tmp, double2* out,
                          double a, double c, double b, const double2* yp, hipStream_t s, Profiler* prof) {
+  if (wilson_pairs(lat, 1)) {
+    pair_launch<true>(lat, links, y, 0, nullptr, 0, out, 0, yp, 0, one_slot(), 1.0, 0.0, a, -c, -b, s, prof);
+    return;
+  }
   wilson_apply(lat, links, y, tmp, nullptr, nullptr, s, prof);
   Terms<double2> t;
   t.prev = y;

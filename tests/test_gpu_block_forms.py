@@ -28,10 +28,12 @@ def env():
 # quarters alone; a last block of 8 columns after blocks of 16 (packed); 9
 # columns (the least that is not packed); fewer rows than a chunk; row
 # remainders of the update's 16- and 32-row workgroups (N = 12 mod 32) with a
-# deflated part
+# deflated part; the largest launch that makes two stencil applications at once
+# (256 workgroups of four sites) against the next larger one
 @pytest.mark.parametrize("dims,m,block,k,nrhs", [
     ((6, 6, 6, 6), 0, 16, 112, 14), ((6, 6, 6, 6), 0, 16, 104, 15), ((3, 3, 3, 5), 0, 9, 40, 9),
-    ((2, 2, 2, 2), 0, 16, 37, 3), ((3, 5, 5, 5), 4, 13, 57, 24), ((4, 4, 4, 5), 3, 8, 44, 40)])
+    ((2, 2, 2, 2), 0, 16, 37, 3), ((3, 5, 5, 5), 4, 13, 57, 24), ((4, 4, 4, 5), 3, 8, 44, 40),
+    ((4, 4, 8, 8), 0, 16, 35, 2), ((2, 3, 2, 5), 0, 5, 18, 40)])
 def test_forms_bitwise_equal(env, dims, m, block, k, nrhs):
     sg, torch = env
     print("block forms", dims, m, block, k, nrhs, flush=True)
