@@ -386,16 +386,21 @@ __device__ inline double raw_part(const double* __restrict__ Pcd, int q, int nrt
   return acc;
 }
 
-// Few row tiles (kPartTiles or fewer): a workgroup takes C columns and the
+// Few row tiles (kPartTiles or fewer): a workgroup takes C ng columns and the
 // tiles p, p + 8, ... of part p = 0..7, a wavefront per tile, and adds their
 // sums in order; the update pass adds the eight parts in order itself.  The
 // sums are those of kdot_kernel and kred_kernel, without the reduction's
-// launch (3.6 us of a step).
+// launch (3.6 us of a step).  A wavefront's weights are as many bytes as one or
+// two columns, so one slot's wavefronts keep them for ng columns (C = 1): dot
+// and update of a step, two columns a workgroup / this, 2400 sites FP64, 150
+// columns 32.8 / 28.0 us, 300 columns 54.4 / 49; 2430 sites FP32, 150 columns
+// 26.4 / 22.1, 300 columns 43.4 / 35.9; 6^4, 150 columns 20.2 / 19.8.
 constexpr int kParts = 8;
 constexpr int kPartTiles = 64;
+constexpr int kPartWidth = 16;  // most columns of a workgroup: a thread of its first wavefront per sum
 template <typename VT, int C>
 __global__ void __launch_bounds__(64 * kPartTiles / kParts) kdot_parts_kernel(KrylovArgs A, int with_z, ColGroups G,
-                                                                      int ngroups) {
+                                                                      int ng) {
   constexpr int R = rows_per_lane<VT>();
   static_assert(kParts == kXcds, "the tiles of a part run on one XCD");
   const unsigned l = blockIdx.x / kParts;
@@ -405,24 +410,33 @@ __global__ void __launch_bounds__(64 * kPartTiles / kParts) kdot_parts_kernel(Kr
   const int lane = threadIdx.x & 63, wave = wave_id();
   const int kcols = step_of(A, zb);
   const bool schur = cg < G.gs;
-  const int c0 = (schur ? cg : cg - G.gs) * C, cend = schur ? A.m : kcols;
+  const int c0 = (schur ? cg : cg - G.gs) * G.width, cend = min(c0 + G.width, schur ? A.m : kcols);
   const bool raw = cg == 0;
   const int ntiles = part < A.nrt_dot ? (A.nrt_dot - part + kParts - 1) / kParts : 0;
-  __shared__ double sums[kPartTiles / kParts][4 * C];
+  __shared__ double sums[kPartTiles / kParts][4 * kPartWidth];
   const int nw = blockDim.x >> 6;
   auto walk = [&](const auto* base, auto tag) {
     using QT = decltype(tag);
     for (int tl = wave; tl < ntiles; tl += nw) {
       const int rt = part + kParts * tl, row0 = rt * kDRows;
-      ColBuf<QT> q[C];
-      if (c0 < cend) load_cols<QT, C, R>(q, base, A.ldq, c0, cend, row0, lane, A.N);
-      Weights<VT, R> w;
-      w.load(A, r, row0, lane, with_z);
-      if (c0 < cend) {
-        const double sum = w.template dot<QT, C>(q, lane);
-        if (lane % (16 / C) == 0) sums[tl][lane / (16 / C)] = sum;
+      if constexpr (C == 1) {
+        Weights<VT, R> w;
+        w.load(A, r, row0, lane, with_z);
+        if (c0 < cend)
+          dot_walk<QT, 1, R, false>(w, base, A.ldq, c0, ng, cend, row0, lane, A.N,
+                                    [&](int c, int k, double sum) { sums[tl][4 * (c - c0) + k] = sum; });
+        if (raw) w.raw_sums(A.Pcd + (size_t)r * A.cdstride + 4 * rt, lane);
+      } else {
+        ColBuf<QT> q[C];
+        if (c0 < cend) load_cols<QT, C, R>(q, base, A.ldq, c0, cend, row0, lane, A.N);
+        Weights<VT, R> w;
+        w.load(A, r, row0, lane, with_z);
+        if (c0 < cend) {
+          const double sum = w.template dot<QT, C>(q, lane);
+          if (lane % (16 / C) == 0) sums[tl][lane / (16 / C)] = sum;
+        }
+        if (raw) w.raw_sums(A.Pcd + (size_t)r * A.cdstride + 4 * rt, lane);
       }
-      if (raw) w.raw_sums(A.Pcd + (size_t)r * A.cdstride + 4 * rt, lane);
     }
   };
   if (c0 < cend || raw) {
@@ -433,7 +447,7 @@ __global__ void __launch_bounds__(64 * kPartTiles / kParts) kdot_parts_kernel(Kr
   }
   __syncthreads();
   const int k = threadIdx.x;
-  if (k < 4 * C && c0 + k / 4 < cend) {
+  if (k < 4 * (cend - c0)) {
     double acc = 0.0;
     for (int tl = 0; tl < ntiles; ++tl) acc += sums[tl][k];
     double2* P = (k & 2 ? A.Pb : A.Pa) + (size_t)r * A.pstride + (size_t)part * A.ldp;
@@ -1214,8 +1228,10 @@ static int kept_tiles(const KrylovWork& w, const KrylovArgs& A) {
   return (int)std::min((double)w.nrt_dot, std::max(0.0, kKeepBytes - 16.0 * A.N * sm) / tile);
 }
 
-// wavefronts that fill the chip in the dot pass by parts
-constexpr size_t kDotWaves = 2048;
+// wavefronts that one slot's dot pass by parts is left with (512 and 1024: up to
+// 3 us slower at 1920 sites and 150 columns, 24.3 us), and those from which
+// several slots take two columns a workgroup
+constexpr size_t kDotWaves = 768, kDotWavesBatch = 2048;
 
 // How a launch forms the dot pass's sums (the same sums in the same order).
 // Dot and update of one step back to back, by form (us; the general one with
@@ -1285,16 +1301,23 @@ void krylov_dot(const KrylovWork& w, const KrylovArgs& Ain, bool with_z, bool re
   }
   const bool parts = form == DotForm::Parts;
   if (parts) {
-    // two columns per workgroup, or one where two would leave the chip short
-    // of wavefronts
-    const int C = A.tune.cpw > 1 && (size_t)w.nrt_dot * A.nb * ((Jmax + 1) / 2) >= kDotWaves ? 2 : 1;
-    const ColGroups G = groups(C, ngroups);
+    // several slots: two columns per workgroup, or one where two would leave the
+    // chip short of wavefronts (1350 sites x 3, 150 columns: 45.4 us a step, 49.7
+    // with columns one after another).  One slot: as many columns one after
+    // another as leave it kDotWaves
+    int C = 1, ng = 1;
+    if (A.nb > 1) {
+      if (A.tune.cpw > 1 && (size_t)w.nrt_dot * A.nb * ((Jmax + 1) / 2) >= kDotWavesBatch) C = 2;
+    } else {
+      while (2 * ng <= kPartWidth && (size_t)w.nrt_dot * (Jmax / (2 * ng)) >= kDotWaves) ng *= 2;
+    }
+    const ColGroups G = groups(C * ng, ngroups);
     const size_t nwg = (size_t)kParts * A.nb * ngroups;
     const int nw = (w.nrt_dot + kParts - 1) / kParts;
     SGN_REQUIRE(nwg * 64 * nw < (size_t(1) << 32), SGN_EINVAL, "krylov: dot grid too large");
     prof_launch(prof, K_KDOT, bytes, flops,
                 C == 1 ? kdot_parts_kernel<VT, 1> : kdot_parts_kernel<VT, 2>,
-                dim3((unsigned)nwg), dim3(64 * nw), 0, s, A, with_z ? 1 : 0, G, ngroups);
+                dim3((unsigned)nwg), dim3(64 * nw), 0, s, A, with_z ? 1 : 0, G, ng);
   } else {
     // columns whose loads a wavefront issues together, and batches of them per
     // wavefront.  8^4, 130 FP32 columns: 21.3 us with the reduction for two

@@ -28,7 +28,9 @@ def env():
 @pytest.mark.parametrize("prec", ["fp64", "mixed"])
 @pytest.mark.parametrize("dims,m,k,nrhs", [
     ((2, 2, 2, 4), 0, 30, 64), ((4, 4, 4, 5), 6, 70, 12), ((2, 2, 2, 43), 0, 45, 16), ((4, 4, 8, 8), 5, 40, 6),
-    ((2, 5, 13, 21), 3, 20, 3), ((2, 8, 9, 19), 0, 20, 2)])
+    ((2, 5, 13, 21), 3, 20, 3), ((2, 8, 9, 19), 0, 20, 2),
+    # one source: 4, 8 and 16 columns a workgroup, with remainders
+    ((5, 5, 6, 6), 6, 151, 5), ((2, 5, 13, 21), 3, 100, 5), ((2, 5, 13, 21), 0, 205, 5)])
 def test_forms_bitwise_equal(env, dims, m, k, nrhs, prec):
     sg, torch = env
     print("forms", dims, m, k, nrhs, prec, flush=True)
