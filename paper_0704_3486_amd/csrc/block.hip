@@ -104,19 +104,22 @@ struct BlockGeo {
 // vectors for every column group, and the rows of the Schur columns for every
 // slot where all positions have the same tile there): with j = z + nb k,
 // i = 8 (j + nb nk q) + x -> b = 8 q + x.  With few tiles some XCDs would have
-// one more than others, so position z counts its tiles on from z ntiles.  The
-// update passes take the tiles downwards, so that what the dot pass read last
-// is still in the caches (and what they read last, for the next dot pass).  A
-// grid of 8 nb nk ceil(ntiles / 8) workgroups covers every (b, z, k) once;
-// false for the padding (b >= ntiles).
-constexpr int kEvenTiles = 128;
+// one more than others, so where the shares would differ by more than an eighth
+// position z counts its tiles on from z ntiles (elsewhere the slots share the
+// Schur rows: 6^4 x 8 slots, 31 chunks, HBM traffic of the dot pass 1.02 of the
+// algorithmic bytes, 1.11 if they counted on).  The update passes take the
+// tiles downwards, so that what the dot pass read last is still in the caches
+// (and what they read last, for the next dot pass).  A grid of 8 nb nk
+// ceil(ntiles / 8) workgroups covers every (b, z, k) once; false for the
+// padding (b >= ntiles).
+__device__ inline bool uneven(int ntiles) { return 8 * ((ntiles + 7) >> 3) > ntiles + (ntiles >> 3); }
 template <bool DOWN>
 __device__ inline bool xcd_tile(int i, int nb, int nk, int ntiles, int& b, int& z, int& k) {
   const int x = i & 7, l = i >> 3, up = l / (nb * nk), j = l - up * nb * nk;
   const int q = DOWN ? ((ntiles - 1) >> 3) - up : up;
   k = j / nb;
   z = j - k * nb;
-  b = 8 * q + (ntiles < kEvenTiles ? (x - z * ntiles) & 7 : x);
+  b = 8 * q + (uneven(ntiles) ? (x - z * ntiles) & 7 : x);
   return b < ntiles;
 }
 inline unsigned xcd_grid(int per, int ntiles) { return 8u * (unsigned)per * (unsigned)((ntiles + 7) / 8); }

@@ -149,10 +149,12 @@ __device__ inline int step_of(const KrylovArgs& A, int z) { return A.jdev ? *A.j
 // way round, as far as they fit (the L2 keeps its contents from one kernel to
 // the next: 32 MB read twice by the same XCDs take no longer than an empty
 // kernel, read by other XCDs 5.8 us).  A launch of few tiles would leave some
-// XCDs with a tile more than others (ten tiles: twice as much), so launch
-// position z counts its tiles on from z ntiles.  The update walks its tiles
-// from the last to the first: what the dot pass read last is then still in the
-// L2 and in the 256 MB of the Infinity Cache, and so for the next dot pass.
+// XCDs with a tile more than others (ten tiles: twice as much), so where the
+// shares would differ by more than an eighth launch position z counts its tiles
+// on from z ntiles (elsewhere the slots share the Schur rows).  The update walks
+// its tiles from the last to the first: what the dot pass read last is then
+// still in the L2 and in the 256 MB of the Infinity Cache, and so for the next
+// dot pass.
 // Dot and update of a step, tiles of both upwards / update downwards: 1764
 // sites x 12 slots, FP64, 100 columns 182 / 160 us, 250 columns 399 / 375; 8^4
 // x 6, FP32, 150 columns 168 / 137; 8^4 x 1, FP64, 50 columns 28.5 / 25.6;
@@ -160,9 +162,9 @@ __device__ inline int step_of(const KrylovArgs& A, int z) { return A.jdev ? *A.j
 // i -> (tile t, index in [0, per) with position z = in mod nb): false for the
 // padding.
 constexpr int kXcds = 8;
-constexpr int kEvenTiles = 128;  // tiles from which their shares are even enough
 __device__ inline int rotate_tile(int t, int z, int ntiles) {
-  return ntiles < kEvenTiles ? (t & ~(kXcds - 1)) | ((t - z * ntiles) & (kXcds - 1)) : t;
+  const bool uneven = kXcds * ((ntiles + kXcds - 1) / kXcds) > ntiles + ntiles / 8;
+  return uneven ? (t & ~(kXcds - 1)) | ((t - z * ntiles) & (kXcds - 1)) : t;
 }
 template <bool DOWN>
 __device__ inline bool tile_of(unsigned i, unsigned per, unsigned nb, int ntiles, int& t, int& z, int& in) {
