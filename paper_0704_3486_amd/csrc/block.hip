@@ -1139,14 +1139,15 @@ __global__ void __launch_bounds__(256) bsmall_kernel(BlockGeo g, BSmall a) {
   }
 }
 
-// Rows per wavefront of the dot pass, a multiple of 16, and its row chunks of
-// four wavefronts.  By N alone (never by the slots, so that a source's sums are
-// the same alone and in a batch): 128 rows, so that the partial sums stay at 3
-// per cent of the basis, and 64 on lattices whose chunks of 512 rows are too
-// few to fill the chip; at most 128 chunks.
+// Rows per wavefront of the dot pass, a multiple of 32 (the update's workgroups
+// of up to 128 rows must tile a chunk), and its row chunks of four wavefronts.
+// By N alone (never by the slots, so that a source's sums are the same alone
+// and in a batch): 128 rows, so that the partial sums stay at 3 per cent of the
+// basis, and 64 on lattices whose chunks of 512 rows are too few to fill the
+// chip; at most 128 chunks.
 int nchunks_for(int N, int& rpw) {
   const int want = (N + 4 * 128 - 1) / (4 * 128);
-  rpw = std::max(N < kSmallRows ? 64 : 128, (want + 15) & ~15);
+  rpw = std::max(N < kSmallRows ? 64 : 128, (want + 31) & ~31);
   return (N + 4 * rpw - 1) / (4 * rpw);
 }
 
@@ -1284,6 +1285,7 @@ void block_step(const BlockSpan& sp, BlockWork& b, const Lattice& lat, const dou
                 dim3(nblk * nb), dim3(256), 0, s, g, rd);
   };
   const int crows = 4 * rpw;
+  SGN_REQUIRE(crows % upd_rows_wg == 0, SGN_EINVAL, "block step: update rows do not tile the chunk");
   const unsigned ugrid = xcd_grid(nb * (crows / upd_rows_wg), nch);
   // the basis (S once for the launch), W read and written, the coefficients
   const double upd_bytes = 16.0 * N * ((double)m + (double)nb * (p - m + 2.0 * sb)) + 16.0 * p * sb * (double)nb;

@@ -33,7 +33,9 @@ def env():
 @pytest.mark.parametrize("dims,m,block,k,nrhs", [
     ((6, 6, 6, 6), 0, 16, 112, 14), ((6, 6, 6, 6), 0, 16, 104, 15), ((3, 3, 3, 5), 0, 9, 40, 9),
     ((2, 2, 2, 2), 0, 16, 37, 3), ((3, 5, 5, 5), 4, 13, 57, 24), ((4, 4, 4, 5), 3, 8, 44, 40),
-    ((4, 4, 8, 8), 0, 16, 35, 2), ((2, 3, 2, 5), 0, 5, 18, 40)])
+    ((4, 4, 8, 8), 0, 16, 35, 2), ((2, 3, 2, 5), 0, 5, 18, 40),
+    # more than 65536 rows, where the chunks grow: whole rows in the batch
+    ((7, 11, 7, 11), 0, 16, 88, 4), ((11, 7, 7, 12), 2, 16, 80, 4)])
 def test_forms_bitwise_equal(env, dims, m, block, k, nrhs):
     sg, torch = env
     print("block forms", dims, m, block, k, nrhs, flush=True)
