@@ -1244,18 +1244,29 @@ constexpr size_t kDotWaves = 768, kDotWavesBatch = 2048;
 // Tiles 52.7, Parts 52.4, former 55.7; FP32: Tiles 36.7, Parts 38.2 (56.7
 // against 47.5 at 260 columns), former 36.7.  8^4 x 6 slots, 180 columns:
 // Tiles 283.5, former 301.7.
-// Every workgroup of the update adds the parts for itself, J times 256 bytes:
-// with several slots of few tiles that costs more than the reduction saves.
-// 256 sites x 16 slots, 50 / 150 / 260 columns: Parts 22.4 / 49.7 / 84.1, Tiles
-// 21.9 / 47.2 / 72.3; 600 sites x 8, 260 columns: 91.7 and 84.7; 400 sites x 5:
-// 47.4 and 44.3; 900 sites x 4: Parts 65.4, former 69.5; 1296 sites x 4: 92.4
-// and 94.0.
+// Every workgroup of the update adds the parts for itself, J times 256 bytes, and
+// every column of Whole reads u and z again: what that costs grows with tiles x
+// slots x columns, and past a bound it is more than the reduction's launch.
+// Parts / Tiles (former kernels): two slots of 900 sites, 60 columns 15.0 / 17.7
+// (20.4), 1440 sites, 300 columns 73.5 / 60.6 (62.6), FP32 60.3 / 43.7 (46.8);
+// four of 450 sites, 60 columns 19.1 / 19.3, 1260 sites, FP32, 420 columns 109 /
+// 79 (82); one of 1260 sites, 120 / 420 / 580 columns 17.3 / 18.1, 43.6 / 43.0,
+// 59.7 / 55.9, of 2640 sites, 60 / 120 / 580 columns 19.4 / 20.0, 29.5 / 28.0,
+// 124 / 101 (108).  Whole / Tiles, FP32: 8 slots of 256 sites, 60 / 120 / 420
+// columns 15.2 / 17.4, 22.5 / 20.6, 57.5 / 49.2; FP64: 12 of 200 sites, 60 / 300 /
+// 580 columns 22.3 / 23.4, 65.3 / 61.8, 139 / 124.
 constexpr int kPartSlots = 4;
+constexpr long long kPartWorkOne = 10000, kPartWork = 5000, kWholeWork = 20000, kWholeWork32 = 5000;
 enum class DotForm { Whole, Parts, Tiles };
+template <typename VT>
 static DotForm dot_form(const KrylovWork& w, const KrylovArgs& A) {
-  const long long work = (long long)w.nrt_dot * A.nb;
-  if (w.nrt_dot <= kParts && work <= kPartTiles) return DotForm::Whole;
-  if (w.nrt_dot <= kPartTiles && A.nb <= kPartSlots && work <= 2 * kPartTiles) return DotForm::Parts;
+  const long long work = (long long)w.nrt_dot * A.nb, cols = work * (A.m + A.jmax());
+  if (w.nrt_dot <= kParts)
+    return work <= kPartTiles && cols <= (sizeof(VT) == 8 ? kWholeWork32 : kWholeWork) ? DotForm::Whole
+                                                                                       : DotForm::Tiles;
+  if (w.nrt_dot <= kPartTiles && A.nb <= kPartSlots && work <= 2 * kPartTiles &&
+      cols <= (A.nb == 1 ? kPartWorkOne : kPartWork))
+    return DotForm::Parts;
   return DotForm::Tiles;
 }
 
@@ -1286,7 +1297,7 @@ void krylov_dot(const KrylovWork& w, const KrylovArgs& Ain, bool with_z, bool re
   // algorithmic bytes: Q, u, z read once; a, b written
   const double bytes = qbytes + A.nb * A.N * (16.0 + (with_z ? vb : 0.0)) + 32.0 * cols;
   const double flops = 16.0 * (double)A.N * cols;
-  const DotForm form = dot_form(w, A);
+  const DotForm form = dot_form<VT>(w, A);
   auto groups = [&](int width, int& ng) {
     ColGroups G{(A.m + width - 1) / width, width};
     ng = std::max(1, G.gs + (kmax + width - 1) / width);
@@ -1363,7 +1374,7 @@ void krylov_update(const KrylovWork& w, const KrylovArgs& Ain, hipStream_t s, Pr
   // read Q, u, z; write v_J, u' (+ its low-precision copy)
   const double vec = A.N * (16.0 + vb + vb + 16.0 + (A.ulonext ? vb : 0.0));
   const double cols = A.nb * (double)A.m + sk;  // per-slot work counts S for every slot
-  const bool parts = dot_form(w, A) == DotForm::Parts;
+  const bool parts = dot_form<VT>(w, A) == DotForm::Parts;
   const uint32_t lds = parts ? (uint32_t)(2 * sizeof(double2)) * (uint32_t)(std::min(Jmax, kCoefCap) + kCoefPad) : 0;
   prof_launch(prof, K_KUPDATE, qbytes + A.nb * vec + 32.0 * cols, 16.0 * (double)A.N * cols,
               parts ? update_kernel_for<VT, true>(A.tune) : update_kernel_for<VT, false>(A.tune), dim3((unsigned)nwg),

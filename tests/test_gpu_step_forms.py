@@ -85,3 +85,56 @@ def test_streamed_tiles(env, prec, k, nrhs):
             assert torch.equal(y, Y[r]), r
     finally:
         sg.sgn_destroy(ctx)
+
+
+def _reductions(sg, torch, dims, nrhs, k, prec):
+    """(steps, reduction launches) of an apply with k columns, and its result"""
+    ctx = sg.sgn_create(synth.random_links(dims, 11), dims, 0.3, M_W)
+    try:
+        sg.sgn_set_precision(ctx, prec)
+        X = torch.from_numpy(np.stack([synth.gaussian_source(dims, 70 + r) for r in range(nrhs)])).cuda()
+        Y = torch.empty_like(X)
+        sg.sgn_set_profiling(ctx, True)
+        sg.sgn_profile_reset(ctx)
+        if nrhs == 1:
+            sg.sgn_apply_fixed(ctx, X[0], Y[0], k)
+        else:
+            sg.sgn_apply_batched_fixed(ctx, X, Y, k)
+        n = {name: st["launches"] for name, st in sg.sgn_profile_read(ctx).items()}
+        return n["krylov_dot"], n.get("krylov_reduce", 0), Y
+    finally:
+        sg.sgn_destroy(ctx)
+
+
+# short bases go without the reduction launch (one is left, at the end), long
+# ones with it: from 5000 tiles x slots x columns on in batches (10000 for one
+# source), on lattices of 8 tiles or fewer from 20000 (FP64) and 5000 (FP32)
+@pytest.mark.parametrize("dims,nrhs,k,prec,first", [
+    ((5, 6, 7, 8), 2, 120, 0, 63), ((5, 6, 7, 8), 3, 120, 1, 42), ((5, 6, 6, 7), 4, 100, 1, 42),
+    ((6, 7, 7, 8), 1, 220, 0, 179), ((5, 6, 6, 7), 1, 360, 1, 334), ((4, 4, 4, 4), 8, 150, 1, 105),
+    ((4, 4, 4, 5), 8, 330, 0, 313), ((5, 6, 6, 7), 1, 300, 0, 334)])
+def test_long_bases_take_the_reduction(env, dims, nrhs, k, prec, first):
+    sg, torch = env
+    print("long bases", dims, nrhs, k, prec, flush=True)
+    steps, reds, Y = _reductions(sg, torch, dims, nrhs, k, prec)
+    tiles = (12 * int(np.prod(dims)) + 511) // 512
+    # steps with 0 .. k - 1 columns, then one dot pass with k for the last column
+    want = max(0, k - first) + (1 if tiles > 8 or first <= k else 0)
+    assert steps == k + 1 and reds == want, (steps, reds, want)
+    # the same bits as one source alone (nrhs > 1) or as in a batch of 16
+    other = 1 if nrhs > 1 else 16
+    ctx = sg.sgn_create(synth.random_links(dims, 11), dims, 0.3, M_W)
+    try:
+        sg.sgn_set_precision(ctx, prec)
+        x = torch.from_numpy(synth.gaussian_source(dims, 70)).cuda()
+        y = torch.empty_like(x)
+        if other == 1:
+            sg.sgn_apply_fixed(ctx, x, y, k)
+        else:
+            X = x.repeat(other, 1)
+            Y2 = torch.empty_like(X)
+            sg.sgn_apply_batched_fixed(ctx, X, Y2, k)
+            y = Y2[other - 1]
+        assert torch.equal(y, Y[0])
+    finally:
+        sg.sgn_destroy(ctx)
