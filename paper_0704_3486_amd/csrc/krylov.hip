@@ -30,6 +30,7 @@
 // has a fixed order, so results are bitwise independent of the batch.
 #include "internal.h"
 #include "krylov.h"
+#include "tilemap.h"
 
 namespace {
 
@@ -142,40 +143,6 @@ __device__ inline int wave_id() { return __builtin_amdgcn_readfirstlane(threadId
 // launch position z (an index into the batch) -> buffer slot and step
 __device__ inline int slot_of(const KrylovArgs& A, int z) { return A.act[z]; }
 __device__ inline int step_of(const KrylovArgs& A, int z) { return A.jdev ? *A.jdev + A.joff : A.jv[z]; }
-
-// Workgroup i runs on XCD i mod 8.  The dot and update passes give the rows of
-// tile t (512 rows) to XCD t mod 8, so the columns that the dot pass reads
-// into an XCD's 4 MB of L2 are still there for the update pass, and the other
-// way round, as far as they fit (the L2 keeps its contents from one kernel to
-// the next: 32 MB read twice by the same XCDs take no longer than an empty
-// kernel, read by other XCDs 5.8 us).  A launch of few tiles would leave some
-// XCDs with a tile more than others (ten tiles: twice as much), so where the
-// shares would differ by more than an eighth launch position z counts its tiles
-// on from z ntiles (elsewhere the slots share the Schur rows).  The update walks
-// its tiles from the last to the first: what the dot pass read last is then
-// still in the L2 and in the 256 MB of the Infinity Cache, and so for the next
-// dot pass.
-// Dot and update of a step, tiles of both upwards / update downwards: 1764
-// sites x 12 slots, FP64, 100 columns 182 / 160 us, 250 columns 399 / 375; 8^4
-// x 6, FP32, 150 columns 168 / 137; 8^4 x 1, FP64, 50 columns 28.5 / 25.6;
-// 12^4 x 8, FP32, 100 + 100 columns 995 / 955.
-// i -> (tile t, index in [0, per) with position z = in mod nb): false for the
-// padding.
-constexpr int kXcds = 8;
-__device__ inline int rotate_tile(int t, int z, int ntiles) {
-  const bool uneven = kXcds * ((ntiles + kXcds - 1) / kXcds) > ntiles + ntiles / 8;
-  return uneven ? (t & ~(kXcds - 1)) | ((t - z * ntiles) & (kXcds - 1)) : t;
-}
-template <bool DOWN>
-__device__ inline bool tile_of(unsigned i, unsigned per, unsigned nb, int ntiles, int& t, int& z, int& in) {
-  const unsigned l = i / kXcds, up = l / per, k = l - up * per;
-  const unsigned q = DOWN ? (unsigned)(ntiles - 1) / kXcds - up : up;
-  in = (int)(k / nb);
-  z = (int)(k - (unsigned)in * nb);
-  t = rotate_tile((int)(q * kXcds + i % kXcds), z, ntiles);
-  return t < ntiles;
-}
-inline size_t tile_grid(size_t per, int ntiles) { return (size_t)kXcds * per * ((ntiles + kXcds - 1) / kXcds); }
 
 // ---------------------------------------------------------------------------
 // dot pass: sums of Q^dag u and Q^dag z over row tiles, plus |u|^2, u^dag z,
@@ -347,7 +314,7 @@ __global__ void __launch_bounds__(256) kdot_kernel(KrylovArgs A, int with_z, Col
                                                    int keep) {
   constexpr int R = rows_per_lane<VT>();
   int rt, zb, cg;
-  if (!tile_of<false>(blockIdx.x, A.nb * ngroups, A.nb, A.nrt_dot, rt, zb, cg)) return;
+  if (!tile_of<false, false>(blockIdx.x, A.nb * ngroups, A.nb, A.nrt_dot, rt, zb, cg)) return;
   const int r = slot_of(A, zb);
   const int lane = threadIdx.x & 63, wave = wave_id();
   const int N = A.N, kcols = step_of(A, zb), J = A.m + kcols;
@@ -930,7 +897,7 @@ __global__ void __launch_bounds__(64 * NW, 4) kupdate_kernel(KrylovArgs A, int n
     if (bb >= nh) return;
   } else {
     int sub;
-    if (!tile_of<true>(blockIdx.x - nhess, A.nb * kSub, A.nb, A.nrt_dot, rt, zb, sub)) return;
+    if (!tile_of<true, PARTS>(blockIdx.x - nhess, A.nb * kSub, A.nb, A.nrt_dot, rt, zb, sub)) return;
     bb = rt * kSub + sub;
     if (bb * 64 * R >= A.N) return;
   }
@@ -1339,7 +1306,7 @@ void krylov_dot(const KrylovWork& w, const KrylovArgs& Ain, bool with_z, bool re
     // two by two, 128.7 for two by four, 133.6 for one by one
     const int C = std::min(A.tune.cpw, 2), batches = sizeof(VT) == 16 ? 2 : 4;
     const ColGroups G = groups(4 * C * batches, ngroups);
-    const size_t nwg = tile_grid((size_t)A.nb * ngroups, w.nrt_dot);
+    const size_t nwg = tile_grid((size_t)A.nb * ngroups, w.nrt_dot, false);
     SGN_REQUIRE(nwg * 256 < (size_t(1) << 32), SGN_EINVAL, "krylov: dot grid too large");
     prof_launch(prof, K_KDOT, bytes, flops, C == 1 ? kdot_kernel<VT, 1> : kdot_kernel<VT, 2>, dim3((unsigned)nwg),
                 dim3(256), 0, s, A, with_z ? 1 : 0, G, batches, ngroups, kept_tiles<VT>(w, A));
@@ -1364,7 +1331,8 @@ void krylov_update(const KrylovWork& w, const KrylovArgs& Ain, hipStream_t s, Pr
   const int nh = (Jmax + 1 + A.tune.uw - 1) / A.tune.uw;
   check_pairs<VT>(A);
   const unsigned nhess = ((unsigned)nh * A.nb + kXcds - 1) / kXcds * kXcds;
-  const size_t nwg = nhess + tile_grid((size_t)A.nb * (kDRows / (64 * rows_per_lane<VT>())), w.nrt_dot);
+  const bool parts = dot_form<VT>(w, A) == DotForm::Parts;
+  const size_t nwg = nhess + tile_grid((size_t)A.nb * (kDRows / (64 * rows_per_lane<VT>())), w.nrt_dot, parts);
   const int nthr = 64 * A.tune.uw;
   SGN_REQUIRE(nwg * nthr < (size_t(1) << 32), SGN_EINVAL, "krylov: update grid too large");
   const double vb = (double)sizeof(VT);
@@ -1374,7 +1342,6 @@ void krylov_update(const KrylovWork& w, const KrylovArgs& Ain, hipStream_t s, Pr
   // read Q, u, z; write v_J, u' (+ its low-precision copy)
   const double vec = A.N * (16.0 + vb + vb + 16.0 + (A.ulonext ? vb : 0.0));
   const double cols = A.nb * (double)A.m + sk;  // per-slot work counts S for every slot
-  const bool parts = dot_form<VT>(w, A) == DotForm::Parts;
   const uint32_t lds = parts ? (uint32_t)(2 * sizeof(double2)) * (uint32_t)(std::min(Jmax, kCoefCap) + kCoefPad) : 0;
   prof_launch(prof, K_KUPDATE, qbytes + A.nb * vec + 32.0 * cols, 16.0 * (double)A.N * cols,
               parts ? update_kernel_for<VT, true>(A.tune) : update_kernel_for<VT, false>(A.tune), dim3((unsigned)nwg),

@@ -1,0 +1,67 @@
+"""The map from workgroups to row tiles of the one-vector step's dot and update
+passes (csrc/tilemap.h), on the CPU: every (tile, launch position, index) is
+taken exactly once, workgroups that share a tile stay on one XCD where the map
+keeps them there, and no XCD is left with much more than its share."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_0704_3486_amd", "csrc")
+
+DRIVER = r"""
+#include <cstdio>
+#include <set>
+#include <tuple>
+#include "tilemap.h"
+
+template <bool DOWN, bool BY_XCD>
+int check(int nt, int nb, int nk, double most) {
+  const unsigned per = nb * nk;
+  const size_t grid = tile_grid(per, nt, BY_XCD);
+  std::set<std::tuple<int, int, int>> seen;
+  int load[kXcds] = {}, prev = DOWN ? nt : -1;
+  for (size_t i = 0; i < grid; ++i) {
+    int t = -1, z = -1, in = -1;
+    if (!tile_of<DOWN, BY_XCD>((unsigned)i, per, nb, nt, t, z, in)) continue;
+    if (t < 0 || t >= nt || z < 0 || z >= nb || in < 0 || in >= nk) return 1;
+    if (!seen.insert({t, z, in}).second) return 2;
+    ++load[i % kXcds];
+    // the walk goes by groups of kXcds tiles (dealt out: by tiles)
+    const bool dealt = !BY_XCD && dealt_out(nt);
+    const int g = dealt ? t : t / kXcds, p = dealt ? prev : (prev < 0 ? -1 : prev / kXcds);
+    if (prev >= 0 && prev < nt && (DOWN ? g > p : g < p)) return 3;
+    prev = t;
+  }
+  if (seen.size() != (size_t)nt * nb * nk) return 4;
+  int mx = 0;
+  for (int l : load) mx = l > mx ? l : mx;
+  return mx > most * ((double)nt * nb * nk / kXcds) + 1.0 ? 5 : 0;
+}
+
+int main() {
+  for (int nt = 1; nt <= 140; ++nt)
+    for (int nb : {1, 2, 3, 5, 8, 64})
+      for (int nk : {1, 3, 8}) {
+        // 25 tiles by XCD: four where the share is 3.125
+        int r = check<false, false>(nt, nb, nk, 1.28);
+        if (!r) r = check<true, false>(nt, nb, nk, 1.28);
+        if (!r && nt > kXcds) r = check<true, true>(nt, nb, nk, 8.0);
+        if (r) return printf("tiles %d slots %d index %d: %d\n", nt, nb, nk, r), 1;
+      }
+  return 0;
+}
+"""
+
+
+def test_every_tile_once_and_even_shares(tmp_path):
+    cxx = shutil.which("g++") or shutil.which("clang++")
+    if cxx is None:
+        pytest.skip("no host compiler")
+    src, exe = tmp_path / "d.cpp", tmp_path / "d"
+    src.write_text(DRIVER)
+    subprocess.run([cxx, "-O1", "-std=c++17", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
