@@ -1218,7 +1218,7 @@ size_t sgn_footprint_bytes(const sgn_ctx* c, int kmax, int nrhs) {
   }
   const size_t ncap = (size_t)c->m + kmax + 1;
   const size_t per = sizeof(double2) * (c->ldq * (ncap + 3) + ncap * ncap + (ncap - 1) * (ncap - 1) + 4 * ncap) +
-                     sizeof(double2) * c->ldq * ((ncap + 31) / 32);
+                     sizeof(double2) * std::max(c->ldq * ((ncap + 31) / 32), 2 * krylov_part_tiles(c->ldq) * ncap);
   const size_t dense = 3 * sizeof(double2) * (ncap - 1) * (ncap - 1);
   return per + dense;
 }

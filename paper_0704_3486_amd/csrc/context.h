@@ -81,7 +81,7 @@ struct BatchWork {
     size_t b = S * ldq * (kcap + 1) * vt;                    // V
     b += S * ldq * (2 * sizeof(double2) + 3 * vt + 2 * sizeof(double2));  // u, ulo, z, xin, y
     b += S * sizeof(double2) * (ncap * ncap + n * n + (size_t)std::max(m, 1) + 2 * ncap);  // H, F, c0, cv
-    b += S * sizeof(double2) * 2 * (ncap + (ldq + 511) / 512 * ncap);  // dot partials, a, b
+    b += S * sizeof(double2) * 2 * (ncap + krylov_part_tiles(ldq) * ncap);  // dot partials, a, b
     b += 3 * sizeof(double2) * n * n * S;                    // sign work matrices
     return b;
   }

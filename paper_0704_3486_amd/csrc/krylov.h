@@ -101,6 +101,10 @@ struct KrylovArgs {
   }
 };
 
+// row tiles of partial sums per slot and column: the dot pass's tiles of 512
+// rows, or the eight parts it leaves on small lattices
+inline size_t krylov_part_tiles(size_t rows) { return std::max<size_t>((rows + 511) / 512, 8); }
+
 // partial sums of the dot pass [slot][row tile][column], the reduced
 // coefficients a, b [slot][column] and the step scalars [slot][kScStride]
 struct KrylovWork {

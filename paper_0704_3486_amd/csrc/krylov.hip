@@ -1107,7 +1107,8 @@ void krylov_alloc(KrylovWork& w, int N, size_t ldq, int ncol_cap, int nslots) {
   w.ncol_cap = ncol_cap;
   w.nslots = nslots;
   w.ldp = ncol_cap;
-  w.pstride = (size_t)std::max(w.nrt_dot, kParts) * ncol_cap;
+  static_assert(kDRows == 512 && kParts == 8, "krylov_part_tiles");
+  w.pstride = krylov_part_tiles(N) * ncol_cap;
   w.cdstride = (size_t)4 * w.nrt_dot;
   w.abstride = (size_t)ncol_cap;
   const size_t S = (size_t)nslots;
