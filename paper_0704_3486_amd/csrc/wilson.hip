@@ -205,10 +205,10 @@ __device__ inline Halves<double> halves(double v) {
 // takes 2.45 us back to back): 6^4 takes 3.4 us with S = 16, 3.9 with S = 32
 // (5.1 with divisions, a switch over nu and both hops' twelve components
 // through the shuffles).  Large ones are bound by memory: 32^4, 0.81 GB of
-// operands, 227 us = 3.5 TB/s with S = 32, 268 us with S = 16 (263 us before),
-// and 242 us in the interface layout with S = 16 (272 us with S = 32, whose
-// 53 KB of LDS leave two wavefronts per SIMD less); packing, applying and
-// unpacking took 415 us.
+// operands, by events in applies 235 us = 3.4 TB/s with S = 32, 280 us with S =
+// 16 (241 us before), and in sgn_matvec 264 us in the interface layout with S =
+// 16 (287 us with S = 32, whose 53 KB of LDS leave two wavefronts per SIMD
+// less); packing, applying (251 us) and unpacking took 415 us.
 // the terms that a launch adds to ca H_w In
 template <typename C>
 struct Terms {
