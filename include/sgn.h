@@ -383,8 +383,10 @@ int sgn_get_block_steps(const sgn_ctx* ctx, int* s, double* e_out);
  * update_batch (4, 8 or 16) basis columns whose loads each lane of the
  * update pass issues before their arithmetic, dot_cols (1, 2 or 4) basis
  * columns whose loads a wavefront of the dot pass issues together (4 acts
- * as 2), and update_waves (8 or 16)
- * wavefronts per 64-row workgroup of the update pass.  update_batch and
+ * as 2), and update_waves (8 or 16) wavefronts per 64-row workgroup of the
+ * update pass.  On lattices of up to 32768 entries the passes over a short
+ * basis have forms of their own, in which update_batch 16 acts as 8 and, with
+ * one source, dot_cols as 1.  update_batch and
  * dot_cols form every sum in the same order, so results are bitwise the
  * same for all their values; update_waves changes which columns each
  * wavefront sums, so results differ between its values at the rounding

@@ -1,14 +1,17 @@
 """Launch-shape autotuner for the Arnoldi step's dot and update passes.
 
-The update pass's column-load batch (4, 8, 16) and the dot pass's columns per
-wavefront (1, 2, 4) form every sum in the same order, so any of them gives
-bitwise the same result; which is fastest depends on the lattice size, the
-precision and the number of sources in flight.  `autotune` times each of the
-nine shapes on the context itself (sgn_apply_fixed, or
-sgn_apply_batched_fixed for several sources, at a given Krylov dimension),
-keeps the fastest and records it in a JSON cache keyed by lattice,
-precision, deflation size, sources, Krylov dimension and device, so a later
-process with the same key sets it without timing.
+The update pass's column-load batch (4, 8, 16) and the columns whose loads a
+wavefront of the dot pass issues together (1, 2; 4 acts as 2) form every sum
+in the same order, so any of them gives bitwise the same result; which is
+fastest depends on the lattice size, the precision and the number of sources in
+flight.  `autotune` times the six shapes that are kernels of their own on the
+context itself (sgn_apply_fixed, or sgn_apply_batched_fixed for several
+sources, at a given Krylov dimension) and keeps the fastest.  On small lattices
+some of the six are the same kernel (the header says which), so the default
+shape stays unless another is faster by more than MARGIN.  The choice is
+recorded in a JSON cache keyed by the kernels' version, lattice, precision,
+deflation size, sources, Krylov dimension and device, so a later process with
+the same key sets it without timing.
 
 This module only schedules and times calls of the library; all arithmetic
 runs in its kernels.
@@ -24,7 +27,10 @@ from . import (sgn_apply_batched_fixed, sgn_apply_fixed, sgn_deflation_size, sgn
                sgn_get_tuning, sgn_matvec, sgn_set_stencil_blocks, sgn_set_tuning)
 
 UPDATE_BATCH = (4, 8, 16)
-DOT_COLS = (1, 2, 4)
+DOT_COLS = (1, 2)
+DEFAULT = (8, 2)  # the library's default shape
+MARGIN = 0.01
+VERSION = "v2"  # of the dot and update kernels that the cached shapes were timed on
 # stencil walk blocks (By, Bz, Bt) tried by autotune_stencil: the default
 # rule, the natural order and blocks around the default
 STENCIL_BLOCKS = ((0, 0, 0), (-1, 0, 0), (4, 16, 2), (4, 16, 8), (4, 8, 8), (8, 8, 2), (8, 8, 4), (2, 8, 4),
@@ -34,7 +40,7 @@ STENCIL_STEPS = 4
 
 def _key(ctx, nrhs, k, device):
     dims, n = sgn_get_dims(ctx)
-    return "|".join(str(v) for v in ("x".join(map(str, dims)), n, sgn_get_precision(ctx), sgn_deflation_size(ctx),
+    return "|".join(str(v) for v in (VERSION, "x".join(map(str, dims)), n, sgn_get_precision(ctx), sgn_deflation_size(ctx),
                                         nrhs, k, device))
 
 
@@ -85,6 +91,8 @@ def autotune(ctx, k=256, nrhs=1, cache=None, reps=3):
             best = min(best, time.perf_counter() - t0)
         times[(ub, cpw)] = best
     (ub, cpw), t = min(times.items(), key=lambda kv: kv[1])
+    if t > (1.0 - MARGIN) * times[DEFAULT]:
+        (ub, cpw), t = DEFAULT, times[DEFAULT]
     sgn_set_tuning(ctx, ub, cpw, uw)
     if cache:
         table = _load(cache)  # merge with what other processes wrote meanwhile
