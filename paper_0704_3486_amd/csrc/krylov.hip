@@ -48,18 +48,6 @@ __device__ inline double2 ld2(const float2* p, size_t i) {
 __device__ inline void st2(double2* p, size_t i, double2 v) { p[i] = v; }
 __device__ inline void st2(float2* p, size_t i, double2 v) { p[i] = make_float2((float)v.x, (float)v.y); }
 
-// two adjacent rows il, il + 1 of one column (il even): FP32 columns in one
-// 16-byte load per lane, FP64 columns in two
-__device__ inline void ld_pair(const double2* __restrict__ p, int il, double2& q0, double2& q1) {
-  q0 = p[il];
-  q1 = p[il + 1];
-}
-__device__ inline void ld_pair(const float2* __restrict__ p, int il, double2& q0, double2& q1) {
-  const float4 v = *reinterpret_cast<const float4*>(p + il);
-  q0 = make_double2((double)v.x, (double)v.y);
-  q1 = make_double2((double)v.z, (double)v.w);
-}
-
 // Rows per lane group of the dot and update passes: 1 with FP64 Krylov
 // columns, 2 with FP32 columns, whose lanes then take adjacent row pairs so
 // that a column load is 16 bytes per lane
