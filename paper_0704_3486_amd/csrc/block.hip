@@ -633,9 +633,9 @@ __device__ void hess_entry(const BlockGeo& g, const BHess& h, int r_slot, int id
 // ---------------------------------------------------------------------------
 // update pass: Wout = (Win - Q C) [Rinv].  With Rinv (the second pass) the
 // first workgroups (padded to whole rounds of the XCDs) write the block's
-// Hessenberg columns (hess).  The others take the rows by the dot pass's row
-// chunks, a chunk on the XCD that read it there: on small lattices the columns
-// are then still in that XCD's L2.
+// Hessenberg columns (hess).  The others take the rows by chunks: with s > 8 the
+// dot pass's row chunks, a chunk on the XCD that read it there (on small
+// lattices the columns are then still in that XCD's L2).
 struct BUpd {
   const double2* C;
   size_t cstride;
@@ -1284,15 +1284,20 @@ void block_step(const BlockSpan& sp, BlockWork& b, const Lattice& lat, const dou
     prof_launch(prof, K_BRED, (16.0 * (double)nch * nent + 16.0 * nent) * nb, 2.0 * nch * nent * nb, bred_kernel,
                 dim3(nblk * nb), dim3(256), 0, s, g, rd);
   };
-  const int crows = 4 * rpw;
+  // rows that a launch keeps on one XCD: the dot pass's chunks, or (packed form)
+  // the workgroup's own 64 rows, whose shares are even on small lattices too.  us
+  // of a whole apply's updates, chunks / own rows (the former kernels): 4^4 x 16
+  // slots, s = 2, 200 columns 5340 / 4580 (4520); 12^4 x 4, s = 4, 240 columns 56.6
+  // / 55.5 ms (56.4)
+  const int crows = gauss ? 4 * rpw : upd_rows_wg, uch = (N + crows - 1) / crows;
   SGN_REQUIRE(crows % upd_rows_wg == 0, SGN_EINVAL, "block step: update rows do not tile the chunk");
-  const unsigned ugrid = xcd_grid(nb * (crows / upd_rows_wg), nch);
+  const unsigned ugrid = xcd_grid(nb * (crows / upd_rows_wg), uch);
   // the basis (S once for the launch), W read and written, the coefficients
   const double upd_bytes = 16.0 * N * ((double)m + (double)nb * (p - m + 2.0 * sb)) + 16.0 * p * sb * (double)nb;
   // pass 1
   dot(b.C1, p, nullptr, nullptr);
   {
-    BUpd u{b.C1, b.cstride, b.W, b.wstride, b.W, b.wstride, nullptr, 0, nch, crows, 0, BHess{}};
+    BUpd u{b.C1, b.cstride, b.W, b.wstride, b.W, b.wstride, nullptr, 0, uch, crows, 0, BHess{}};
     prof_launch(prof, K_BUPDATE, upd_bytes, 8.0 * N * p * sb * nb, upd_kernel, dim3(ugrid), dim3(256), 0, s, g, u);
   }
   // pass 2 with the Gram matrix of the projected block
@@ -1308,7 +1313,7 @@ void block_step(const BlockSpan& sp, BlockWork& b, const Lattice& lat, const dou
             sp.ldh};
     const int nh = (((p + sb) * kBlockMax + 255) / 256 * nb + 7) / 8 * 8;
     BUpd u{b.C2, b.cstride, b.W, b.wstride, const_cast<double2*>(sp.V) + (size_t)(p - m) * ldq, sp.vstride,
-           b.R + kBlockMax * kBlockMax, b.rstride, nch, crows, nh, h};
+           b.R + kBlockMax * kBlockMax, b.rstride, uch, crows, nh, h};
     prof_launch(prof, K_BUPDATE, upd_bytes, 8.0 * N * p * sb * nb, upd_kernel, dim3(nh + ugrid), dim3(256), 0, s, g,
                 u);
   }
