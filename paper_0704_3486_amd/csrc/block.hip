@@ -40,6 +40,7 @@
 // Per slot the arithmetic does not depend on the other slots.
 #include "internal.h"
 #include "context.h"
+#include "tilemap.h"
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
@@ -74,8 +75,6 @@ constexpr int kDot3Tiles = 4;
 constexpr int kFullChip = 512;
 // slots from which a launch takes the wide tiles
 constexpr int kWideFrom = 4;
-// rows below which the dot pass takes shorter row chunks
-constexpr int kSmallRows = 12288;
 // blocks of 16 rows per wavefront of the three-multiplication update pass, and
 // the basis (entries over all slots) from which its wavefronts take whole
 // rows: past the 256 MB of the Infinity Cache, where reading 2048 adjacent
@@ -1139,18 +1138,6 @@ __global__ void __launch_bounds__(256) bsmall_kernel(BlockGeo g, BSmall a) {
   }
 }
 
-// Rows per wavefront of the dot pass, a multiple of 32 (the update's workgroups
-// of up to 128 rows must tile a chunk), and its row chunks of four wavefronts.
-// By N alone (never by the slots, so that a source's sums are the same alone
-// and in a batch): 128 rows, so that the partial sums stay at 3 per cent of the
-// basis, and 64 on lattices whose chunks of 512 rows are too few to fill the
-// chip; at most 128 chunks.
-int nchunks_for(int N, int& rpw) {
-  const int want = (N + 4 * 128 - 1) / (4 * 128);
-  rpw = std::max(N < kSmallRows ? 64 : 128, (want + 31) & ~31);
-  return (N + 4 * rpw - 1) / (4 * rpw);
-}
-
 BlockGeo make_geo(const BlockSpan& sp) {
   BlockGeo g;
   g.S = sp.S;
@@ -1171,7 +1158,7 @@ BlockGeo make_geo(const BlockSpan& sp) {
 void block_alloc(BlockWork& b, int N, size_t ldq, int ncap, int nslots) {
   block_free(b);
   int rpw = 0;
-  const int nch = nchunks_for(N, rpw);
+  const int nch = row_chunks(N, rpw);
   const size_t S = (size_t)nslots;
   b.nslots = nslots;
   b.wstride = ldq * kBlockMax;
@@ -1246,7 +1233,7 @@ void block_step(const BlockSpan& sp, BlockWork& b, const Lattice& lat, const dou
     }
   }
   int rpw = 0;
-  const int nch = nchunks_for(N, rpw);
+  const int nch = row_chunks(N, rpw);
   // more than 8 block vectors: the products in their three-multiplication form
   const bool gauss = sb > 8;
   // launches of several slots: four column tiles per dot wavefront and two
@@ -1284,12 +1271,14 @@ void block_step(const BlockSpan& sp, BlockWork& b, const Lattice& lat, const dou
     prof_launch(prof, K_BRED, (16.0 * (double)nch * nent + 16.0 * nent) * nb, 2.0 * nch * nent * nb, bred_kernel,
                 dim3(nblk * nb), dim3(256), 0, s, g, rd);
   };
-  // rows that a launch keeps on one XCD: the dot pass's chunks, or (packed form)
-  // the workgroup's own 64 rows, whose shares are even on small lattices too.  us
+  // rows that a launch keeps on one XCD: the dot pass's chunks (on lattices where
+  // their columns may still be in the L2; else chunks of about that size, whole
+  // workgroups of 128 rows), or (packed form) the workgroup's own 64 rows, whose
+  // shares are even on small lattices too.  us
   // of a whole apply's updates, chunks / own rows (the former kernels): 4^4 x 16
   // slots, s = 2, 200 columns 5340 / 4580 (4520); 12^4 x 4, s = 4, 240 columns 56.6
   // / 55.5 ms (56.4)
-  const int crows = gauss ? 4 * rpw : upd_rows_wg, uch = (N + crows - 1) / crows;
+  const int crows = gauss ? update_chunk(rpw) : upd_rows_wg, uch = (N + crows - 1) / crows;
   SGN_REQUIRE(crows % upd_rows_wg == 0, SGN_EINVAL, "block step: update rows do not tile the chunk");
   const unsigned ugrid = xcd_grid(nb * (crows / upd_rows_wg), uch);
   // the basis (S once for the launch), W read and written, the coefficients

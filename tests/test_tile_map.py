@@ -65,3 +65,41 @@ def test_every_tile_once_and_even_shares(tmp_path):
     subprocess.run([cxx, "-O1", "-std=c++17", "-I", CSRC, str(src), "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+CHUNKS = r"""
+#include <cstdio>
+#include "tilemap.h"
+
+int main() {
+  for (int V = 16; V <= 200000; V += V < 12000 ? 1 : 7) {
+    const int N = 12 * V;
+    int rpw = 0;
+    const int nch = row_chunks(N, rpw), up = update_chunk(rpw);
+    if (nch < 1 || nch > (N < kSmallRows ? 48 : 128) || rpw % 8 || (long long)nch * 4 * rpw < N ||
+        (long long)(nch - 1) * 4 * rpw >= N)
+      return printf("rows %d: %d chunks of 4 x %d\n", N, nch, rpw), 1;
+    // the update's chunks hold whole workgroups, and are the dot pass's where those do
+    if (up % 128 || up < 4 * rpw || up >= 4 * rpw + 128 || (rpw % 32 == 0 && up != 4 * rpw))
+      return printf("rows %d: update chunks of %d rows\n", N, up), 1;
+    // large lattices: 128 chunks but for rounding their rows up to whole lines, so an XCD takes at most
+    // 16 chunks of 4 (N / 512 + 8) rows, 1 + 4096 / N times an eighth of N
+    if (N > 65536 && 16.0 * 4 * rpw > (1.0 + 4096.0 / N) * N / 8)
+      return printf("rows %d: %d chunks\n", N, nch), 1;
+  }
+  int rpw = 0;
+  if (row_chunks(12 * 20736, rpw) != 128) return printf("12^4: %d rows a wavefront\n", rpw), 1;
+  return 0;
+}
+"""
+
+
+def test_row_chunks(tmp_path):
+    cxx = shutil.which("g++") or shutil.which("clang++")
+    if cxx is None:
+        pytest.skip("no host compiler")
+    src, exe = tmp_path / "c.cpp", tmp_path / "c"
+    src.write_text(CHUNKS)
+    subprocess.run([cxx, "-O1", "-std=c++17", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
