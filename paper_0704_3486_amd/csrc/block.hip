@@ -75,15 +75,22 @@ constexpr int kDot3Tiles = 4;
 constexpr int kFullChip = 512;
 // slots from which a launch takes the wide tiles
 constexpr int kWideFrom = 4;
-// blocks of 16 rows per wavefront of the three-multiplication update pass, and
-// the basis (entries over all slots) from which its wavefronts take whole
-// rows: past the 256 MB of the Infinity Cache, where reading 2048 adjacent
-// bytes of a column per workgroup instead of 256 counts.  us by events, split
-// / whole: 6^4 x 8 slots, 116 columns, 14.5 M entries 50 / 55, 196 columns,
-// 24.5 M 91 / 86, 340 columns 152 / 139; x 4, 340 columns, 21.2 M 73 / 71; x 3,
-// 15.9 M 48 / 55
+// The three-multiplication update pass takes whole rows per wavefront (else a
+// quarter of the columns) in launches of kWholeRows rows over all slots, which
+// fill the chip so and whose short bases leave a quarter few products, and from
+// kWholeEntries entries of basis over all slots on: past the 256 MB of the
+// Infinity Cache, where reading 2048 adjacent bytes of a column per workgroup
+// instead of 256 counts; there a wavefront has kRowBlocks blocks of 16 rows,
+// below one.  us by events, split / whole: 6^4 x 8 slots, 116 columns, 14.5 M
+// entries 50 / 55, 196 columns, 24.5 M 91 / 86, 340 columns 152 / 139; x 4, 340
+// columns, 21.2 M 73 / 71; x 3, 15.9 M 48 / 55.  All updates of a short apply,
+// split / one / two blocks of rows (the former kernel): 12^4 x 4, 32 columns 703 /
+// 598 / 615 us (587), x 1, 48 columns 272 / 250 / 257 (234); 1680 sites x 8, 161280
+// rows, 48 columns 214 / 204 / - (198); 8^4 x 3, 147456 rows, 48 columns 172 / 166 /
+// 176 (167), 300 columns 3.33 / 3.33 / - ms (3.44); 6^4 x 8, 124416 rows, 160 columns
+// 890 / 912 / - us (870); 6^4 x 7 780 / 822 / - (800).
 constexpr int kRowBlocks = 2;
-constexpr double kWholeEntries = 20e6;
+constexpr double kWholeEntries = 20e6, kWholeRows = 1.5e5;
 
 // the composite basis of one launch: column c < m is S[c], column c >= m of
 // slot r is V_r[c - m] (V_r = V + r vstride), all with leading dimension ldq
@@ -1247,10 +1254,13 @@ void block_step(const BlockSpan& sp, BlockWork& b, const Lattice& lat, const dou
   };
   // rows per workgroup of the update pass: whole rows per wavefront, or in
   // small launches the columns split over the wavefronts
-  const bool whole = !gauss || (double)N * nb * p >= kWholeEntries;
-  const int upd_rows_wg = !whole ? 16 : gauss ? 64 * kRowBlocks : 64;
-  void (*upd_kernel)(BlockGeo, BUpd) =
-      !gauss ? bupdate_kernel : whole ? bupdate3_kernel<kRowBlocks> : bupdate3_split_kernel;
+  const bool large = (double)N * nb * p >= kWholeEntries;
+  const bool whole = !gauss || large || (double)N * nb >= kWholeRows;
+  const int upd_rows_wg = !whole ? 16 : gauss && large ? 64 * kRowBlocks : 64;
+  void (*upd_kernel)(BlockGeo, BUpd) = !gauss  ? bupdate_kernel
+                                       : large ? bupdate3_kernel<kRowBlocks>
+                                       : whole ? bupdate3_kernel<1>
+                                               : bupdate3_split_kernel;
   auto dot = [&](double2* C, int ncol, const double2* C1, double2* Ct) {
     const int tiles = tiles_for(ncol);
     void (*dot_kernel)(BlockGeo, BDot) = !gauss       ? bdot_kernel

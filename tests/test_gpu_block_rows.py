@@ -15,7 +15,10 @@ M_W = -1.6
     ((4, 4, 4, 4), 4, 2, 30, 16), ((4, 5, 7, 9), 0, 8, 41, 5), ((3, 5, 7, 11), 2, 6, 37, 9),
     # more than 65536 rows: chunks of the dot pass that are no multiple of the update's rows
     ((7, 11, 7, 11), 0, 7, 44, 3), ((11, 7, 7, 12), 2, 16, 50, 5), ((12, 12, 12, 12), 0, 8, 33, 3),
-    ((12, 12, 12, 12), 0, 16, 49, 2), ((10, 10, 10, 11), 0, 16, 60, 6)])
+    ((12, 12, 12, 12), 0, 16, 49, 2), ((10, 10, 10, 11), 0, 16, 60, 6),
+    # 150000 rows over the sources: whole rows also for short bases (one source: quarters)
+    ((6, 6, 6, 6), 3, 16, 37, 10), ((5, 5, 6, 9), 0, 11, 30, 10), ((3, 3, 7, 11), 0, 13, 29, 18),
+    ((3, 3, 7, 11), 0, 13, 29, 19)])
 def test_every_row_is_updated(dims, m, block, k, nrhs):
     import torch
 
