@@ -1208,21 +1208,23 @@ constexpr size_t kDotWaves = 768, kDotWavesBatch = 2048;
 // four of 450 sites, 60 columns 19.1 / 19.3, 1260 sites, FP32, 420 columns 109 /
 // 79 (82); one of 1260 sites, 120 / 420 / 580 columns 17.3 / 18.1, 43.6 / 43.0,
 // 59.7 / 55.9, of 2640 sites, 60 / 120 / 580 columns 19.4 / 20.0, 29.5 / 28.0,
-// 124 / 101 (108).  Whole / Tiles, FP32: 8 slots of 256 sites, 60 / 120 / 420
+// 124 / 101 (108).  In applies of one source the line lies higher, and higher for
+// FP64: 400 columns, lines at 10000 / 18000: 2352 sites 16.36 / 16.19 ms, FP32 12.81 /
+// 12.85, 1440 sites FP32 10.45 / 10.76.  Whole / Tiles, FP32: 8 slots of 256 sites, 60 / 120 / 420
 // columns 15.2 / 17.4, 22.5 / 20.6, 57.5 / 49.2; FP64: 12 of 200 sites, 60 / 300 /
 // 580 columns 22.3 / 23.4, 65.3 / 61.8, 139 / 124.
 constexpr int kPartSlots = 4;
-constexpr long long kPartWorkOne = 10000, kPartWork = 5000, kWholeWork = 20000, kWholeWork32 = 5000;
+constexpr long long kPartWork = 5000, kPartWorkOne = 18000, kPartWorkOne32 = 10000;
+constexpr long long kWholeWork = 20000, kWholeWork32 = 5000;
 enum class DotForm { Whole, Parts, Tiles };
 template <typename VT>
 static DotForm dot_form(const KrylovWork& w, const KrylovArgs& A) {
+  constexpr bool kF32 = sizeof(VT) == 8;
   const long long work = (long long)w.nrt_dot * A.nb, cols = work * (A.m + A.jmax());
   if (w.nrt_dot <= kParts)
-    return work <= kPartTiles && cols <= (sizeof(VT) == 8 ? kWholeWork32 : kWholeWork) ? DotForm::Whole
-                                                                                       : DotForm::Tiles;
-  if (w.nrt_dot <= kPartTiles && A.nb <= kPartSlots && work <= 2 * kPartTiles &&
-      cols <= (A.nb == 1 ? kPartWorkOne : kPartWork))
-    return DotForm::Parts;
+    return work <= kPartTiles && cols <= (kF32 ? kWholeWork32 : kWholeWork) ? DotForm::Whole : DotForm::Tiles;
+  const long long most = A.nb > 1 ? kPartWork : kF32 ? kPartWorkOne32 : kPartWorkOne;
+  if (w.nrt_dot <= kPartTiles && A.nb <= kPartSlots && work <= 2 * kPartTiles && cols <= most) return DotForm::Parts;
   return DotForm::Tiles;
 }
 

@@ -107,12 +107,12 @@ def _reductions(sg, torch, dims, nrhs, k, prec):
 
 
 # short bases go without the reduction launch (one is left, at the end), long
-# ones with it: from 5000 tiles x slots x columns on in batches (10000 for one
-# source), on lattices of 8 tiles or fewer from 20000 (FP64) and 5000 (FP32)
+# ones with it: from 5000 tiles x slots x columns on in batches (one source: 18000,
+# FP32 10000), on lattices of 8 tiles or fewer from 20000 (FP32 5000)
 @pytest.mark.parametrize("dims,nrhs,k,prec,first", [
     ((5, 6, 7, 8), 2, 120, 0, 63), ((5, 6, 7, 8), 3, 120, 1, 42), ((5, 6, 6, 7), 4, 100, 1, 42),
-    ((6, 7, 7, 8), 1, 220, 0, 179), ((5, 6, 6, 7), 1, 360, 1, 334), ((4, 4, 4, 4), 8, 150, 1, 105),
-    ((4, 4, 4, 5), 8, 330, 0, 313), ((5, 6, 6, 7), 1, 300, 0, 334)])
+    ((6, 7, 7, 8), 1, 350, 0, 322), ((5, 6, 6, 7), 1, 360, 1, 334), ((4, 4, 4, 4), 8, 150, 1, 105),
+    ((4, 4, 4, 5), 8, 330, 0, 313), ((5, 6, 6, 7), 1, 300, 0, 601)])
 def test_long_bases_take_the_reduction(env, dims, nrhs, k, prec, first):
     sg, torch = env
     print("long bases", dims, nrhs, k, prec, flush=True)
