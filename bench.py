@@ -820,10 +820,12 @@ def stored_traffic(kernel):
                         rec = r
     if not rec:
         return None
-    with open(os.path.join(ROOT, rec["source"]), "rb") as f:
-        if hashlib.sha256(f.read()).hexdigest() != rec["source_sha256"]:
-            return None
-    return rec["bytes_per_launch"]
+    sources = rec["source"] if isinstance(rec["source"], list) else [rec["source"]]
+    digest = hashlib.sha256()
+    for name in sources:
+        with open(os.path.join(ROOT, name), "rb") as f:
+            digest.update(f.read())
+    return rec["bytes_per_launch"] if digest.hexdigest() == rec["source_sha256"] else None
 
 
 def stencil_leg(sg, synth, torch, tune=True):
