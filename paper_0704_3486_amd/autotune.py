@@ -9,9 +9,10 @@ context itself (sgn_apply_fixed, or sgn_apply_batched_fixed for several
 sources, at a given Krylov dimension) and keeps the fastest.  On small lattices
 some of the six are the same kernel (the header says which), so the default
 shape stays unless another is faster by more than MARGIN.  The choice is
-recorded in a JSON cache keyed by the kernels' version, lattice, precision,
-deflation size, sources, Krylov dimension and device, so a later process with
-the same key sets it without timing.
+recorded in a JSON cache keyed by lattice, precision, deflation size, sources,
+Krylov dimension and device, so a later process with the same key sets it
+without timing (also one that a former version of the library wrote: the
+results are the same, and deleting the file has the shapes timed anew).
 
 This module only schedules and times calls of the library; all arithmetic
 runs in its kernels.
@@ -31,7 +32,6 @@ UPDATE_BATCH = (4, 8, 16)
 DOT_COLS = (1, 2)
 DEFAULT = (8, 2)  # the library's default shape
 MARGIN = 0.01
-VERSION = "v2"  # of the dot and update kernels that the cached shapes were timed on
 # stencil walk blocks (By, Bz, Bt) tried by autotune_stencil: the default
 # rule, the natural order and blocks around the default
 STENCIL_BLOCKS = ((0, 0, 0), (-1, 0, 0), (4, 16, 2), (4, 16, 8), (4, 8, 8), (8, 8, 2), (8, 8, 4), (2, 8, 4),
@@ -42,8 +42,8 @@ STENCIL_MARGIN = 0.015  # of a short apply, about a quarter of which is stencils
 
 def _key(ctx, nrhs, k, device):
     dims, n = sgn_get_dims(ctx)
-    return "|".join(str(v) for v in (VERSION, "x".join(map(str, dims)), n, sgn_get_precision(ctx),
-                                     sgn_deflation_size(ctx), nrhs, k, device))
+    return "|".join(str(v) for v in ("x".join(map(str, dims)), n, sgn_get_precision(ctx), sgn_deflation_size(ctx),
+                                        nrhs, k, device))
 
 
 def _load(path):

@@ -1,7 +1,5 @@
-"""autotune times shapes that are kernels of their own, keeps the default shape
-unless another is clearly faster, and does not take shapes that were cached for
-other kernels."""
-import json
+"""autotune times shapes that are kernels of their own and keeps the default
+shape unless another is clearly faster."""
 import types
 
 import pytest
@@ -55,18 +53,3 @@ def test_distinct_shapes_and_margin(ctx, monkeypatch):
     shapes = _fake(monkeypatch, at, lambda ub, cpw: 0.9 if (ub, cpw) == (16, 1) else 1.0)
     r = at.autotune(ctx, k=20, reps=1)
     assert (r["update_batch"], r["dot_cols"]) == (16, 1) == shapes[-1]
-
-
-def test_cached_for_other_kernels(ctx, monkeypatch, tmp_path):
-    import torch
-
-    from paper_0704_3486_amd import autotune as at
-
-    print("cache", flush=True)
-    _fake(monkeypatch, at, lambda ub, cpw: 1.0)
-    path = str(tmp_path / "tune.json")
-    old = "|".join(["4x4x4x4", str(12 * 256), "0", "0", "1", "20", torch.cuda.get_device_name()])  # no version
-    with open(path, "w") as f:
-        json.dump({old: {"update_batch": 16, "dot_cols": 4, "ms": 1.0}}, f)
-    assert not at.autotune(ctx, k=20, cache=path, reps=1)["cached"]
-    assert at.autotune(ctx, k=20, cache=path, reps=1)["cached"]
