@@ -36,6 +36,7 @@ namespace {
 
 constexpr int kRpl = 8;                 // dot: rows per lane
 constexpr int kDRows = 64 * kRpl;       // dot: rows per tile (4 wavefronts of CPW columns each)
+static_assert(kDRows == kTileRows, "the tile map's rows");
 constexpr int kUWaves = 8;              // combine (and the default update): wavefronts per 64-row workgroup
 constexpr int kUThreads = 64 * kUWaves;
 constexpr int kCBatch = 8;              // combine: column loads issued together per lane
@@ -302,7 +303,7 @@ __global__ void __launch_bounds__(256) kdot_kernel(KrylovArgs A, int with_z, Col
                                                    int keep) {
   constexpr int R = rows_per_lane<VT>();
   int rt, zb, cg;
-  if (!tile_of<false, false>(blockIdx.x, A.nb * ngroups, A.nb, A.nrt_dot, rt, zb, cg)) return;
+  if (!tile_of<false, false>(blockIdx.x, A.nb * ngroups, A.nb, A.nrt_dot, A.N, rt, zb, cg)) return;
   const int r = slot_of(A, zb);
   const int lane = threadIdx.x & 63, wave = wave_id();
   const int N = A.N, kcols = step_of(A, zb), J = A.m + kcols;
@@ -885,7 +886,7 @@ __global__ void __launch_bounds__(64 * NW, 4) kupdate_kernel(KrylovArgs A, int n
     if (bb >= nh) return;
   } else {
     int sub;
-    if (!tile_of<true, PARTS>(blockIdx.x - nhess, A.nb * kSub, A.nb, A.nrt_dot, rt, zb, sub)) return;
+    if (!tile_of<true, PARTS>(blockIdx.x - nhess, A.nb * kSub, A.nb, A.nrt_dot, A.N, rt, zb, sub)) return;
     bb = rt * kSub + sub;
     if (bb * 64 * R >= A.N) return;
   }
@@ -1297,7 +1298,7 @@ void krylov_dot(const KrylovWork& w, const KrylovArgs& Ain, bool with_z, bool re
     // two by two, 128.7 for two by four, 133.6 for one by one
     const int C = std::min(A.tune.cpw, 2), batches = sizeof(VT) == 16 ? 2 : 4;
     const ColGroups G = groups(4 * C * batches, ngroups);
-    const size_t nwg = tile_grid((size_t)A.nb * ngroups, w.nrt_dot, false);
+    const size_t nwg = tile_grid((size_t)A.nb * ngroups, w.nrt_dot, A.N, false);
     SGN_REQUIRE(nwg * 256 < (size_t(1) << 32), SGN_EINVAL, "krylov: dot grid too large");
     prof_launch(prof, K_KDOT, bytes, flops, C == 1 ? kdot_kernel<VT, 1> : kdot_kernel<VT, 2>, dim3((unsigned)nwg),
                 dim3(256), 0, s, A, with_z ? 1 : 0, G, batches, ngroups, kept_tiles<VT>(w, A));
@@ -1323,7 +1324,7 @@ void krylov_update(const KrylovWork& w, const KrylovArgs& Ain, hipStream_t s, Pr
   check_pairs<VT>(A);
   const unsigned nhess = ((unsigned)nh * A.nb + kXcds - 1) / kXcds * kXcds;
   const bool parts = dot_form<VT>(w, A) == DotForm::Parts;
-  const size_t nwg = nhess + tile_grid((size_t)A.nb * (kDRows / (64 * rows_per_lane<VT>())), w.nrt_dot, parts);
+  const size_t nwg = nhess + tile_grid((size_t)A.nb * (kDRows / (64 * rows_per_lane<VT>())), w.nrt_dot, A.N, parts);
   const int nthr = 64 * A.tune.uw;
   SGN_REQUIRE(nwg * nthr < (size_t(1) << 32), SGN_EINVAL, "krylov: update grid too large");
   const double vb = (double)sizeof(VT);

@@ -18,19 +18,19 @@ DRIVER = r"""
 #include "tilemap.h"
 
 template <bool DOWN, bool BY_XCD>
-int check(int nt, int nb, int nk, double most) {
+int check(int nt, int nb, int nk, double most, int rows) {
   const unsigned per = nb * nk;
-  const size_t grid = tile_grid(per, nt, BY_XCD);
+  const size_t grid = tile_grid(per, nt, rows, BY_XCD);
   std::set<std::tuple<int, int, int>> seen;
   int load[kXcds] = {}, prev = DOWN ? nt : -1;
   for (size_t i = 0; i < grid; ++i) {
     int t = -1, z = -1, in = -1;
-    if (!tile_of<DOWN, BY_XCD>((unsigned)i, per, nb, nt, t, z, in)) continue;
+    if (!tile_of<DOWN, BY_XCD>((unsigned)i, per, nb, nt, rows, t, z, in)) continue;
     if (t < 0 || t >= nt || z < 0 || z >= nb || in < 0 || in >= nk) return 1;
     if (!seen.insert({t, z, in}).second) return 2;
     ++load[i % kXcds];
     // the walk goes by groups of kXcds tiles (dealt out: by tiles)
-    const bool dealt = !BY_XCD && dealt_out(nt);
+    const bool dealt = !BY_XCD && dealt_out(nt, rows);
     const int g = dealt ? t : t / kXcds, p = dealt ? prev : (prev < 0 ? -1 : prev / kXcds);
     if (prev >= 0 && prev < nt && (DOWN ? g > p : g < p)) return 3;
     prev = t;
@@ -45,10 +45,15 @@ int main() {
   for (int nt = 1; nt <= 140; ++nt)
     for (int nb : {1, 2, 3, 5, 8, 64})
       for (int nk : {1, 3, 8}) {
-        // 25 tiles by XCD: four where the share is 3.125
-        int r = check<false, false>(nt, nb, nk, 1.28);
-        if (!r) r = check<true, false>(nt, nb, nk, 1.28);
-        if (!r && nt > kXcds) r = check<true, true>(nt, nb, nk, 8.0);
+        int r = 0;
+        for (int rows : {512 * nt, 512 * nt - 496}) {  // a full last tile, and one of 16 rows
+          // 25 tiles by XCD: four where the share is 3.125
+          if (!r) r = check<false, false>(nt, nb, nk, 1.28, rows);
+          if (!r) r = check<true, false>(nt, nb, nk, 1.28, rows);
+          if (!r && nt > kXcds) r = check<true, true>(nt, nb, nk, 8.0, rows);
+          // up to eight tiles: no XCD idles for the lack of an eighth of the rows
+          if (!r && nt <= kXcds && !dealt_out(nt, rows) && 8 * rows < 7 * kXcds * kTileRows) r = 6;
+        }
         if (r) return printf("tiles %d slots %d index %d: %d\n", nt, nb, nk, r), 1;
       }
   return 0;
