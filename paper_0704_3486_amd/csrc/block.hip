@@ -40,7 +40,7 @@
 // Per slot the arithmetic does not depend on the other slots.
 #include "internal.h"
 #include "context.h"
-#include "tilemap.h"
+#include "rowchunks.h"
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 

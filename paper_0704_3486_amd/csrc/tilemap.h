@@ -1,10 +1,8 @@
-// How the passes over the basis divide its rows: which workgroup of the
-// one-vector step's dot and update passes takes which row tile (512 rows) and
-// launch position, and the row chunks of the block process.  Plain integers, so
-// that the host and a CPU test use the kernels' own map.
+// Which workgroup of the one-vector step's dot and update passes takes which
+// row tile (512 rows) and launch position.  Plain integers, so that the host
+// and a CPU test use the kernels' own map.
 #pragma once
 
-#include <algorithm>
 #include <cstddef>
 
 #ifdef __HIPCC__
@@ -41,8 +39,8 @@ constexpr int kTileRows = 512;
 // XCD: 560 x 8, 580 columns 1.14 times the former kernels' speed, dealt out 1.12;
 // 850 x 8, 60 columns 1.18 and 1.12.
 // Up to eight tiles the rows count, as the last tile may hold few of them: 300
-// sites (seven tiles and 16 rows) x 32, 150 columns 12.78 / 11.9 ms an apply
-// (12.35).
+// sites (seven tiles and 16 rows) x 32, 150 columns 12.6 / 11.7 ms an apply
+// (12.3).
 SGN_MAP_FN bool dealt_out(int ntiles, int rows) {
   if (ntiles <= kXcds) return rows + rows / 8 < kXcds * kTileRows;
   return ntiles < 3 * kXcds && kXcds * ((ntiles + kXcds - 1) / kXcds) > ntiles + ntiles / 4;
@@ -76,21 +74,3 @@ inline size_t tile_grid(size_t per, int ntiles, int rows, bool by_xcd) {
   if (!by_xcd && dealt_out(ntiles, rows)) return per * ntiles;
   return (size_t)kXcds * per * ((ntiles + kXcds - 1) / kXcds);
 }
-
-// The block process's dot pass: rows per wavefront, and its row chunks of four
-// wavefronts.  By N alone (never by the slots, so that a source's sums are the
-// same alone and in a batch): 128 rows, so that the partial sums stay at 3 per
-// cent of the basis, and 64 on lattices whose chunks of 512 rows are too few to
-// fill the chip; at most 128 chunks.  Whole lines of 128 bytes (8 rows), and no
-// coarser, so that 128 chunks of a large lattice stay 128, the same number on
-// every XCD: 12^4 x 4, s = 4, 240 columns, chunks of 1952 / 2048 rows (128 and
-// 122 of them): 51.5 / 53.4 ms of dot passes.  132000 rows x 4, s = 8, chunks of
-// 1056 / 1040 rows (no whole lines): 15.9 / 16.9 ms.
-constexpr int kSmallRows = 12288;  // below: the shorter chunks
-inline int row_chunks(int N, int& rpw) {
-  const int want = (N + 4 * 128 - 1) / (4 * 128);
-  rpw = std::max(N < kSmallRows ? 64 : 128, (want + 7) & ~7);
-  return (N + 4 * rpw - 1) / (4 * rpw);
-}
-// rows of a chunk of the update pass, whose workgroups take 16 to 128 of them
-inline int update_chunk(int rpw) { return (4 * rpw + 127) & ~127; }

@@ -1,5 +1,6 @@
 """The map from workgroups to row tiles of the one-vector step's dot and update
-passes (csrc/tilemap.h), on the CPU: every (tile, launch position, index) is
+passes (csrc/tilemap.h) and the row chunks of the block process
+(csrc/rowchunks.h), on the CPU: every (tile, launch position, index) is
 taken exactly once, workgroups that share a tile stay on one XCD where the map
 keeps them there, and no XCD is left with much more than its share."""
 import os
@@ -74,7 +75,7 @@ def test_every_tile_once_and_even_shares(tmp_path):
 
 CHUNKS = r"""
 #include <cstdio>
-#include "tilemap.h"
+#include "rowchunks.h"
 
 int main() {
   for (int V = 16; V <= 200000; V += V < 12000 ? 1 : 7) {
